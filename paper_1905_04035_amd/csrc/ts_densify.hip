@@ -432,6 +432,14 @@ struct SortParams {
 
 enum { SORT_FUSED = 0, SORT_SCATTER = 2 };
 
+// Wavefront w of copying work-group cw of a sort launch.
+template <int EPI>
+__device__ __forceinline__ void blind_copy(const SortParams& p, int cw, int w, int lane)
+{
+    const int v = p.copy_row0 + (cw * kSortWaves + w) * kBigCopyRows;
+    copy_rows<kBigCopyRows, EPI>(p.copy_in, p.copy_out, 0u, v, p.copy_row1, p.d, lane, p.scale);
+}
+
 // One wavefront walks its sub-slice [a, b) in rounds of kRoundTiles tiles of 64 pairs.
 // All ids of a round are loaded before any is used, so a round costs one memory
 // latency; with a single round (slices of at most 16384 pairs) the ids stay in
@@ -534,6 +542,7 @@ __device__ __forceinline__ void own_pairs(const int32_t (&idr)[kRoundTiles], int
 // with an id outside the vocabulary (p.bad).  One LDS table for the whole work-group: the order
 // of the pairs does not matter here.  It also clears the arrival counters of the reduce kernel,
 // and the work-groups past the counting ones copy dense rows like those of sort_kernel.
+template <int EPI>
 __global__ __launch_bounds__(1024) void count_kernel(SortParams p, ShardTable sh)
 {
     extern __shared__ __align__(16) uint32_t tab[];     // [part]
@@ -544,9 +553,7 @@ __global__ __launch_bounds__(1024) void count_kernel(SortParams p, ShardTable sh
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int nsort = p.G * p.S;
     if ((int)blockIdx.x >= nsort) {
-        const int cw = (int)blockIdx.x - nsort;
-        const int v = p.copy_row0 + (cw * kSortWaves + w) * kBigCopyRows;
-        copy_rows<kBigCopyRows, EPI_NONE>(p.copy_in, p.copy_out, 0u, v, p.copy_row1, p.d, lane, p.scale);
+        blind_copy<EPI>(p, (int)blockIdx.x - nsort, w, lane);
         return;
     }
     const int g = (int)blockIdx.x % p.G;
@@ -712,9 +719,7 @@ __global__ __launch_bounds__(1024) void sort_kernel(SortParams p, ShardTable sh)
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int nsort = p.G * p.S;
     if ((int)blockIdx.x >= nsort) {
-        const int cw = (int)blockIdx.x - nsort;
-        const int v = p.copy_row0 + (cw * kSortWaves + w) * kBigCopyRows;
-        copy_rows<kBigCopyRows, EPI>(p.copy_in, p.copy_out, 0u, v, p.copy_row1, p.d, lane, p.scale);
+        blind_copy<EPI>(p, (int)blockIdx.x - nsort, w, lane);
         return;
     }
     const int g = (int)blockIdx.x % p.G;
@@ -1783,6 +1788,18 @@ int static_scratch(void** out)
 // The three kinds of launches, one instantiation per epilogue (the epilogue is a template
 // argument so that the plain path keeps its code).
 template <int EPI>
+void launch_count(dim3 grid, size_t lds, hipStream_t stream, const SortParams& sp, const ShardTable& sh)
+{
+    hipLaunchKernelGGL((count_kernel<EPI>), grid, dim3(1024), lds, stream, sp, sh);
+}
+
+template <int EPI>
+void launch_sort_scatter(dim3 grid, size_t lds, hipStream_t stream, const SortParams& sp, const ShardTable& sh)
+{
+    hipLaunchKernelGGL((sort_kernel<SORT_SCATTER, EPI>), grid, dim3(1024), lds, stream, sp, sh);
+}
+
+template <int EPI>
 void launch_sort_fused(dim3 grid, size_t lds, hipStream_t stream, const SortParams& sp, const ShardTable& sh)
 {
     hipLaunchKernelGGL((sort_kernel<SORT_FUSED, EPI>), grid, dim3(1024), lds, stream, sp, sh);
@@ -1885,8 +1902,12 @@ int densify_impl(const ShardTable& sh, int64_t n, int32_t row_dtype, int32_t d, 
     const int64_t budget_multi = pl.S <= 4 ? (32ll << 20) : (pl.S <= 6 ? (16ll << 20) : 0);
     const int64_t budget = g_overlap_sort >= 0 ? g_overlap_sort
                                                : (pl.S == 1 ? budget_single : budget_multi);
-    int64_t rows_per_launch = (in_place || (pl.S > 1 && epi != EPI_NONE)) ? 0 : budget / ((int64_t)8 * d);
-    rows_per_launch = rows_per_launch / (kBigCopyRows * kSortWaves) * (kBigCopyRows * kSortWaves);
+    // The budget counts the bytes that a copied row really moves: without a dense operand it is only
+    // written, and a bf16 result is half as long (V = 33801, d = 1024, without a dense operand: 4987 pairs
+    // 33.0 -> 32.0 us, 16384 pairs 42.8 -> 40.5; two or three times the rows per work-group 32.4-32.8 / 41.2-43.9).
+    const int64_t row_bytes = (int64_t)d * ((dense_in ? 4 : 0) + (epi == EPI_SCALE_BF16 ? 2 : 4));
+    const int64_t wg_rows = (int64_t)kBigCopyRows * kSortWaves;
+    int64_t rows_per_launch = in_place ? 0 : budget / row_bytes / wg_rows * wg_rows;
     // A work-group of these launches holds a compute unit (1024 threads, most of the LDS).  Where the
     // default budget comes to a little less than one work-group per compute unit in all, make it exactly
     // one: fewer leave compute units idle, and a few more than one leave a second round of stragglers
@@ -1894,7 +1915,6 @@ int densify_impl(const ShardTable& sh, int64_t n, int32_t row_dtype, int32_t d, 
     // 2048-12800 pairs 1-2 % faster than 136-178 do, and 208 cost 1.5 us more than 192 at 16384 pairs).
     if (pl.S == 1 && g_overlap_sort < 0 && rows_per_launch > 0) {
         const int64_t cus = compute_units();
-        const int64_t wg_rows = kBigCopyRows * kSortWaves;
         const int64_t all = pl.G + rows_per_launch / wg_rows;
         if (cus > pl.G && 4 * all >= 3 * cus && all < cus) rows_per_launch = (cus - pl.G) * wg_rows;
     }
@@ -1904,7 +1924,7 @@ int densify_impl(const ShardTable& sh, int64_t n, int32_t row_dtype, int32_t d, 
         q.copy_row0 = copy_done;
         q.copy_row1 = (int32_t)(copy_done + rows_per_launch < tail0 ? copy_done + rows_per_launch : tail0);
         copy_done = q.copy_row1;
-        return dim3((unsigned)(pl.G * pl.S + (q.copy_row1 - q.copy_row0 + kBigCopyRows * kSortWaves - 1) / (kBigCopyRows * kSortWaves)));
+        return dim3((unsigned)(pl.G * pl.S + (q.copy_row1 - q.copy_row0 + wg_rows - 1) / wg_rows));
     };
     sp.copy_in = dense_in;
     sp.copy_out = dense_out;
@@ -1917,9 +1937,9 @@ int densify_impl(const ShardTable& sh, int64_t n, int32_t row_dtype, int32_t d, 
         TS_DISPATCH_EPI(epi, launch_sort_fused, g1, lds, stream, sp, sh);
     } else {
         const dim3 g1 = sort_grid(sp);
-        hipLaunchKernelGGL(count_kernel, g1, dim3(1024), (size_t)pl.part * sizeof(uint32_t), stream, sp, sh);
+        TS_DISPATCH_EPI(epi, launch_count, g1, (size_t)pl.part * sizeof(uint32_t), stream, sp, sh);
         const dim3 g2 = sort_grid(sp);
-        hipLaunchKernelGGL((sort_kernel<SORT_SCATTER, EPI_NONE>), g2, dim3(1024), lds, stream, sp, sh);
+        TS_DISPATCH_EPI(epi, launch_sort_scatter, g2, lds, stream, sp, sh);
     }
     if (hipGetLastError() != hipSuccess) return TS_ERR_HIP;
 
