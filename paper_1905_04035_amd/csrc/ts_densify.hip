@@ -83,7 +83,6 @@ static_assert(sizeof(SortedPair) == 32, "two 16-byte accesses per record");
 
 constexpr int kMaxPart = 2048;     // most ids one sort work-group owns (LDS: 18 x part x 4 B + 8 KiB of lists = 152 KiB)
 constexpr int kMinPart = 128;
-constexpr int kBigCopyRows = 2;    // rows per wavefront in the copying work-groups of 1024 threads
 constexpr int kSortWaves = 16;     // wavefronts per sort work-group
 constexpr int kColBlock = 256;     // fp32 columns per wavefront item (64 lanes x 4)
 constexpr int kMaxSlices = 64;
@@ -271,62 +270,60 @@ __device__ __forceinline__ void store_out(void* out, size_t idx, f4 v, float sca
     }
 }
 
-// One wavefront copies the dense rows v0 .. v0 + R - 1 that lie below vend, except those whose
-// bit is set in `skip` (bit r: row v0 + r): all loads of all rows are issued before the first store.
-template <int R, int EPI>
-__device__ __forceinline__ void copy_rows(const float* dense_in, void* dense_out, uint32_t skip,
-                                          int v0, int vend, int d, int lane, float scale)
+// One wavefront copies the elements [e, e + 2048) that lie below e_end, from dense_in to the output: the
+// copies beside the sort take whole rows, one behind the other, so where a row ends does not matter
+// here.  All loads are issued before the first store.  (Two rows per wavefront, as it used to be, is the
+// same 8 KiB at d = 1024 but a fraction of it in narrow rows: V = 32768, d = 512, 8192 pairs, the
+// launch had 320 copying work-groups and now has 192, one per compute unit that does not sort: call
+// 30.4 -> 29.9 us; V = 20000, d = 2048, 9000 pairs 75.6 -> 73.0.  Loads that are the same for every lane, with
+// the index clamped, cost 1.3 us at d = 1024 and 1.4 us at d = 512: beside the sort gentler copies are better.)
+constexpr int kBlindElems = 2048;
+
+template <int EPI>
+__device__ __forceinline__ void copy_flat(const float* dense_in, void* dense_out, int64_t e, int64_t e_end, int lane,
+                                          float scale)
 {
-    bool go[R];
-    bool any = false;
+    constexpr int U = kBlindElems / kColBlock;
+    if (e >= e_end) return;
+    const int rest = (int)min(e_end - e, (int64_t)kBlindElems);
+    f4 x[U];
+    if (dense_in) {
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        go[r] = v0 + r < vend && !((skip >> r) & 1u);
-        any = any || go[r];
-    }
-    if (!any) return;
-    for (int c0 = 0; c0 < d; c0 += 4 * kColBlock) {
-        f4 x[R][4];
-#pragma unroll
-        for (int r = 0; r < R; ++r)
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int col = c0 + u * kColBlock + lane * 4;
-                x[r][u] = (f4)(0.0f);
-                if (go[r] && dense_in && col < d) x[r][u] = load_f4_stream(dense_in + (size_t)(v0 + r) * d + col);
-            }
-        // With an epilogue every value is transformed before the first store is issued: a
-        // multiply placed between two stores makes the compiler wait for the earlier store
-        // (the empty asm statements keep it from moving the arithmetic down to the stores).
-        u2 packed[R][4];
-        if constexpr (EPI != EPI_NONE) {
-#pragma unroll
-            for (int r = 0; r < R; ++r)
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    x[r][u] = x[r][u] * scale;
-                    if constexpr (EPI == EPI_SCALE_BF16) {
-                        packed[r][u].x = bf16_rne(x[r][u].x) | (bf16_rne(x[r][u].y) << 16);
-                        packed[r][u].y = bf16_rne(x[r][u].z) | (bf16_rne(x[r][u].w) << 16);
-                        asm volatile("" : "+v"(packed[r][u]));
-                    } else {
-                        asm volatile("" : "+v"(x[r][u]));
-                    }
-                }
+        for (int u = 0; u < U; ++u) {
+            const int i = u * kColBlock + lane * 4;
+            x[u] = (f4)(0.0f);
+            if (i < rest) x[u] = load_f4_stream(dense_in + e + i);
         }
+    } else {
 #pragma unroll
-        for (int r = 0; r < R; ++r)
+        for (int u = 0; u < U; ++u) x[u] = (f4)(0.0f);
+    }
+    // With an epilogue every value is transformed before the first store is issued: a
+    // multiply placed between two stores makes the compiler wait for the earlier store
+    // (the empty asm statements keep it from moving the arithmetic down to the stores).
+    u2 packed[U];
+    if constexpr (EPI != EPI_NONE) {
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int col = c0 + u * kColBlock + lane * 4;
-                if (go[r] && col < d) {
-                    const size_t idx = (size_t)(v0 + r) * d + col;
-                    if constexpr (EPI == EPI_SCALE_BF16)
-                        __builtin_nontemporal_store(packed[r][u], reinterpret_cast<u2*>(reinterpret_cast<uint16_t*>(dense_out) + idx));
-                    else
-                        store_f4_stream(reinterpret_cast<float*>(dense_out) + idx, x[r][u]);
-                }
+        for (int u = 0; u < U; ++u) {
+            x[u] = x[u] * scale;
+            if constexpr (EPI == EPI_SCALE_BF16) {
+                packed[u].x = bf16_rne(x[u].x) | (bf16_rne(x[u].y) << 16);
+                packed[u].y = bf16_rne(x[u].z) | (bf16_rne(x[u].w) << 16);
+                asm volatile("" : "+v"(packed[u]));
+            } else {
+                asm volatile("" : "+v"(x[u]));
             }
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int i = u * kColBlock + lane * 4;
+        if (i < rest) {
+            if constexpr (EPI == EPI_SCALE_BF16)
+                __builtin_nontemporal_store(packed[u], reinterpret_cast<u2*>(reinterpret_cast<uint16_t*>(dense_out) + e + i));
+            else
+                store_f4_stream(reinterpret_cast<float*>(dense_out) + e + i, x[u]);
+        }
     }
 }
 
@@ -346,7 +343,7 @@ __device__ __forceinline__ void copy_chunk(const float* dense_in, void* dense_ou
 #pragma unroll
         for (int u = 0; u < 4; ++u) x[u] = (f4)(0.0f);
     }
-    // every value is transformed before the first store is issued, as in copy_rows
+    // every value is transformed before the first store is issued, as in copy_flat
     u2 packed[4];
     if constexpr (EPI != EPI_NONE) {
 #pragma unroll
@@ -363,7 +360,7 @@ __device__ __forceinline__ void copy_chunk(const float* dense_in, void* dense_ou
     }
     // One wait for all loads: the stores sit in blocks of their own (not every lane stores), and the
     // compiler would wait at each of them for everything before it, the store before it included.
-    // (In the copies beside the sort, copy_rows, that chain of stores is left as it is: there it
+    // (In the copies beside the sort, copy_flat, that chain of stores is left as it is: there it
     // measured 0.7-1 us faster per launch, the sort's own loads wait less behind gentler copies.)
     wait_vm_all();
 #pragma unroll
@@ -377,6 +374,44 @@ __device__ __forceinline__ void copy_chunk(const float* dense_in, void* dense_ou
                 store_f4_stream(reinterpret_cast<float*>(dense_out) + idx, x[u]);
         }
     }
+}
+
+// Narrow rows: one wavefront takes the R = 1024 / d (at most 64) rows from v0 on, which lie one behind
+// the other, and copies those that received no pair.  The lane's four elements at u * 256 + 4 * lane
+// belong to row elem * row_magic >> 20 (row_magic = ceil(2^20 / d): exact for elements below 1024 and d
+// below 1028).  One row per wavefront moves 4 d bytes for a chain of two latencies and leaves lanes
+// idle below 256 columns: V = 100000, 8000 pairs 46.9 -> 40.1 us at d = 256, 29.8 -> 20.3 at d = 64; V = 130000,
+// d = 256, 100000 pairs 113.3 -> 102.4.  A lane without anything to copy reads the first untouched row again.
+template <int EPI>
+__device__ __forceinline__ void copy_narrow(const int32_t* count, const float* dense_in, void* dense_out, int v0,
+                                            int rows, uint32_t row_magic, int d, int lane, float scale)
+{
+    const bool untouched = lane < rows && count[v0 + min(lane, rows - 1)] == 0;
+    const uint64_t todo = ballot64(untouched);
+    if (!todo) return;
+    const size_t base = (size_t)v0 * d;
+    const int first = (int)__builtin_ctzll(todo) * d, end = rows * d;
+    f4 x[4];
+    int at[4];
+    bool go[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int i = u * kColBlock + lane * 4;
+        const uint32_t r = ((uint32_t)i * row_magic) >> 20;
+        go[u] = i < end && ((todo >> (r & 63u)) & 1ull);
+        at[u] = go[u] ? i : first;
+    }
+    if (dense_in) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) x[u] = load_f4_stream(dense_in + base + at[u]);
+    } else {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) x[u] = (f4)(0.0f);
+    }
+    wait_vm_all();          // one wait for all loads, as in copy_chunk
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+        if (go[u]) store_out<EPI>(dense_out, base + at[u], x[u], scale);
 }
 
 // ------------------------------------------------------------------ shard table
@@ -421,12 +456,12 @@ struct SortParams {
     int32_t* n_bad;
     int32_t* arrive;    // arrival counters of the reduce kernel, cleared here (arrive_vec 16-byte words)
     int32_t arrive_vec;
-    // Work-groups past the sorting ones copy dense rows [copy_row0, copy_row1) to the output
+    // Work-groups past the sorting ones copy the elements [copy_e0, copy_e1) (whole rows) to the output
     // without knowing yet which rows receive pairs (the reduce kernel, which runs after,
     // overwrites those).  It keeps HBM busy while the latency-bound sort runs.
     const float* copy_in;
     void* copy_out;
-    int32_t copy_row0, copy_row1, d;
+    int64_t copy_e0, copy_e1;
     float scale;
 };
 
@@ -436,8 +471,8 @@ enum { SORT_FUSED = 0, SORT_SCATTER = 2 };
 template <int EPI>
 __device__ __forceinline__ void blind_copy(const SortParams& p, int cw, int w, int lane)
 {
-    const int v = p.copy_row0 + (cw * kSortWaves + w) * kBigCopyRows;
-    copy_rows<kBigCopyRows, EPI>(p.copy_in, p.copy_out, 0u, v, p.copy_row1, p.d, lane, p.scale);
+    const int64_t e = p.copy_e0 + (int64_t)(cw * kSortWaves + w) * kBlindElems;
+    copy_flat<EPI>(p.copy_in, p.copy_out, e, p.copy_e1, lane, p.scale);
 }
 
 // One wavefront walks its sub-slice [a, b) in rounds of kRoundTiles tiles of 64 pairs.
@@ -936,7 +971,8 @@ struct ReduceParams {
     void* dense_out;
     float scale;
     int32_t copy_untouched;     // 0: rows without pairs are left as they are (in place, no epilogue)
-    int32_t row_chunks;         // a wavefront of those work-groups takes 1024 columns of a row: chunks per row
+    int32_t row_chunks;         // a wavefront of those work-groups takes 1024 columns of a row: chunks per row;
+                                // negative: it takes -row_chunks narrow rows, and only copies
     // the rest
     const int32_t* row_start;
     const SortedPair* sorted;
@@ -947,6 +983,7 @@ struct ReduceParams {
                                 // slot 2g + 1 its share of a row that begins in it and goes on beyond it
     int32_t* arrive;            // [levels][2 * groups][ncb] arrival counters, all zero when the launch starts
     int32_t logC, logG;         // log2 C; log2 of the sorted positions of a group of pieces
+    uint32_t row_magic;         // ceil(2^20 / d), where row_chunks < 0
 };
 
 constexpr int kGroupPieces = 4;     // pieces per work-group of the reduce kernel, one per wavefront
@@ -1370,6 +1407,15 @@ __global__ __launch_bounds__(256) void reduce_kernel(ReduceParams p)
         // one wavefront per row and chunk of 1024 columns (wider rows: several wavefronts, so that
         // no wavefront has to work through its row chunk after chunk)
         const int item = ((int)blockIdx.x - p.n_piece_groups) * kGroupPieces + wave;
+        if constexpr (!SHORT) {
+            if (p.row_chunks < 0) {
+                const int v0 = p.row0 - item * p.row_chunks;
+                if (v0 < p.V)
+                    copy_narrow<EPI>(p.count, p.dense_in, p.dense_out, v0, min(-p.row_chunks, p.V - v0), p.row_magic, p.d,
+                                     lane, p.scale);
+                return;
+            }
+        }
         int v = p.row0 + item, c0 = 0;
         if (p.row_chunks > 1) {
             const int r = item / p.row_chunks;
@@ -1890,15 +1936,18 @@ int densify_impl(const ShardTable& sh, int64_t n, int32_t row_dtype, int32_t d, 
     const bool in_place = (const void*)dense_in == (const void*)dense_out;
     const bool skip_untouched = in_place && epi == EPI_NONE;
     // Rows copied by the sort launches: about as many bytes as HBM moves while a sort runs
-    // (measured defaults).  One slice: 32 MiB plus 1 MiB per 1024 pairs up to 16384 pairs, 2.5 MiB
-    // per 1024 pairs beyond (the wavefronts then walk their shares in several rounds).  A sort
+    // (measured defaults).  One slice: 32 MiB plus 1 MiB per 1024 pairs up to 16384 pairs, 1.25 MiB
+    // per 1024 pairs beyond (the wavefronts then walk their shares in several rounds).  With 2.5 MiB, as it
+    // used to be, too many rows were copied that receive pairs: V = 32768, d = 1024, 40000 pairs 86.5 us (now
+    // 84.9; 32 / 48 / 112 MiB 89.8 / 88.1 / 86.5), 51200 pairs 95.3 (94.3; 99.6 / 98.3 / 94.3); d = 512,
+    // 40000 pairs 51.5 (48.4; 52.2 / 49.9 / 51.5).  A sort
     // of a few slices leaves compute units idle, and a smaller blind copy beside
     // each of its two launches still pays (+4 % at 3-4 slices); a sort of many slices keeps the
     // whole GPU busy by itself (a copying work-group beside every sorting one lengthens the sort
     // by more than the copy is worth), and with that many pairs a large share of the rows
     // copied blindly would be overwritten: no blind copy then.
     const int64_t budget_single = n <= 16384 ? (32ll << 20) + (n / 1024 << 20)
-                                             : (48ll << 20) + (n - 16384) / 1024 * (5ll << 19);
+                                             : (48ll << 20) + (n - 16384) / 1024 * (5ll << 18);
     const int64_t budget_multi = pl.S <= 4 ? (32ll << 20) : (pl.S <= 6 ? (16ll << 20) : 0);
     const int64_t budget = g_overlap_sort >= 0 ? g_overlap_sort
                                                : (pl.S == 1 ? budget_single : budget_multi);
@@ -1906,29 +1955,29 @@ int densify_impl(const ShardTable& sh, int64_t n, int32_t row_dtype, int32_t d, 
     // written, and a bf16 result is half as long (V = 33801, d = 1024, without a dense operand: 4987 pairs
     // 33.0 -> 32.0 us, 16384 pairs 42.8 -> 40.5; two or three times the rows per work-group 32.4-32.8 / 41.2-43.9).
     const int64_t row_bytes = (int64_t)d * ((dense_in ? 4 : 0) + (epi == EPI_SCALE_BF16 ? 2 : 4));
-    const int64_t wg_rows = (int64_t)kBigCopyRows * kSortWaves;
-    int64_t rows_per_launch = in_place ? 0 : budget / row_bytes / wg_rows * wg_rows;
+    const int64_t wg_elems = (int64_t)kBlindElems * kSortWaves;
+    int64_t copy_wgs = in_place ? 0 : budget / (row_bytes / d * wg_elems);
     // A work-group of these launches holds a compute unit (1024 threads, most of the LDS).  Where the
     // default budget comes to a little less than one work-group per compute unit in all, make it exactly
     // one: fewer leave compute units idle, and a few more than one leave a second round of stragglers
     // (measured on 256 compute units, d = 1024: 192 copying work-groups beside 64 sorting ones take
     // 2048-12800 pairs 1-2 % faster than 136-178 do, and 208 cost 1.5 us more than 192 at 16384 pairs).
-    if (pl.S == 1 && g_overlap_sort < 0 && rows_per_launch > 0) {
+    if (pl.S == 1 && g_overlap_sort < 0 && copy_wgs > 0) {
         const int64_t cus = compute_units();
-        const int64_t all = pl.G + rows_per_launch / wg_rows;
-        if (cus > pl.G && 4 * all >= 3 * cus && all < cus) rows_per_launch = (cus - pl.G) * wg_rows;
+        const int64_t all = pl.G + copy_wgs;
+        if (cus > pl.G && 4 * all >= 3 * cus && all < cus) copy_wgs = cus - pl.G;
     }
-    const int32_t tail0 = V;
+    const int64_t rows_per_launch = copy_wgs * wg_elems / d;
     int32_t copy_done = 0;
     auto sort_grid = [&](SortParams& q) {
-        q.copy_row0 = copy_done;
-        q.copy_row1 = (int32_t)(copy_done + rows_per_launch < tail0 ? copy_done + rows_per_launch : tail0);
-        copy_done = q.copy_row1;
-        return dim3((unsigned)(pl.G * pl.S + (q.copy_row1 - q.copy_row0 + wg_rows - 1) / wg_rows));
+        const int32_t row1 = (int32_t)(copy_done + rows_per_launch < V ? copy_done + rows_per_launch : V);
+        q.copy_e0 = (int64_t)copy_done * d;
+        q.copy_e1 = (int64_t)row1 * d;
+        copy_done = row1;
+        return dim3((unsigned)(pl.G * pl.S + (q.copy_e1 - q.copy_e0 + wg_elems - 1) / wg_elems));
     };
     sp.copy_in = dense_in;
     sp.copy_out = dense_out;
-    sp.d = d;
     sp.scale = scale;
     sp.list_cap = pl.list_cap;
     const size_t lds = ((size_t)(kSortWaves + 2) * pl.part + (size_t)kSortWaves * sp.list_cap) * sizeof(uint32_t);
@@ -1972,8 +2021,13 @@ int densify_impl(const ShardTable& sh, int64_t n, int32_t row_dtype, int32_t d, 
     if (rp.short_max > 0 && kGroupPieces * pl.C <= 64) rp.n_piece_groups = (pl.NBG + 3) / 4 * rp.ncb;
     // after the work-groups of the pieces, one wavefront for every output row that may need one
     rp.row0 = rp.short_max > 0 ? 0 : (skip_untouched ? V : copy_done);
-    rp.row_chunks = (d + 4 * kColBlock - 1) / (4 * kColBlock);
-    const unsigned rgrid = (unsigned)(rp.n_piece_groups + ((int64_t)(V - rp.row0) * rp.row_chunks + kGroupPieces - 1) / kGroupPieces);
+    // rows of at most 512 columns that are only copied: as many as make up 1024 columns per wavefront (below)
+    const int32_t wave_rows = rp.short_max == 0 && d <= 512 ? (1024 / d < 64 ? 1024 / d : 64) : 1;
+    const int32_t chunks = (d + 4 * kColBlock - 1) / (4 * kColBlock);
+    rp.row_chunks = wave_rows > 1 ? -wave_rows : chunks;
+    rp.row_magic = (uint32_t)(((1 << 20) + d - 1) / d);
+    const int64_t row_items = ((int64_t)(V - rp.row0) + wave_rows - 1) / wave_rows * chunks;
+    const unsigned rgrid = (unsigned)(rp.n_piece_groups + (row_items + kGroupPieces - 1) / kGroupPieces);
 
     const bool prof = g_prof_used < g_prof_cap && rgrid > 0;
     hipEvent_t ev_begin = prof ? g_ev[2 * g_prof_used] : nullptr;
@@ -1987,7 +2041,7 @@ int densify_impl(const ShardTable& sh, int64_t n, int32_t row_dtype, int32_t d, 
     g_last_V = V;
     g_last_info[0] = pl.C;
     g_last_info[1] = copy_done;
-    g_last_info[2] = tail0;
+    g_last_info[2] = V;
     g_last_info[3] = pl.S;
     g_last_info[4] = pl.part;
     g_last_info[5] = pl.NB;
