@@ -962,7 +962,7 @@ __global__ __launch_bounds__(1024) void sort_kernel(SortParams p, ShardTable sh)
 struct ReduceParams {
     // the first 64 bytes: all that a wavefront which copies a row needs
     int32_t V, d, C, ncb;
-    int32_t n_piece_groups;     // work-groups that sum pieces: (groups of kGroupPieces pieces) x column blocks
+    int32_t n_piece_groups;     // work-groups that sum pieces: (groups of pieces) x column blocks
     int32_t row0;               // the work-groups after them take the rows from here on, one per wavefront
     int32_t short_max;          // rows with at most this many pairs are added up row by row (0 or C)
     int32_t copy_row0;          // untouched rows below this one have been copied by the sort launches
@@ -986,8 +986,9 @@ struct ReduceParams {
     uint32_t row_magic;         // ceil(2^20 / d), where row_chunks < 0
 };
 
-constexpr int kGroupPieces = 4;     // pieces per work-group of the reduce kernel, one per wavefront
-constexpr int kLogGroupPieces = 2;
+// Pieces per work-group of the reduce kernel, one per wavefront: 64 sorted positions with pieces of 8
+// or 16, 128 with pieces of 32.
+constexpr __host__ __device__ int group_pieces(int C) { return C <= 8 ? 8 : 4; }
 
 // Fixed-order combine of a row that spans several work-groups, inside the launch that made
 // the shares (a share: what one work-group's pieces hold of the row, already added up in
@@ -1196,7 +1197,7 @@ __device__ __forceinline__ void short_row(const ReduceParams& p, int v, int c0, 
 }
 
 // Where short rows are added up row by row, the long rows are added up by wavefronts that
-// work alone: one wavefront takes a whole group of kGroupPieces pieces (4C sorted positions)
+// work alone: one wavefront takes a whole group of pieces (64 sorted positions)
 // and one block of columns, walks the pieces one after the other and keeps in registers
 // what the work-group form keeps in LDS.  The sums are the same, in the same order: a piece's
 // pairs in sorted order, the pieces of the group in order; a row that lies inside the group is
@@ -1210,7 +1211,7 @@ __device__ __forceinline__ void group_wave(const ReduceParams& p, int kg, int cb
     constexpr int BATCH = 16;                   // value rows in flight together
     constexpr int NW = 1;                       // windows of 64 sorted positions
     const int C = p.C;
-    const int G = C << kLogGroupPieces;          // sorted positions of the group (at most 64)
+    const int G = 1 << p.logG;                   // sorted positions of the group (at most 64)
     const int gpos0 = kg << p.logG;
     const int col = (cb * kColBlock + lane * 4) * NV;
     const bool colok = col < p.d;
@@ -1341,7 +1342,7 @@ __device__ __forceinline__ void group_wave(const ReduceParams& p, int kg, int cb
                                 }
                             } else {
                                 // the group's share of a row that began before it or goes on beyond it
-                                const int kg0 = (sj >> p.logC) >> kLogGroupPieces;
+                                const int kg0 = sj >> p.logG;
                                 const size_t slot = share_slot(kg0, kg - kg0);
                                 if (colok) {
 #pragma unroll
@@ -1376,7 +1377,7 @@ __device__ __forceinline__ void group_wave(const ReduceParams& p, int kg, int cb
 // NV: 16-byte fp32 vectors per lane (a wavefront of a piece covers 256 * NV columns); BATCH:
 // sorted positions whose rows are loaded together.
 //
-// Output rows with more than C pairs are added up by pieces.  A work-group takes kGroupPieces
+// Output rows with more than C pairs are added up by pieces.  A work-group takes GP
 // consecutive pieces of C sorted positions, one per wavefront, and one block of columns.  A
 // wavefront adds up the pairs of such a row that lie in its piece and leaves the sum in LDS.
 // After one barrier the wavefront that holds a row's last piece within the work-group adds
@@ -1392,13 +1393,13 @@ __device__ __forceinline__ void group_wave(const ReduceParams& p, int kg, int cb
 // SHORT = 1 (pieces of at most 16 positions) the long rows go to wavefronts that work alone
 // (group_wave) instead of the work-groups described here.  The order of additions, and so
 // every bit of the result, is the same in all three.
-template <typename RowT, int NV, int BATCH, int EPI, int SHORT>
-__global__ __launch_bounds__(256) void reduce_kernel(ReduceParams p)
+template <typename RowT, int NV, int BATCH, int EPI, int SHORT, int GP>
+__global__ __launch_bounds__(64 * GP) void reduce_kernel(ReduceParams p)
 {
     // SHORT: 0 short rows in the pieces; 1 row by row, long rows by lone wavefronts (group_wave);
     // 2 row by row, long rows by the work-groups below
     // [wavefront][0: of a row that began before the piece, 1: of a row that begins in it][vector][lane]
-    __shared__ f4 chain[SHORT == 1 ? 1 : kGroupPieces][2][NV][64];
+    __shared__ f4 chain[SHORT == 1 ? 1 : GP][2][NV][64];
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1406,7 +1407,7 @@ __global__ __launch_bounds__(256) void reduce_kernel(ReduceParams p)
     if ((int)blockIdx.x >= p.n_piece_groups) {
         // one wavefront per row and chunk of 1024 columns (wider rows: several wavefronts, so that
         // no wavefront has to work through its row chunk after chunk)
-        const int item = ((int)blockIdx.x - p.n_piece_groups) * kGroupPieces + wave;
+        const int item = ((int)blockIdx.x - p.n_piece_groups) * GP + wave;
         if constexpr (!SHORT) {
             if (p.row_chunks < 0) {
                 const int v0 = p.row0 - item * p.row_chunks;
@@ -1459,7 +1460,7 @@ __global__ __launch_bounds__(256) void reduce_kernel(ReduceParams p)
     // ---- piece k: sorted positions [pos0, pos0 + C), columns [cb*256*NV, (cb+1)*256*NV)
     const int kg = (int)blockIdx.x / p.ncb;
     const int cb = (int)blockIdx.x - kg * p.ncb;
-    const int k = kg * kGroupPieces + wave;
+    const int k = kg * GP + wave;
     const int col = (cb * kColBlock + lane * 4) * NV;
     const bool colok = col < p.d;
     const int C = p.C;
@@ -1569,7 +1570,7 @@ __global__ __launch_bounds__(256) void reduce_kernel(ReduceParams p)
     // it, one that begins in it).  The wavefront with the row's last piece inside the
     // work-group adds the work-group's pieces of the row, in piece order.
     uint64_t cuts = Lm & ~W;
-    const int g_first = kg * kGroupPieces, g_last = g_first + kGroupPieces - 1;
+    const int g_first = kg * GP, g_last = g_first + GP - 1;
     CutRef ref[2];
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
@@ -1610,7 +1611,7 @@ __global__ __launch_bounds__(256) void reduce_kernel(ReduceParams p)
                     }
                 } else {
                     // the work-group's share of a row that goes beyond it
-                    const int kg0 = piece_first >> kLogGroupPieces;
+                    const int kg0 = sj >> p.logG;
                     const size_t slot = share_slot(kg0, kg - kg0);
                     if (colok) {
 #pragma unroll
@@ -1717,6 +1718,33 @@ int piece_tokens_for(int64_t n, bool wide_bf16)
     return (wide_bf16 || n <= kPieceSmallMax) ? 16 : 32;
 }
 
+// Calls that add up their short rows in the pieces: pieces of 8 positions instead of 16 (a workspace of the
+// same size: groups of pieces are 64 positions either way).  A piece's window is then 16 positions, and all
+// its value rows are in flight at once: the launch of a call with few pairs is as long as a wavefront's
+// chain of batches.  But work-groups of eight wavefronts (and twice as many of them) suit a launch that mostly copies
+// or mostly gathers less.  fp32 rows, us with 8 / 16: d = 1024 in place, 3000 pairs 14.7 / 15.7, 8000 pairs 22.8 /
+// 22.3; V = 4000, d = 256, 2000 pairs 13.1 / 14.9, 20000 pairs 24.0 / 22.9; V = 16000, d = 512, 8000 pairs 23.8 / 25.5;
+// V = 32768, d = 512, 8192 pairs 30.1 / 28.0.  bf16 rows (half the bytes per row, half the work-groups), V = 32768: d = 512,
+// 12000 pairs 30.7 / 33.9, 24000 pairs 38.5 / 41.3; d = 1024, 24000 pairs 63.9 / 63.3; d = 256, 100000 pairs 49.7 / 45.6.
+bool pieces_of_8(int64_t n, int32_t d, int32_t V, int32_t row_dtype, bool wide, bool in_place)
+{
+    const int64_t cols = d < kColBlock ? kColBlock : d;
+    if (wide) return d <= 512 && n <= 32768 && (in_place || (int64_t)V * d <= 20 << 20);
+    return row_dtype == TS_ROW_FP32 && n * cols <= 9 << 19 && (in_place || (int64_t)V * d <= 12 << 20);
+}
+
+// ... and twice as many value rows in flight per wavefront (32-64 registers more, so fewer wavefronts): not
+// where narrow rows come in large numbers, and not where the launch has nothing to copy beside a large
+// gather.  us with 16 / 8 fp32 rows in flight, V = 32768: d = 1024, 16384 pairs 58.5 / 59.7, without a dense
+// operand 38.1 / 39.2, 25000 pairs 70.0 / 71.5; d = 512, 8192 pairs 28.0 / 29.7; d = 128, 30000 pairs 24.8 / 25.0, 100000 pairs
+// 40.4 / 39.1; d = 64, 200000 pairs 66.2 / 58.6; in place d = 1024, 4000 pairs 16.7 / 17.5, 16384 pairs 32.4 / 31.8.
+// bf16 rows, 8 / 4 in flight: d = 1024, 12000 pairs 52.7 / 55.4; d = 64, 200000 pairs 65.5 / 61.6.
+bool deep_batches(int64_t n, int32_t d, bool in_place)
+{
+    if (d < kColBlock && n > 65536) return false;
+    return !(in_place && n * d > 8 << 20);
+}
+
 // bound: size the arrays that depend on how the sort is split (slices, parts) for the largest
 // split any call of at most n pairs and at most V rows can choose, so that the total never
 // shrinks when n or V grows.
@@ -1759,9 +1787,9 @@ void make_plan(int64_t n, int32_t d, int32_t V, int32_t C, Plan* pl, bool bound 
     pl->G = (V + part - 1) / part;
     pl->C = C;
     pl->NB = (int32_t)((n + pl->C - 1) / pl->C);
-    // a work-group of the reduce kernel takes kGroupPieces pieces; the shares of a row that spans several
+    // a work-group of the reduce kernel takes a group of pieces; the shares of a row that spans several
     // work-groups are added up in a tree with a fan-in of 16: levels needed for a row that spans them all
-    pl->NBG = (pl->NB + kGroupPieces - 1) / kGroupPieces;
+    pl->NBG = (pl->NB + group_pieces(pl->C) - 1) / group_pieces(pl->C);
     pl->levels = 1;
     for (int64_t reach = kFanIn; reach < pl->NBG; reach *= kFanIn) ++pl->levels;
     pl->ncb = (d + kColBlock - 1) / kColBlock;
@@ -1854,38 +1882,43 @@ void launch_sort_fused(dim3 grid, size_t lds, hipStream_t stream, const SortPara
 // With events (benchmarks only) the launch goes through the variant that stamps them with the
 // kernel's own begin and end, so that their difference is the kernel's duration.
 template <typename Kernel>
-void launch_timed(Kernel kernel, unsigned grid, hipStream_t stream, hipEvent_t begin, hipEvent_t end,
+void launch_timed(Kernel kernel, unsigned grid, int threads, hipStream_t stream, hipEvent_t begin, hipEvent_t end,
                   const ReduceParams& rp)
 {
     if (begin)
-        hipExtLaunchKernelGGL(kernel, dim3(grid), dim3(256), 0, stream, begin, end, 0, rp);
+        hipExtLaunchKernelGGL(kernel, dim3(grid), dim3(threads), 0, stream, begin, end, 0, rp);
     else
-        hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), 0, stream, rp);
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), 0, stream, rp);
 }
 
-template <int EPI, int SHORT>
+// DEEP: sixteen (bf16 rows read 16 bytes per lane: eight) value rows in flight per wavefront, else half.
+template <int EPI, int SHORT, int GP, bool DEEP>
 void launch_reduce_as(unsigned grid, bool wide, int32_t row_dtype, hipStream_t stream, hipEvent_t begin,
                       hipEvent_t end, const ReduceParams& rp)
 {
     if (wide)
-        launch_timed(reduce_kernel<uint16_t, 2, 4, EPI, SHORT>, grid, stream, begin, end, rp);
+        launch_timed(reduce_kernel<uint16_t, 2, DEEP ? 8 : 4, EPI, SHORT, GP>, grid, 64 * GP, stream, begin, end, rp);
     else if (row_dtype == TS_ROW_BF16)
-        launch_timed(reduce_kernel<uint16_t, 1, 8, EPI, SHORT>, grid, stream, begin, end, rp);
+        launch_timed(reduce_kernel<uint16_t, 1, 8, EPI, SHORT, GP>, grid, 64 * GP, stream, begin, end, rp);
     else
-        launch_timed(reduce_kernel<float, 1, 8, EPI, SHORT>, grid, stream, begin, end, rp);
+        launch_timed(reduce_kernel<float, 1, DEEP ? 16 : 8, EPI, SHORT, GP>, grid, 64 * GP, stream, begin, end, rp);
 }
 
 template <int EPI>
-void launch_reduce(unsigned grid, bool wide, int32_t row_dtype, hipStream_t stream, hipEvent_t begin,
+void launch_reduce(unsigned grid, bool wide, bool deep, int32_t row_dtype, hipStream_t stream, hipEvent_t begin,
                    hipEvent_t end, const ReduceParams& rp)
 {
     // short rows row by row: long rows by lone wavefronts where a group of pieces fits the lanes of one
-    if (rp.short_max > 0 && kGroupPieces * rp.C > 64)
-        launch_reduce_as<EPI, 2>(grid, wide, row_dtype, stream, begin, end, rp);
+    if (rp.short_max > 0 && rp.logG > 6)
+        launch_reduce_as<EPI, 2, 4, false>(grid, wide, row_dtype, stream, begin, end, rp);
     else if (rp.short_max > 0)
-        launch_reduce_as<EPI, 1>(grid, wide, row_dtype, stream, begin, end, rp);
+        launch_reduce_as<EPI, 1, 4, false>(grid, wide, row_dtype, stream, begin, end, rp);
+    else if (rp.C <= 8)
+        launch_reduce_as<EPI, 0, 8, true>(grid, wide, row_dtype, stream, begin, end, rp);
+    else if (deep)
+        launch_reduce_as<EPI, 0, 4, true>(grid, wide, row_dtype, stream, begin, end, rp);
     else
-        launch_reduce_as<EPI, 0>(grid, wide, row_dtype, stream, begin, end, rp);
+        launch_reduce_as<EPI, 0, 4, false>(grid, wide, row_dtype, stream, begin, end, rp);
 }
 
 #define TS_DISPATCH_EPI(epi, fn, ...)                              \
@@ -1901,8 +1934,15 @@ int densify_impl(const ShardTable& sh, int64_t n, int32_t row_dtype, int32_t d, 
                  void* ws_v, int64_t ws_bytes)
 {
     const bool wide = row_dtype == TS_ROW_BF16 && (d % 8) == 0;     // 16-byte loads of bf16 rows
+    const bool in_place = (const void*)dense_in == (const void*)dense_out;
+    // Output rows with at most C pairs: with many pairs in the call they are added up row by row, by the
+    // wavefronts that would otherwise copy the row; with few, the pieces take them along.
+    const bool by_row = g_short_rows < 0 ? n >= short_rows_from(d, V, row_dtype == TS_ROW_BF16) : g_short_rows == 1;
+    int32_t C = piece_tokens_for(n, wide);
+    if (!g_piece_override && !by_row && pieces_of_8(n, d, V, row_dtype, wide, in_place)) C = 8;
+    const bool deep = deep_batches(n, d, in_place);
     Plan pl;
-    make_plan(n, d, V, piece_tokens_for(n, wide), &pl);
+    make_plan(n, d, V, C, &pl);
     if (!ws_v || (int64_t)pl.total > ws_bytes) return TS_ERR_WORKSPACE;
     if ((int64_t)pl.NB * pl.ncb + (int64_t)V * ((d + 4 * kColBlock - 1) / (4 * kColBlock)) >= ((int64_t)1 << 31) - 8)
         return TS_ERR_OVERFLOW;
@@ -1933,7 +1973,6 @@ int densify_impl(const ShardTable& sh, int64_t n, int32_t row_dtype, int32_t d, 
     // In place, the plain path leaves untouched rows alone.  With an epilogue they still have
     // to be scaled, by the item that reads them; only the copy made before the pairs are
     // sorted must go, because the reduce kernel would read scaled values.
-    const bool in_place = (const void*)dense_in == (const void*)dense_out;
     const bool skip_untouched = in_place && epi == EPI_NONE;
     // Rows copied by the sort launches: about as many bytes as HBM moves while a sort runs
     // (measured defaults).  One slice: 32 MiB plus 1 MiB per 1024 pairs up to 16384 pairs, 1.25 MiB
@@ -2009,16 +2048,15 @@ int densify_impl(const ShardTable& sh, int64_t n, int32_t row_dtype, int32_t d, 
     rp.arrive = sp.arrive;
     rp.nslots = 2 * pl.NBG;
     rp.logC = __builtin_ctz((unsigned)pl.C);
-    rp.logG = rp.logC + kLogGroupPieces;
+    const int gp = group_pieces(pl.C);
+    rp.logG = rp.logC + (gp == 8 ? 3 : 2);
     rp.copy_row0 = copy_done;
     rp.copy_untouched = skip_untouched ? 0 : 1;
     rp.row_start = sp.row_start;
-    // Output rows with at most C pairs: with many pairs in the call they are added up row by row, by the
-    // wavefronts that would otherwise copy the row; with few, the pieces take them along.
-    rp.short_max = (g_short_rows < 0 ? n >= short_rows_from(d, V, row_dtype == TS_ROW_BF16) : g_short_rows == 1) ? pl.C : 0;
-    // ... and, with pieces of at most 16 positions, their long rows by wavefronts that work alone, four groups
+    rp.short_max = by_row ? pl.C : 0;
+    // with pieces of at most 16 positions, the long rows by wavefronts that work alone, four groups
     // of pieces to a work-group
-    if (rp.short_max > 0 && kGroupPieces * pl.C <= 64) rp.n_piece_groups = (pl.NBG + 3) / 4 * rp.ncb;
+    if (rp.short_max > 0 && rp.logG <= 6) rp.n_piece_groups = (pl.NBG + 3) / 4 * rp.ncb;
     // after the work-groups of the pieces, one wavefront for every output row that may need one
     rp.row0 = rp.short_max > 0 ? 0 : (skip_untouched ? V : copy_done);
     // rows of at most 512 columns that are only copied: as many as make up 1024 columns per wavefront (below)
@@ -2027,12 +2065,13 @@ int densify_impl(const ShardTable& sh, int64_t n, int32_t row_dtype, int32_t d, 
     rp.row_chunks = wave_rows > 1 ? -wave_rows : chunks;
     rp.row_magic = (uint32_t)(((1 << 20) + d - 1) / d);
     const int64_t row_items = ((int64_t)(V - rp.row0) + wave_rows - 1) / wave_rows * chunks;
-    const unsigned rgrid = (unsigned)(rp.n_piece_groups + (row_items + kGroupPieces - 1) / kGroupPieces);
+    const int wg_waves = rp.short_max > 0 ? 4 : gp;
+    const unsigned rgrid = (unsigned)(rp.n_piece_groups + (row_items + wg_waves - 1) / wg_waves);
 
     const bool prof = g_prof_used < g_prof_cap && rgrid > 0;
     hipEvent_t ev_begin = prof ? g_ev[2 * g_prof_used] : nullptr;
     hipEvent_t ev_end = prof ? g_ev[2 * g_prof_used + 1] : nullptr;
-    if (rgrid > 0) TS_DISPATCH_EPI(epi, launch_reduce, rgrid, wide, row_dtype, stream, ev_begin, ev_end, rp);
+    if (rgrid > 0) TS_DISPATCH_EPI(epi, launch_reduce, rgrid, wide, deep, row_dtype, stream, ev_begin, ev_end, rp);
     if (prof) ++g_prof_used;
     if (hipGetLastError() != hipSuccess) return TS_ERR_HIP;
 
@@ -2048,7 +2087,7 @@ int densify_impl(const ShardTable& sh, int64_t n, int32_t row_dtype, int32_t d, 
     g_last_info[6] = pl.levels;
     // bit 0: in place; bits 1-2: how short rows were added up (0 in the pieces, 1 row by row with the long
     // rows by lone wavefronts, 2 row by row with the long rows by work-groups)
-    g_last_info[7] = (in_place ? 1 : 0) | ((rp.short_max == 0 ? 0 : (kGroupPieces * rp.C <= 64 ? 1 : 2)) << 1);
+    g_last_info[7] = (in_place ? 1 : 0) | ((rp.short_max == 0 ? 0 : (rp.logG <= 6 ? 1 : 2)) << 1);
     g_have_last = true;
     return TS_OK;
 }
