@@ -87,6 +87,7 @@ constexpr int kSortWaves = 16;     // wavefronts per sort work-group
 constexpr int kColBlock = 256;     // fp32 columns per wavefront item (64 lanes x 4)
 constexpr int kMaxSlices = 64;
 constexpr int kSliceTokens = 16384;
+constexpr int kRangeSliceTokens = 8192;     // slices of a sort that owns few parts of the ids
 constexpr int kFusedSortMax = 57344;   // up to here one launch sorts everything (measured against two launches)
 constexpr int kPieceSmallMax = 96256;  // up to here pieces of 16 positions, above 32 (bf16 rows read 16 bytes
                                        // per lane: always 16) -- measured: equal up to 25600 pairs, 16 ahead by
@@ -984,6 +985,7 @@ struct ReduceParams {
     int32_t* arrive;            // [levels][2 * groups][ncb] arrival counters, all zero when the launch starts
     int32_t logC, logG;         // log2 C; log2 of the sorted positions of a group of pieces
     uint32_t row_magic;         // ceil(2^20 / d), where row_chunks < 0
+    int32_t part_owned;         // the call owns a range of the ids: most groups of pieces may be empty
 };
 
 // Pieces per work-group of the reduce kernel, one per wavefront: 64 sorted positions with pieces of 8
@@ -1453,12 +1455,16 @@ __global__ __launch_bounds__(64 * GP) void reduce_kernel(ReduceParams p)
             cb = b - kq * p.ncb;
         }
         const int kg = kq * 4 + wave;
+        if (p.part_owned && (kg << p.logG) >= *p.n_valid) return;
         if (kg < p.nslots / 2) group_wave<RowT, NV, EPI>(p, kg, cb, lane);
         return;
     }
 
     // ---- piece k: sorted positions [pos0, pos0 + C), columns [cb*256*NV, (cb+1)*256*NV)
     const int kg = (int)blockIdx.x / p.ncb;
+    // a range's groups beyond its pairs, most of them: out before the records are asked for (one eighth of
+    // 32768 ids, 131072 pairs: 41.3 -> 39.1 us; where all pairs are owned the question would be one latency more)
+    if (p.part_owned && (kg << p.logG) >= *p.n_valid) return;
     const int cb = (int)blockIdx.x - kg * p.ncb;
     const int k = kg * GP + wave;
     const int col = (cb * kColBlock + lane * 4) * NV;
@@ -1748,8 +1754,12 @@ bool deep_batches(int64_t n, int32_t d, bool in_place)
 // bound: size the arrays that depend on how the sort is split (slices, parts) for the largest
 // split any call of at most n pairs and at most V rows can choose, so that the total never
 // shrinks when n or V grows.
-void make_plan(int64_t n, int32_t d, int32_t V, int32_t C, Plan* pl, bool bound = false)
+// group: sorted positions of a group of pieces (0: as many as go with C).  range_cus: of a call that owns
+// a range of the vocabulary, the compute units of the GPU (0: slices as for a whole vocabulary).
+void make_plan(int64_t n, int32_t d, int32_t V, int32_t C, Plan* pl, bool bound = false, int32_t group = 0,
+               int32_t range_cus = 0)
 {
+    if (group == 0) group = C * group_pieces(C);
     if (n <= kFusedSortMax) {
         pl->S = 1;
         pl->SL = (int32_t)align_up((size_t)(n > 0 ? n : 1), 1024);
@@ -1789,7 +1799,7 @@ void make_plan(int64_t n, int32_t d, int32_t V, int32_t C, Plan* pl, bool bound 
     pl->NB = (int32_t)((n + pl->C - 1) / pl->C);
     // a work-group of the reduce kernel takes a group of pieces; the shares of a row that spans several
     // work-groups are added up in a tree with a fan-in of 16: levels needed for a row that spans them all
-    pl->NBG = (pl->NB + group_pieces(pl->C) - 1) / group_pieces(pl->C);
+    pl->NBG = (int32_t)((n + group - 1) / group);
     pl->levels = 1;
     for (int64_t reach = kFanIn; reach < pl->NBG; reach *= kFanIn) ++pl->levels;
     pl->ncb = (d + kColBlock - 1) / kColBlock;
@@ -1822,6 +1832,24 @@ void make_plan(int64_t n, int32_t d, int32_t V, int32_t C, Plan* pl, bool bound 
     pl->off_partial = o;
     o = align_up(o + (size_t)2 * pl->NBG * (size_t)d * 4, 256);
     pl->total = o;
+    const int64_t S = (n + kRangeSliceTokens - 1) / kRangeSliceTokens;
+    if (pl->S > 1 && S > pl->S && S <= kMaxSlices && S * pl->G <= range_cus) {
+        // A range has few parts, so slices of 16384 pairs leave most compute units without a work-group while
+        // the others look at every pair of their slice: smaller slices, as long as every work-group still
+        // has a compute unit.  The tables are done with before the first share of a long row is stored, so they
+        // may take that place too: the workspace stays what it was, and a call whose tables don't fit keeps
+        // its slices.  (32768 ids, d = 1024, 131072 pairs, with slices of 16384 / 8192 / 4096: 4097 rows 39.1 / 37.8 /
+        // 37.6 us, 8192 rows 50.5 / 49.5 / 49.3; 4097 rows at d = 64, 200000 pairs 34.7 / 33.3 / 34.7.  A quarter of 100000
+        // ids has 25 parts: 10 slices instead of 8 cost 40.0 -> 44.2, more work-groups than compute units.)
+        const size_t below = align_up(pl->off_tot + (size_t)S * ids_tab * 4, 256);
+        const size_t bad = align_up(below + (size_t)S * G_tab * 4, 256);
+        if (bad + (size_t)S * 4 <= pl->total) {
+            pl->S = (int32_t)S;
+            pl->SL = kRangeSliceTokens;
+            pl->off_below = below;
+            pl->off_bad = bad;
+        }
+    }
 }
 
 int check_hip(hipError_t e) { return e == hipSuccess ? TS_OK : TS_ERR_HIP; }
@@ -1913,7 +1941,7 @@ void launch_reduce(unsigned grid, bool wide, bool deep, int32_t row_dtype, hipSt
         launch_reduce_as<EPI, 2, 4, false>(grid, wide, row_dtype, stream, begin, end, rp);
     else if (rp.short_max > 0)
         launch_reduce_as<EPI, 1, 4, false>(grid, wide, row_dtype, stream, begin, end, rp);
-    else if (rp.C <= 8)
+    else if (rp.logG - rp.logC == 3)
         launch_reduce_as<EPI, 0, 8, true>(grid, wide, row_dtype, stream, begin, end, rp);
     else if (deep)
         launch_reduce_as<EPI, 0, 4, true>(grid, wide, row_dtype, stream, begin, end, rp);
@@ -1937,12 +1965,18 @@ int densify_impl(const ShardTable& sh, int64_t n, int32_t row_dtype, int32_t d, 
     const bool in_place = (const void*)dense_in == (const void*)dense_out;
     // Output rows with at most C pairs: with many pairs in the call they are added up row by row, by the
     // wavefronts that would otherwise copy the row; with few, the pieces take them along.
-    const bool by_row = g_short_rows < 0 ? n >= short_rows_from(d, V, row_dtype == TS_ROW_BF16) : g_short_rows == 1;
+    // What counts is the pairs that the call will own: of a range, about its share of the vocabulary.  (One
+    // eighth of 32768 ids, 131072 bf16 pairs, d = 1024: with short rows in the pieces 37.7 us, by row 42.)
+    const bool range = V < V_total;
+    const int64_t n_own = range ? (int64_t)((double)n * V / V_total) + 1 : n;
+    const bool by_row = g_short_rows < 0 ? n_own >= short_rows_from(d, V, row_dtype == TS_ROW_BF16) : g_short_rows == 1;
+    // The groups of pieces, and with them the workspace, go by all pairs.
     int32_t C = piece_tokens_for(n, wide);
-    if (!g_piece_override && !by_row && pieces_of_8(n, d, V, row_dtype, wide, in_place)) C = 8;
-    const bool deep = deep_batches(n, d, in_place);
+    const int32_t group = C * group_pieces(C);
+    if (!g_piece_override && !by_row && group == 64 && pieces_of_8(n_own, d, V, row_dtype, wide, in_place)) C = 8;
+    const bool deep = deep_batches(n_own, d, in_place);
     Plan pl;
-    make_plan(n, d, V, C, &pl);
+    make_plan(n, d, V, C, &pl, false, group, range ? compute_units() : 0);
     if (!ws_v || (int64_t)pl.total > ws_bytes) return TS_ERR_WORKSPACE;
     if ((int64_t)pl.NB * pl.ncb + (int64_t)V * ((d + 4 * kColBlock - 1) / (4 * kColBlock)) >= ((int64_t)1 << 31) - 8)
         return TS_ERR_OVERFLOW;
@@ -1987,7 +2021,8 @@ int densify_impl(const ShardTable& sh, int64_t n, int32_t row_dtype, int32_t d, 
     // copied blindly would be overwritten: no blind copy then.
     const int64_t budget_single = n <= 16384 ? (32ll << 20) + (n / 1024 << 20)
                                              : (48ll << 20) + (n - 16384) / 1024 * (5ll << 18);
-    const int64_t budget_multi = pl.S <= 4 ? (32ll << 20) : (pl.S <= 6 ? (16ll << 20) : 0);
+    const int64_t slices = (n + kSliceTokens - 1) / kSliceTokens;      // a range may have more, smaller ones
+    const int64_t budget_multi = slices <= 4 ? (32ll << 20) : (slices <= 6 ? (16ll << 20) : 0);
     const int64_t budget = g_overlap_sort >= 0 ? g_overlap_sort
                                                : (pl.S == 1 ? budget_single : budget_multi);
     // The budget counts the bytes that a copied row really moves: without a dense operand it is only
@@ -2047,9 +2082,10 @@ int densify_impl(const ShardTable& sh, int64_t n, int32_t row_dtype, int32_t d, 
     rp.partial = (float*)(ws + pl.off_partial);
     rp.arrive = sp.arrive;
     rp.nslots = 2 * pl.NBG;
+    rp.part_owned = range;
     rp.logC = __builtin_ctz((unsigned)pl.C);
-    const int gp = group_pieces(pl.C);
-    rp.logG = rp.logC + (gp == 8 ? 3 : 2);
+    rp.logG = group == 128 ? 7 : 6;
+    const int gp = group / pl.C;
     rp.copy_row0 = copy_done;
     rp.copy_untouched = skip_untouched ? 0 : 1;
     rp.row_start = sp.row_start;
