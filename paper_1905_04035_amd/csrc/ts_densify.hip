@@ -1745,10 +1745,12 @@ bool pieces_of_8(int64_t n, int32_t d, int32_t V, int32_t row_dtype, bool wide, 
 // operand 38.1 / 39.2, 25000 pairs 70.0 / 71.5; d = 512, 8192 pairs 28.0 / 29.7; d = 128, 30000 pairs 24.8 / 25.0, 100000 pairs
 // 40.4 / 39.1; d = 64, 200000 pairs 66.2 / 58.6; in place d = 1024, 4000 pairs 16.7 / 17.5, 16384 pairs 32.4 / 31.8.
 // bf16 rows, 8 / 4 in flight: d = 1024, 12000 pairs 52.7 / 55.4; d = 64, 200000 pairs 65.5 / 61.6.
-bool deep_batches(int64_t n, int32_t d, bool in_place)
+// Few rows for many pairs is a gather too: V = 3713, d = 256, 212086 bf16 pairs 69.1 / 65.7, V = 3080, d = 316, 65536 fp32
+// pairs 60.5 / 58.4, V = 4000, d = 1024, 20000 pairs 36.8 / 36.2, but V = 8000 40.1 / 40.4.
+bool deep_batches(int64_t n, int32_t d, int32_t V, bool in_place)
 {
     if (d < kColBlock && n > 65536) return false;
-    return !(in_place && n * d > 8 << 20);
+    return !((in_place || n > 4 * (int64_t)V) && n * d > 8 << 20);
 }
 
 // bound: size the arrays that depend on how the sort is split (slices, parts) for the largest
@@ -1974,7 +1976,7 @@ int densify_impl(const ShardTable& sh, int64_t n, int32_t row_dtype, int32_t d, 
     int32_t C = piece_tokens_for(n, wide);
     const int32_t group = C * group_pieces(C);
     if (!g_piece_override && !by_row && group == 64 && pieces_of_8(n_own, d, V, row_dtype, wide, in_place)) C = 8;
-    const bool deep = deep_batches(n_own, d, in_place);
+    const bool deep = deep_batches(n_own, d, V, in_place);
     Plan pl;
     make_plan(n, d, V, C, &pl, false, group, range ? compute_units() : 0);
     if (!ws_v || (int64_t)pl.total > ws_bytes) return TS_ERR_WORKSPACE;
@@ -2082,7 +2084,7 @@ int densify_impl(const ShardTable& sh, int64_t n, int32_t row_dtype, int32_t d, 
     rp.partial = (float*)(ws + pl.off_partial);
     rp.arrive = sp.arrive;
     rp.nslots = 2 * pl.NBG;
-    rp.part_owned = range;
+    rp.part_owned = range && pl.S > 1;      // few pairs: few groups, and the question costs more (16.4 -> 16.8 us)
     rp.logC = __builtin_ctz((unsigned)pl.C);
     rp.logG = group == 128 ? 7 : 6;
     const int gp = group / pl.C;
