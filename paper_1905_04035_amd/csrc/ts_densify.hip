@@ -22,7 +22,7 @@
 //                   table per work-group, no lists) fills a [slice][id] table first.
 //                   The sort leaves one 32-byte record per sorted pair.
 //   reduce_kernel   the HBM-bound kernel.  First the work-groups that add value rows: each
-//                   takes four consecutive pieces of C sorted positions (one per wavefront)
+//                   takes four (C = 8: eight) consecutive pieces of C sorted positions (one per wavefront)
 //                   and one block of 256 columns.  The pieces of a row with more than C
 //                   pairs are added up through LDS by the wavefront that holds the row's
 //                   last piece in the work-group.  A row that spans several work-groups
