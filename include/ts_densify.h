@@ -31,7 +31,9 @@
  *   - Sums are fp32.  Within one output row the pairs are added in input order
  *     inside fixed-size pieces, the pieces are combined in a fixed order and
  *     dense_in is added last; no floating-point atomics are used, so the same
- *     inputs give the same bits on every run.
+ *     inputs give the same bits on every run.  The size of the pieces follows from
+ *     the number of pairs, d, V and the row type alone: the same bits in place and
+ *     out of place, from one buffer and from shards.
  *   - Return value: TS_OK or a ts_status; it covers only what the host can check
  *     (arguments, workspace, launch errors).
  *   - One call at a time per process: calls share the bound workspace, and the library

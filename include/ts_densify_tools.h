@@ -61,8 +61,9 @@ int ts_profile_end(float* ms_out, int32_t capacity, int32_t* n_out);
 
 /*
  * Tuning.  piece_tokens: sorted positions handled by one wavefront item of the
- * row-reduce kernel (8, 16 or 32; 0 = choose from n and the row type).  Changes the fixed
- * summation order (still deterministic) and the workspace size.
+ * row-reduce kernel (8, 16 or 32; 0 = choose from the pairs of the call, d, the vocabulary and the
+ * row type, whatever the other settings and the other arguments are).  Changes the fixed summation
+ * order (still deterministic); pieces of 32 also need a smaller workspace than pieces of 8 or 16.
  */
 int ts_set_piece_tokens(int32_t piece_tokens);
 

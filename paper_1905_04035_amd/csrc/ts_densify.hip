@@ -1724,19 +1724,21 @@ int piece_tokens_for(int64_t n, bool wide_bf16)
     return (wide_bf16 || n <= kPieceSmallMax) ? 16 : 32;
 }
 
-// Calls that add up their short rows in the pieces: pieces of 8 positions instead of 16 (a workspace of the
-// same size: groups of pieces are 64 positions either way).  A piece's window is then 16 positions, and all
-// its value rows are in flight at once: the launch of a call with few pairs is as long as a wavefront's
-// chain of batches.  But work-groups of eight wavefronts (and twice as many of them) suit a launch that mostly copies
-// or mostly gathers less.  fp32 rows, us with 8 / 16: d = 1024 in place, 3000 pairs 14.7 / 15.7, 8000 pairs 22.8 /
-// 22.3; V = 4000, d = 256, 2000 pairs 13.1 / 14.9, 20000 pairs 24.0 / 22.9; V = 16000, d = 512, 8000 pairs 23.8 / 25.5;
-// V = 32768, d = 512, 8192 pairs 30.1 / 28.0.  bf16 rows (half the bytes per row, half the work-groups), V = 32768: d = 512,
-// 12000 pairs 30.7 / 33.9, 24000 pairs 38.5 / 41.3; d = 1024, 24000 pairs 63.9 / 63.3; d = 256, 100000 pairs 49.7 / 45.6.
-bool pieces_of_8(int64_t n, int32_t d, int32_t V, int32_t row_dtype, bool wide, bool in_place)
+// Few pairs: pieces of 8 positions instead of 16 (a workspace of the same size: groups of pieces are 64 positions
+// either way).  A piece's window is then 16 positions, and all its value rows are in flight at once: the launch of
+// a call with few pairs is as long as a wavefront's chain of batches.  But work-groups of eight wavefronts (and twice
+// as many of them) suit a launch that mostly copies or mostly gathers less.  fp32 rows, us with 8 / 16: V = 4000, d = 256,
+// 2000 pairs 13.1 / 14.9, 20000 pairs 24.0 / 22.9; V = 16000, d = 512, 8000 pairs 23.8 / 25.5; V = 32768, d = 512, 8192 pairs
+// 30.1 / 28.0.  bf16 rows (half the bytes per row, half the work-groups), V = 32768: d = 512, 12000 pairs 30.7 / 33.9, 24000
+// pairs 38.5 / 41.3; d = 1024, 24000 pairs 63.9 / 63.3; d = 256, 100000 pairs 49.7 / 45.6.
+// The length of the pieces fixes the order of additions, so it goes by the pairs, the width, the row type and the
+// whole vocabulary alone: what only spreads the work (in place or not, short rows in the pieces or row by
+// row, the range that a call owns) must not change a bit.  In these limits no call goes row by row unless forced to.
+bool pieces_of_8(int64_t n, int32_t d, int32_t V_total, int32_t row_dtype, bool wide)
 {
     const int64_t cols = d < kColBlock ? kColBlock : d;
-    if (wide) return d <= 512 && n <= 32768 && (in_place || (int64_t)V * d <= 20 << 20);
-    return row_dtype == TS_ROW_FP32 && n * cols <= 9 << 19 && (in_place || (int64_t)V * d <= 12 << 20);
+    if (wide) return d <= 512 && n <= 32768 && (int64_t)V_total * d <= 20 << 20;
+    return row_dtype == TS_ROW_FP32 && n * cols <= 9 << 19 && (int64_t)V_total * d <= 12 << 20;
 }
 
 // ... and twice as many value rows in flight per wavefront (32-64 registers more, so fewer wavefronts): not
@@ -1975,7 +1977,7 @@ int densify_impl(const ShardTable& sh, int64_t n, int32_t row_dtype, int32_t d, 
     // The groups of pieces, and with them the workspace, go by all pairs.
     int32_t C = piece_tokens_for(n, wide);
     const int32_t group = C * group_pieces(C);
-    if (!g_piece_override && !by_row && group == 64 && pieces_of_8(n_own, d, V, row_dtype, wide, in_place)) C = 8;
+    if (!g_piece_override && group == 64 && pieces_of_8(n, d, V_total, row_dtype, wide)) C = 8;
     const bool deep = deep_batches(n_own, d, V, in_place);
     Plan pl;
     make_plan(n, d, V, C, &pl, false, group, range ? compute_units() : 0);
