@@ -2017,14 +2017,19 @@ int densify_impl(const ShardTable& sh, int64_t n, int32_t row_dtype, int32_t d, 
     // per 1024 pairs beyond (the wavefronts then walk their shares in several rounds).  With 2.5 MiB, as it
     // used to be, too many rows were copied that receive pairs: V = 32768, d = 1024, 40000 pairs 86.5 us (now
     // 84.9; 32 / 48 / 112 MiB 89.8 / 88.1 / 86.5), 51200 pairs 95.3 (94.3; 99.6 / 98.3 / 94.3); d = 512,
-    // 40000 pairs 51.5 (48.4; 52.2 / 49.9 / 51.5).  A sort
+    // 40000 pairs 51.5 (48.4; 52.2 / 49.9 / 51.5).  Where a wavefront's share of the pairs holds the begin of a
+    // shard, though, it looks up every id of the share in the shard table and the sort launch takes 2-10 us
+    // longer: 2.5 MiB there.  V = 32768, d = 1024, 2.5 / 1.25: 57000 pairs in 2 / 4 / 8 shards 101.9 / 106.3, 105.6 / 111.1,
+    // 109.3 / 114.9 us (in one 100.9 / 99.9), 40000 in 3 shards 85.3 / 88.7; 28000 in 4 of bf16 rows 64.2 / 66.0.  A sort
     // of a few slices leaves compute units idle, and a smaller blind copy beside
     // each of its two launches still pays (+4 % at 3-4 slices); a sort of many slices keeps the
     // whole GPU busy by itself (a copying work-group beside every sorting one lengthens the sort
     // by more than the copy is worth), and with that many pairs a large share of the rows
     // copied blindly would be overwritten: no blind copy then.
+    bool cut_share = false;
+    for (int j = 1; j < sh.k; ++j) cut_share |= sh.off[j] < n && sh.off[j] % (pl.SL / kSortWaves) != 0;
     const int64_t budget_single = n <= 16384 ? (32ll << 20) + (n / 1024 << 20)
-                                             : (48ll << 20) + (n - 16384) / 1024 * (5ll << 18);
+                                             : (48ll << 20) + (n - 16384) / 1024 * ((cut_share ? 10ll : 5ll) << 18);
     const int64_t slices = (n + kSliceTokens - 1) / kSliceTokens;      // a range may have more, smaller ones
     const int64_t budget_multi = slices <= 4 ? (32ll << 20) : (slices <= 6 ? (16ll << 20) : 0);
     const int64_t budget = g_overlap_sort >= 0 ? g_overlap_sort

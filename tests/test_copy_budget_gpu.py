@@ -1,0 +1,29 @@
+"""How many dense rows are copied beside a one-launch sort of more than 16384 pairs: more of them where a
+shard begins inside a wavefront's share of the pairs, which makes the sort longer.  Small integers:
+every bit is fixed, whatever was copied."""
+import pytest
+
+from paper_1905_04035_amd import binding as ts
+from paper_1905_04035_amd import workloads as wl
+
+from parity import check, run_gpu, run_oracle
+
+pytestmark = pytest.mark.gpu
+
+
+def _rows_copied(V, d, lengths, dt=wl.ROW_FP32):
+    w = wl.make_custom(V=V, d=d, n_list=lengths, zipf_s=1.1, seed=V + d + len(lengths), row_dtype=dt, integer_values=True)
+    g = run_gpu(w, mode="multi")
+    check(g, run_oracle(w), w, exact_bits=True)
+    assert g["info"]["sort_slices"] == 1
+    return g["info"]["sort_copy_rows_end"]
+
+
+@pytest.mark.parametrize("dt", [wl.ROW_FP32, wl.ROW_BF16])
+def test_a_shard_that_begins_inside_a_share(dt):
+    # 40000 pairs: shares of 2560; 48 MiB and 1.25 or 2.5 MiB per whole 1024 pairs beyond 16384, in work-groups of 256 KiB
+    budget = lambda quarters: ((48 << 20) + 23 * (quarters << 18)) // (256 << 10) * 32
+    for lengths in ([40000], [25600, 14400], [2560, 0, 37440], [40000, 0]):
+        assert _rows_copied(32768, 1024, lengths, dt) == budget(5)
+    for lengths in ([20000, 20000], [25601, 14399], [13333, 13333, 13334], [39999, 1], [1, 0, 39999]):
+        assert _rows_copied(32768, 1024, lengths, dt) == budget(10)
