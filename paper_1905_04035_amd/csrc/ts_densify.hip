@@ -2044,11 +2044,15 @@ int densify_impl(const ShardTable& sh, int64_t n, int32_t row_dtype, int32_t d, 
     // default budget comes to a little less than one work-group per compute unit in all, make it exactly
     // one: fewer leave compute units idle, and a few more than one leave a second round of stragglers
     // (measured on 256 compute units, d = 1024: 192 copying work-groups beside 64 sorting ones take
-    // 2048-12800 pairs 1-2 % faster than 136-178 do, and 208 cost 1.5 us more than 192 at 16384 pairs).
+    // 2048-12800 pairs 1-2 % faster than 136-178 do, and 208 cost 1.5 us more than 192 at 16384 pairs).  So it is made
+    // one too where the budget of a call with more than 16384 pairs comes to at most an eighth more, unless its sort is a
+    // longer one (above): V = 32768, 18500 pairs, with a few more / exactly one: d = 1024 64.1 / 62.0 us, d = 512 36.5 / 34.5,
+    // d = 256 27.6 / 26.2 (26.5 when the copies went by rows in smaller work-groups, which the stragglers cost nothing).
     if (pl.S == 1 && g_overlap_sort < 0 && copy_wgs > 0) {
         const int64_t cus = compute_units();
         const int64_t all = pl.G + copy_wgs;
-        if (cus > pl.G && 4 * all >= 3 * cus && all < cus) copy_wgs = cus - pl.G;
+        const bool few_more = n > 16384 && !cut_share && all > cus && 8 * all <= 9 * cus;
+        if (cus > pl.G && ((4 * all >= 3 * cus && all < cus) || few_more)) copy_wgs = cus - pl.G;
     }
     const int64_t rows_per_launch = copy_wgs * wg_elems / d;
     int32_t copy_done = 0;

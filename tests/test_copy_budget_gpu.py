@@ -2,6 +2,7 @@
 shard begins inside a wavefront's share of the pairs, which makes the sort longer.  Small integers:
 every bit is fixed, whatever was copied."""
 import pytest
+import torch
 
 from paper_1905_04035_amd import binding as ts
 from paper_1905_04035_amd import workloads as wl
@@ -27,3 +28,17 @@ def test_a_shard_that_begins_inside_a_share(dt):
         assert _rows_copied(32768, 1024, lengths, dt) == budget(5)
     for lengths in ([20000, 20000], [25601, 14399], [13333, 13333, 13334], [39999, 1], [1, 0, 39999]):
         assert _rows_copied(32768, 1024, lengths, dt) == budget(10)
+
+
+@pytest.mark.parametrize("V,d,part", [(32768, 256, 512), (32768, 1024, 512), (9000, 1024, 128)])
+@pytest.mark.parametrize("n", [16385, 18500, 22528, 22529, 27000])
+def test_one_work_group_per_compute_unit_instead_of_a_few_more(V, d, part, n):
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    G = -(-V // part)
+    wgs = ((48 << 20) + (n - 16384) // 1024 * (5 << 18)) // (256 << 10)
+    if G + wgs > cus and 8 * (G + wgs) <= 9 * cus:
+        wgs = cus - G
+    assert _rows_copied(V, d, [n]) == min(V, wgs * 32 * 1024 // d)
+    # a shard that begins inside a share: the copies that the longer sort has room for
+    wgs = ((48 << 20) + (n - 16384) // 1024 * (10 << 18)) // (256 << 10)
+    assert _rows_copied(V, d, [n // 2 + 1, n - n // 2 - 1]) == min(V, wgs * 32 * 1024 // d)
