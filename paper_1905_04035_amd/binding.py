@@ -332,7 +332,8 @@ def ts_last_launch_info() -> dict:
     keys = ["piece_tokens", "sort_copy_rows_end", "reduce_copy_rows_end", "sort_slices", "sort_part",
             "pieces", "combine_levels", "in_place"]
     info = dict(zip(keys, list(buf)))
-    info["short_rows"] = info["in_place"] >> 1      # 0 in the pieces, 1 / 2 row by row
+    info["deep_batches"] = info["in_place"] >> 3
+    info["short_rows"] = (info["in_place"] >> 1) & 3      # 0 in the pieces, 1 / 2 row by row
     info["in_place"] &= 1
     return info
 

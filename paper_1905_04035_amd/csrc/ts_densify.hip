@@ -1741,17 +1741,17 @@ bool pieces_of_8(int64_t n, int32_t d, int32_t V_total, int32_t row_dtype, bool 
     return row_dtype == TS_ROW_FP32 && n * cols <= 9 << 19 && (int64_t)V_total * d <= 12 << 20;
 }
 
-// ... and twice as many value rows in flight per wavefront (32-64 registers more, so fewer wavefronts): not
+// Twice as many value rows in flight per wavefront (32-64 registers more, so fewer wavefronts): not
 // where narrow rows come in large numbers, and not where the launch has nothing to copy beside a large
 // gather.  us with 16 / 8 fp32 rows in flight, V = 32768: d = 1024, 16384 pairs 58.5 / 59.7, without a dense
-// operand 38.1 / 39.2, 25000 pairs 70.0 / 71.5; d = 512, 8192 pairs 28.0 / 29.7; d = 128, 30000 pairs 24.8 / 25.0, 100000 pairs
-// 40.4 / 39.1; d = 64, 200000 pairs 66.2 / 58.6; in place d = 1024, 4000 pairs 16.7 / 17.5, 16384 pairs 32.4 / 31.8.
-// bf16 rows, 8 / 4 in flight: d = 1024, 12000 pairs 52.7 / 55.4; d = 64, 200000 pairs 65.5 / 61.6.
+// operand 38.1 / 39.2, 25000 pairs 70.0 / 71.5; d = 512, 8192 pairs 28.0 / 29.7; in place d = 1024, 4000 pairs 16.7 / 17.5,
+// 16384 pairs 32.4 / 31.8; d = 64, 47000 pairs 31.3 / 31.4, 50000 33.0 / 31.7, 65000 34.0 / 31.0; d = 128, 47000 31.5 / 31.9, 50000
+// 34.5 / 33.0; d = 192, 55000 39.5 / 39.1, 80000 41.8 / 40.7, but V = 100000 43.7 / 44.8, 71.2 / 70.7.  bf16 rows, 8 / 4 in flight: d = 1024, 12000 pairs 52.7 / 55.4; d = 64, 65000 33.3 / 33.9, 80000 38.4 / 35.4.
 // Few rows for many pairs is a gather too: V = 3713, d = 256, 212086 bf16 pairs 69.1 / 65.7, V = 3080, d = 316, 65536 fp32
 // pairs 60.5 / 58.4, V = 4000, d = 1024, 20000 pairs 36.8 / 36.2, but V = 8000 40.1 / 40.4.
-bool deep_batches(int64_t n, int32_t d, int32_t V, bool in_place)
+bool deep_batches(int64_t n, int32_t d, int32_t V, int32_t row_dtype, bool in_place)
 {
-    if (d < kColBlock && n > 65536) return false;
+    if (d < kColBlock && n > (row_dtype == TS_ROW_FP32 && d <= 128 ? 49152 : 65536)) return false;
     return !((in_place || n > 4 * (int64_t)V) && n * d > 8 << 20);
 }
 
@@ -1978,7 +1978,7 @@ int densify_impl(const ShardTable& sh, int64_t n, int32_t row_dtype, int32_t d, 
     int32_t C = piece_tokens_for(n, wide);
     const int32_t group = C * group_pieces(C);
     if (!g_piece_override && group == 64 && pieces_of_8(n, d, V_total, row_dtype, wide)) C = 8;
-    const bool deep = deep_batches(n_own, d, V, in_place);
+    const bool deep = deep_batches(n_own, d, V, row_dtype, in_place);
     Plan pl;
     make_plan(n, d, V, C, &pl, false, group, range ? compute_units() : 0);
     if (!ws_v || (int64_t)pl.total > ws_bytes) return TS_ERR_WORKSPACE;
@@ -2135,8 +2135,9 @@ int densify_impl(const ShardTable& sh, int64_t n, int32_t row_dtype, int32_t d, 
     g_last_info[5] = pl.NB;
     g_last_info[6] = pl.levels;
     // bit 0: in place; bits 1-2: how short rows were added up (0 in the pieces, 1 row by row with the long
-    // rows by lone wavefronts, 2 row by row with the long rows by work-groups)
-    g_last_info[7] = (in_place ? 1 : 0) | ((rp.short_max == 0 ? 0 : (rp.logG <= 6 ? 1 : 2)) << 1);
+    // rows by lone wavefronts, 2 row by row with the long rows by work-groups); bit 3: the deep batches
+    const bool deep_form = rp.short_max == 0 && (gp == 8 || deep) && (wide || row_dtype == TS_ROW_FP32);
+    g_last_info[7] = (in_place ? 1 : 0) | ((rp.short_max == 0 ? 0 : (rp.logG <= 6 ? 1 : 2)) << 1) | (deep_form ? 8 : 0);
     g_have_last = true;
     return TS_OK;
 }
