@@ -1747,12 +1747,20 @@ bool pieces_of_8(int64_t n, int32_t d, int32_t V_total, int32_t row_dtype, bool 
 // operand 38.1 / 39.2, 25000 pairs 70.0 / 71.5; d = 512, 8192 pairs 28.0 / 29.7; in place d = 1024, 4000 pairs 16.7 / 17.5,
 // 16384 pairs 32.4 / 31.8; d = 64, 47000 pairs 31.3 / 31.4, 50000 33.0 / 31.7, 65000 34.0 / 31.0; d = 128, 47000 31.5 / 31.9, 50000
 // 34.5 / 33.0; d = 192, 55000 39.5 / 39.1, 80000 41.8 / 40.7, but V = 100000 43.7 / 44.8, 71.2 / 70.7.  bf16 rows, 8 / 4 in flight: d = 1024, 12000 pairs 52.7 / 55.4; d = 64, 65000 33.3 / 33.9, 80000 38.4 / 35.4.
-// Few rows for many pairs is a gather too: V = 3713, d = 256, 212086 bf16 pairs 69.1 / 65.7, V = 3080, d = 316, 65536 fp32
-// pairs 60.5 / 58.4, V = 4000, d = 1024, 20000 pairs 36.8 / 36.2, but V = 8000 40.1 / 40.4.
-bool deep_batches(int64_t n, int32_t d, int32_t V, int32_t row_dtype, bool in_place)
+// Many pairs per row is a gather too, but the limit depends on the form.  fp32 rows in pieces of 16, 2.2 / 3.5 / 5 / 7 pairs
+// per row: d = 1024, 20000 pairs 41.0 / 41.5, 37.2 / 36.6, 37.6 / 36.2, 36.1 / 35.8; 33000 pairs, where rows are left
+// to copy, 58.3 / 61.8, 53.7 / 54.4, 53.0 / 52.6; d = 256, 80000 pairs 45.9 / 47.0, 45.3 / 45.9, 44.3 / 43.1, 45.8 / 45.1.  In pieces
+// of 32, 4.2 / 7 / 16 / 25: d = 256, 140000 pairs 72.3 / 75.6, 59.4 / 61.7, 60.8 / 61.1, 62.2 / 62.7; d = 384 at 5 / 16 / 25 / 50 83.3 / 84.8,
+// 79.0 / 79.5, 81.8 / 81.1, 86.1 / 85.1.  bf16 rows, 4.2 / 7 / 10 / 16 / 50: d = 256, 140000 pairs 62.9 / 64.2, 49.9 / 50.7,
+// 49.9 / 49.7, 50.6 / 49.3, 61.3 / 59.0; d = 384 72.1 / 76.4, 58.9 / 62.4, 57.3 / 59.6, 56.8 / 58.0, 65.9 / 65.5.
+// A range is taken to own its share of the pairs: one eighth of 32768 ids, d = 1024, 131072 fp32 pairs 38.2 / 40.7 us, with the
+// hottest id in it 53.5 / 55.3, with all hot ids in it 126.8 / 125.0; bf16 rows 36.6 / 37.7, 46.5 / 48.0, 94.2 / 94.0.
+bool deep_batches(int64_t n, int32_t d, int32_t V, int32_t row_dtype, int32_t C, bool in_place)
 {
     if (d < kColBlock && n > (row_dtype == TS_ROW_FP32 && d <= 128 ? 49152 : 65536)) return false;
-    return !((in_place || n > 4 * (int64_t)V) && n * d > 8 << 20);
+    if (n * d <= 8 << 20) return true;
+    if (in_place) return false;
+    return n <= (row_dtype == TS_ROW_BF16 ? 8 : C >= 32 ? 16 : 4) * (int64_t)V;
 }
 
 // bound: size the arrays that depend on how the sort is split (slices, parts) for the largest
@@ -1972,13 +1980,13 @@ int densify_impl(const ShardTable& sh, int64_t n, int32_t row_dtype, int32_t d, 
     // What counts is the pairs that the call will own: of a range, about its share of the vocabulary.  (One
     // eighth of 32768 ids, 131072 bf16 pairs, d = 1024: with short rows in the pieces 37.7 us, by row 42.)
     const bool range = V < V_total;
-    const int64_t n_own = range ? (int64_t)((double)n * V / V_total) + 1 : n;
+    const int64_t n_own = range ? (int64_t)((double)n * V / V_total) : n;
     const bool by_row = g_short_rows < 0 ? n_own >= short_rows_from(d, V, row_dtype == TS_ROW_BF16) : g_short_rows == 1;
     // The groups of pieces, and with them the workspace, go by all pairs.
     int32_t C = piece_tokens_for(n, wide);
     const int32_t group = C * group_pieces(C);
     if (!g_piece_override && group == 64 && pieces_of_8(n, d, V_total, row_dtype, wide)) C = 8;
-    const bool deep = deep_batches(n_own, d, V, row_dtype, in_place);
+    const bool deep = deep_batches(n_own, d, V, row_dtype, C, in_place);
     Plan pl;
     make_plan(n, d, V, C, &pl, false, group, range ? compute_units() : 0);
     if (!ws_v || (int64_t)pl.total > ws_bytes) return TS_ERR_WORKSPACE;

@@ -7,7 +7,7 @@ from paper_1905_04035_amd import binding as ts
 from paper_1905_04035_amd import workloads as wl
 
 from parity import check, run_gpu, run_oracle
-from test_range_gpu import run_range, check_range
+from test_range_gpu import check_range
 
 pytestmark = pytest.mark.gpu
 
@@ -18,6 +18,41 @@ def _depth(V, d, n, dt, **kw):
     check(g, run_oracle(w), w, exact_bits=True)
     assert g["info"]["short_rows"] == 0
     return g["info"]["deep_batches"]
+
+
+# pairs per row up to which the batches are deep: fp32 rows in pieces of 16 and of 32, bf16 rows
+@pytest.mark.parametrize("d,dt,n,limit", [(512, wl.ROW_FP32, 20000, 4), (256, wl.ROW_FP32, 96256, 4), (256, wl.ROW_FP32, 96257, 16),
+                                          (256, wl.ROW_BF16, 40000, 8), (512, wl.ROW_BF16, 60000, 8)])
+def test_many_pairs_per_row(d, dt, n, limit):
+    V = -(-n // limit)
+    assert _depth(V, d, n, dt) == 1
+    assert _depth(V - 1, d, n, dt) == 0
+
+
+@pytest.mark.parametrize("d,n", [(1024, 8192), (2048, 4096)])
+def test_in_place_and_small_gathers(d, n):
+    for pairs, deep in ((n, 1), (n + 1, 0)):
+        assert _depth(700, d, pairs, wl.ROW_FP32) == deep             # many pairs per row
+        assert _depth(4000, d, pairs, wl.ROW_FP32, in_place=True) == deep
+        assert _depth(4000, d, pairs, wl.ROW_FP32) == 1
+
+
+# a range is taken to own its share of the pairs (rounded down), whatever it really owns
+@pytest.mark.parametrize("V,d,dt,n,v0,v1,deep", [
+    (9000, 512, wl.ROW_FP32, 36000, 1000, 6000, 1), (9000, 512, wl.ROW_FP32, 36002, 1000, 6000, 0),
+    (9000, 512, wl.ROW_FP32, 36001, 0, 9000, 0), (32768, 256, wl.ROW_FP32, 131072, 8193, 12290, 1),
+    (32767, 256, wl.ROW_FP32, 131073, 8193, 12290, 1), (6500, 1024, wl.ROW_BF16, 52000, 0, 1700, 1),
+    (6500, 1024, wl.ROW_BF16, 52008, 0, 1700, 0)])
+def test_ranges(monkeypatch, V, d, dt, n, v0, v1, deep):
+    seen, read_views = {}, ts.ts_read_views
+    monkeypatch.setattr(ts, "ts_read_views", lambda *a: (seen.update(ts.ts_last_launch_info()), read_views(*a))[1])
+    for into_range in (False, True):
+        w = wl.make_custom(V=V, d=d, n_list=[n // 2, n - n // 2], zipf_s=1.1, seed=V + d + n, row_dtype=dt, integer_values=True)
+        if into_range:
+            for a in w.ids:
+                a[:] = v0 + a % (v1 - v0)
+        check_range(w, oracle.densify(w.ids, w.rows, d, V, w.dense_in, dt), v0, v1, exact_bits=True)
+        assert (seen["short_rows"], seen["deep_batches"]) == (0, deep)
 
 
 @pytest.mark.parametrize("d,dt,limit", [(64, wl.ROW_FP32, 49152), (128, wl.ROW_FP32, 49152), (132, wl.ROW_FP32, 65536),
