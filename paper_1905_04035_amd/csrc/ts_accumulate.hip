@@ -126,13 +126,19 @@ int launch_sum(const DenseList& l, float* out, int64_t n4, hipStream_t stream)
     return hipGetLastError() == hipSuccess ? TS_OK : TS_ERR_HIP;
 }
 
-// Collects runs and launches when the table or the grid is full.
+bool overlap(const void* a, int64_t a_bytes, const void* b, int64_t b_bytes)
+{
+    return (uintptr_t)a < (uintptr_t)b + (uintptr_t)b_bytes && (uintptr_t)b < (uintptr_t)a + (uintptr_t)a_bytes;
+}
+
+// Collects runs and launches when the table or the grid is full, or (in_order) run by run.
 struct Gather {
     RunTable t;
     int64_t wgs;
     hipStream_t stream;
+    bool in_order;
 
-    explicit Gather(hipStream_t s) : wgs(0), stream(s) { t.m = 0; }
+    Gather(hipStream_t s, bool order) : wgs(0), stream(s), in_order(order) { t.m = 0; }
     void flush()
     {
         if (t.m > 0) hipLaunchKernelGGL(gather_kernel, dim3((unsigned)wgs), dim3(kGatherThreads), 0, stream, t);
@@ -146,7 +152,7 @@ struct Gather {
         for (int64_t a = 0, len; a < n; a += len) {
             len = n - a < kMaxWgs * kGatherThreads ? n - a : kMaxWgs * kGatherThreads;
             const int64_t need = (len + kGatherThreads - 1) / kGatherThreads;
-            if (t.m == kMaxRuns || wgs + need > kMaxWgs) flush();
+            if (t.m == kMaxRuns || wgs + need > kMaxWgs || in_order) flush();
             t.run[t.m++] = Run{(const void*)((uintptr_t)src + (uintptr_t)(a * src_bytes)), (char*)dst + a * dst_bytes, len, (int32_t)wgs, kind};
             wgs += need;
         }
@@ -259,8 +265,22 @@ int ts_accumulate(const ts_grad* grads, int32_t m, int32_t rule, int32_t d, int3
     if (total > 0 && (!ids_out || !rows_out)) return TS_ERR_NULL;
     if ((uintptr_t)rows_out & 15u) return TS_ERR_ALIGN;
     *n_slices_out = total;
-    Gather g(stream);
+    // An input that lies in an output, but not where it is copied to (ids in the place of a later gradient's
+    // ids, say), is read before later runs are written over it: the runs are then launched one by one.
+    bool in_order = false;
     int64_t at = 0;
+    for (int i = 0; i < m; ++i) {
+        const bool dense = grads[i].kind == TS_GRAD_DENSE;
+        const int64_t n = dense ? (int64_t)V : grads[i].n;
+        const auto in_outputs = [&](const void* src, int64_t bytes, const void* dst) {
+            return src != dst && (overlap(src, bytes, ids_out, total * 4) || overlap(src, bytes, rows_out, total * d * 4));
+        };
+        if (n > 0 && !dense) in_order = in_order || in_outputs(grads[i].ids, n * 4, ids_out + at);
+        if (n > 0) in_order = in_order || in_outputs(grads[i].values, n * d * 4, rows_out + at * d);
+        at += n;
+    }
+    Gather g(stream, in_order);
+    at = 0;
     for (int i = 0; i < m; ++i) {
         const bool dense = grads[i].kind == TS_GRAD_DENSE;
         const int64_t n = dense ? (int64_t)V : grads[i].n;
