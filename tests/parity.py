@@ -8,7 +8,7 @@ from paper_1905_04035_amd import binding as ts
 from paper_1905_04035_amd import workloads as wl
 
 # fp32 outputs must satisfy |gpu - exact| <= TOL * (sum of |terms| of that element).
-# The library adds at most C <= 32 rows in sequence inside a piece, the 4 pieces of a
+# The library adds at most C <= 32 rows in sequence inside a piece, the 4 pieces (C = 8: 8) of a
 # work-group in sequence, then the work-groups' shares of a long row in a tree with a fan-in
 # of 16, and dense_in last; with fp32 unit round-off 2^-24
 # the first-order bound is (depth - 1) * 2^-24 * sum|terms|, below 1e-5 for any row of
@@ -95,20 +95,27 @@ def check(g, r: oracle.OracleResult, w: wl.Workload, exact_bits=False):
     return float(np.max(err / scale))
 
 
+def group_pieces(C: int) -> int:
+    """Pieces of C sorted positions that a work-group of the reduce kernel takes: 64 positions with C = 8
+    or 16, 128 with C = 32."""
+    return 8 if C <= 8 else 4
+
+
 def error_depth(count_max: int, C: int) -> int:
     """Additions on the longest chain a term of the fullest row can take: C inside a piece; the
-    4 pieces of a work-group in sequence; then, per level of the tree in which the shares of a
+    4 pieces (8 of them where C = 8) of a work-group in sequence; then, per level of the tree in which the shares of a
     row that spans several work-groups are added up (fan-in 16: one level up to 16 work-groups,
     two up to 256, ...), a balanced tree over a batch of shares followed by the batches in
     sequence: 3 + 2 for two batches of 8 (fp32 rows), 2 + 4 for four batches of 4 (bf16 rows read
     16 bytes per lane); dense_in last."""
     if count_max <= C:
         return count_max + 1
-    groups = -(-count_max // (4 * C)) + 1
+    pieces = group_pieces(C)
+    groups = -(-count_max // (pieces * C)) + 1
     levels = 1
     while 16 ** levels < groups:
         levels += 1
-    return C + 3 + 6 * levels + 1
+    return C + (pieces - 1) + 6 * levels + 1
 
 
 def error_bound(count_max: int, C: int) -> float:

@@ -6,7 +6,7 @@ import pytest
 from paper_1905_04035_amd import binding as ts
 from paper_1905_04035_amd import workloads as wl
 
-from parity import check, run_gpu, run_oracle
+from parity import TOL, check, error_bound, run_gpu, run_oracle
 from test_epilogue_gpu import check_scaled
 
 pytestmark = pytest.mark.gpu
@@ -32,6 +32,18 @@ def test_around_the_limits(V, d, dt, n, piece):
     g = run_gpu(w, mode="multi")
     assert g["info"]["piece_tokens"] == piece
     check(g, run_oracle(w), w, exact_bits=True)
+
+
+@pytest.mark.parametrize("V,d,n,dt", [(1000, 64, 2048, wl.ROW_FP32), (4000, 256, 18000, wl.ROW_FP32),
+                                      (2000, 512, 30000, wl.ROW_BF16), (300, 264, 30000, wl.ROW_BF16)])
+@pytest.mark.parametrize("s", [1.1, 1.8])
+def test_measured_error_stays_under_the_a_priori_bound(V, d, n, dt, s):
+    w = wl.make_custom(V=V, d=d, n_list=[n - n // 3, n // 3], zipf_s=s, seed=V + n, row_dtype=dt)
+    g, r = run_gpu(w, mode="multi"), run_oracle(w)
+    assert g["info"]["piece_tokens"] == 8
+    bound = error_bound(int(r.count.max()), 8)
+    worst = check(g, r, w)
+    assert worst <= bound < TOL, (worst, bound)
 
 
 @pytest.mark.parametrize("n", [8191, 8192, 8193])
