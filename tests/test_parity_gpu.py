@@ -8,7 +8,7 @@ import oracle
 from paper_1905_04035_amd import binding as ts
 from paper_1905_04035_amd import workloads as wl
 
-from parity import TOL, check, error_bound, run_gpu, run_oracle, to_dev, DEV
+from parity import TOL, check, error_bound, group_pieces, run_gpu, run_oracle, to_dev, DEV
 
 pytestmark = pytest.mark.gpu
 
@@ -171,15 +171,15 @@ def test_piece_sizes_and_exact_boundaries(piece):
 
 
 @pytest.mark.parametrize("shift", [0, 1, 37])
-@pytest.mark.parametrize("piece", [16, 32])
+@pytest.mark.parametrize("piece", [8, 16, 32])
 def test_rows_at_the_boundaries_of_work_groups_and_of_the_combine_tree(piece, shift):
-    # A reduce work-group takes 4 pieces; a row inside one work-group is finished there, a longer
+    # A reduce work-group takes 4 pieces, or 8 of 8 positions; a row inside one work-group is finished there, a longer
     # one leaves a share per work-group, and shares are added up 16 at a time, level by level.
     # Rows of exactly those sizes, one pair less and one more, starting `shift` sorted positions
     # after a work-group boundary; small-integer values, so every bit must match.
     ts.ts_set_piece_tokens(piece)
     try:
-        G = 4 * piece                       # sorted positions of one work-group
+        G = group_pieces(piece) * piece     # sorted positions of one work-group
         counts = [shift] if shift else []
         for c in (G - 1, G, G + 1, 2 * G, 16 * G - 1, 16 * G, 16 * G + 1, 17 * G, 2, piece + 1, 256 * G + 3, 5):
             counts.append(c)

@@ -10,7 +10,7 @@ import oracle
 from paper_1905_04035_amd import binding as ts
 from paper_1905_04035_amd import workloads as wl
 
-from parity import check, run_gpu, run_oracle
+from parity import check, group_pieces, run_gpu, run_oracle
 from test_epilogue_gpu import check_scaled, run_scaled
 from test_range_gpu import check_range
 
@@ -72,12 +72,13 @@ def test_bf16_rows_narrow_and_wide_loads(short_rows, V, d, n):
 def test_rows_just_below_at_and_above_the_limit_between_the_two_ways(short_rows, piece):
     ts.ts_set_piece_tokens(piece)
     try:
+        G = group_pieces(piece) * piece         # sorted positions of one work-group; 17 of them: two levels of the tree
         counts = [piece - 1, piece, piece + 1, 1, 2 * piece, 2, piece, piece + 1, 4 * piece + 1, piece - 1, 1, 1,
-                  3, 17 * 4 * piece, piece]
+                  3, 17 * G, piece]
         for dt in (wl.ROW_FP32, wl.ROW_BF16):
             w = _counts_workload(counts, V=3 * len(counts) + 5, d=520, seed=piece, row_dtype=dt)
             worst, g, r = _case(w, exact_bits=True)
-            assert int(r.count.max()) == 17 * 4 * piece
+            assert int(r.count.max()) == 17 * G and g["info"]["combine_levels"] >= 2
     finally:
         ts.ts_set_piece_tokens(0)
 
