@@ -36,7 +36,7 @@
 //                   a row starts finishes it (dense_in + sum straight to dense_out); else
 //                   the wavefront that would copy the row adds up its few value rows
 //                   instead, and the pieces pass over them; there, with pieces of 16
-//                   positions, one wavefront walks the four pieces of a group by itself
+//                   positions or fewer, one wavefront walks the pieces of a group by itself
 //                   and keeps their sums in registers (no LDS, no barrier).  Same order of
 //                   additions, same bits in every form.
 //
@@ -46,8 +46,8 @@
 // those).  The reduce kernel copies the untouched rows of [X, V).
 //
 // No floating-point atomics anywhere: the position of every pair, the cut points and
-// the order of every addition depend on the ids alone, so results are reproducible
-// bit for bit.
+// the order of every addition depend on the ids and the sizes (pairs, columns, vocabulary,
+// row type) alone, so results are reproducible bit for bit.
 #include <hip/hip_runtime.h>
 #include <hip/hip_ext.h>
 #include <stdint.h>
@@ -1699,8 +1699,8 @@ size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 // Calls with at least this many pairs add up their short rows row by row, the others in the pieces.
 // Row by row a wavefront has one output row's few value rows in flight, all columns of them, after
-// three loads that depend on each other; in the pieces it has up to eight pairs of 256 (bf16: 512)
-// columns in flight, and every block of columns repeats the bookkeeping.  So the wider the rows and
+// three loads that depend on each other; in the pieces it has up to sixteen pairs of 256 (bf16: eight of 512)
+// columns in flight (half as many when the limits below were measured), and every block of columns repeats the bookkeeping.  So the wider the rows and
 // the more pairs, the better the first does.  Measured on V = 8192 .. 131072, Zipf ids: narrower than
 // 256 columns it never pays (half-empty wavefronts), at 256 from about 400 thousand pairs (2 %), at 512
 // from 65 to 100 thousand, at 1024 from 25 thousand (bf16 rows, 6-13 % by 50 thousand) or 40-50
@@ -1730,14 +1730,17 @@ int piece_tokens_for(int64_t n, bool wide_bf16)
 // as many of them) suit a launch that mostly copies or mostly gathers less.  fp32 rows, us with 8 / 16: V = 4000, d = 256,
 // 2000 pairs 13.1 / 14.9, 20000 pairs 24.0 / 22.9; V = 16000, d = 512, 8000 pairs 23.8 / 25.5; V = 32768, d = 512, 8192 pairs
 // 30.1 / 28.0.  bf16 rows (half the bytes per row, half the work-groups), V = 32768: d = 512, 12000 pairs 30.7 / 33.9, 24000
-// pairs 38.5 / 41.3; d = 1024, 24000 pairs 63.9 / 63.3; d = 256, 100000 pairs 49.7 / 45.6.
+// pairs 38.5 / 41.3; d = 1024, 24000 pairs 63.9 / 63.3; d = 256, 100000 pairs 49.7 / 45.6.  They don't mind the copies up to
+// 16384 pairs: V = 42000 / 131072, d = 512, 12000 pairs 35.3 / 36.4, 96.3 / 95.1, in place 20.9 / 22.2, 21.4 / 22.5; beyond that
+// V = 131072 20000 pairs 100.3 / 98.3.  For fp32 rows the limit on the vocabulary costs calls in place that touch little of a large
+// one (V = 74365, d = 256, 3280 pairs 13.8 / 15.5), but out of place 8 loses 2-9 % there (29.7 / 28.6, V = 131072, d = 512 98.0 / 90.3).
 // The length of the pieces fixes the order of additions, so it goes by the pairs, the width, the row type and the
 // whole vocabulary alone: what only spreads the work (in place or not, short rows in the pieces or row by
 // row, the range that a call owns) must not change a bit.  In these limits no call goes row by row unless forced to.
 bool pieces_of_8(int64_t n, int32_t d, int32_t V_total, int32_t row_dtype, bool wide)
 {
     const int64_t cols = d < kColBlock ? kColBlock : d;
-    if (wide) return d <= 512 && n <= 32768 && (int64_t)V_total * d <= 20 << 20;
+    if (wide) return d <= 512 && (n <= 16384 || (n <= 32768 && (int64_t)V_total * d <= 20 << 20));
     return row_dtype == TS_ROW_FP32 && n * cols <= 9 << 19 && (int64_t)V_total * d <= 12 << 20;
 }
 
