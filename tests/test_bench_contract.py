@@ -18,6 +18,12 @@ def test_more_than_one_gpu_is_refused_with_a_message():
     assert r.stdout.strip() == ""
 
 
+def test_the_counted_traffic_belongs_to_the_present_kernels():
+    sys.path.insert(0, ROOT)
+    import bench
+    assert bench.code_digest(bench.KERNEL_SOURCE) == bench.COUNTED_TRAFFIC["code_sha256"]
+
+
 @pytest.mark.gpu
 def test_json_line_has_the_agreed_fields():
     r = subprocess.run([sys.executable, os.path.join(ROOT, "bench.py"), "--steps", "20", "--warmup", "5",
