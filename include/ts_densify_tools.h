@@ -70,8 +70,8 @@ int ts_set_piece_tokens(int32_t piece_tokens);
 
 /*
  * Tuning.  The sort launches are latency-bound, so work-groups that copy dense rows run
- * beside them to keep HBM busy.  sort_bytes: dense bytes (read + write) copied from dense_in
- * to dense_out beside each sort launch, before it is known which rows receive pairs (those
+ * beside them to keep HBM busy.  sort_bytes: dense bytes moved (read from dense_in, if there is
+ * one, and written to the result) beside each sort launch, before it is known which rows receive pairs (those
  * are overwritten afterwards).  -1 = default, 0 = none.  Results do not depend on it.
  */
 int ts_set_overlap_bytes(int64_t sort_bytes);
