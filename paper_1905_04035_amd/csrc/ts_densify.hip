@@ -1730,17 +1730,17 @@ int piece_tokens_for(int64_t n, bool wide_bf16)
 // as many of them) suit a launch that mostly copies or mostly gathers less.  fp32 rows, us with 8 / 16: V = 4000, d = 256,
 // 2000 pairs 13.1 / 14.9, 20000 pairs 24.0 / 22.9; V = 16000, d = 512, 8000 pairs 23.8 / 25.5; V = 32768, d = 512, 8192 pairs
 // 30.1 / 28.0.  bf16 rows (half the bytes per row, half the work-groups), V = 32768: d = 512, 12000 pairs 30.7 / 33.9, 24000
-// pairs 38.5 / 41.3; d = 1024, 24000 pairs 63.9 / 63.3; d = 256, 100000 pairs 49.7 / 45.6.  They don't mind the copies up to
-// 16384 pairs: V = 42000 / 131072, d = 512, 12000 pairs 35.3 / 36.4, 96.3 / 95.1, in place 20.9 / 22.2, 21.4 / 22.5; beyond that
-// V = 131072 20000 pairs 100.3 / 98.3.  For fp32 rows the limit on the vocabulary costs calls in place that touch little of a large
-// one (V = 74365, d = 256, 3280 pairs 13.8 / 15.5), but out of place 8 loses 2-9 % there (29.7 / 28.6, V = 131072, d = 512 98.0 / 90.3).
+// pairs 38.5 / 41.3; d = 1024, 24000 pairs 63.9 / 63.3; d = 256, 100000 pairs 49.7 / 45.6.  The limits on the vocabulary cost
+// calls in place that touch little of a large one (fp32, V = 74365, d = 256, 3280 pairs 13.8 / 15.5; bf16, V = 131072, d = 512, 5000 pairs
+// 17.3 / 18.8), but out of place 8 loses there: fp32 29.7 / 28.6 and, d = 512, 98.0 / 90.3; bf16 rows to a bf16 result, V = 108448, d = 512,
+// 4325 pairs 64.6 / 60.6.
 // The length of the pieces fixes the order of additions, so it goes by the pairs, the width, the row type and the
 // whole vocabulary alone: what only spreads the work (in place or not, short rows in the pieces or row by
 // row, the range that a call owns) must not change a bit.  In these limits no call goes row by row unless forced to.
 bool pieces_of_8(int64_t n, int32_t d, int32_t V_total, int32_t row_dtype, bool wide)
 {
     const int64_t cols = d < kColBlock ? kColBlock : d;
-    if (wide) return d <= 512 && (n <= 16384 || (n <= 32768 && (int64_t)V_total * d <= 20 << 20));
+    if (wide) return d <= 512 && n <= 32768 && (int64_t)V_total * d <= 20 << 20;
     return row_dtype == TS_ROW_FP32 && n * cols <= 9 << 19 && (int64_t)V_total * d <= 12 << 20;
 }
 

@@ -20,7 +20,7 @@ pytestmark = pytest.mark.gpu
 # (V, d, row type, pairs, pieces)
 SHAPES = [(4000, 256, wl.ROW_FP32, 2000, 8), (2000, 512, wl.ROW_BF16, 12000, 8), (1000, 64, wl.ROW_FP32, 2048, 8),
           (12288, 1024, wl.ROW_FP32, 3000, 8), (12289, 1024, wl.ROW_FP32, 3000, 16), (32768, 1024, wl.ROW_FP32, 3000, 16),
-          (40960, 512, wl.ROW_BF16, 16385, 8), (40961, 512, wl.ROW_BF16, 16384, 8), (40961, 512, wl.ROW_BF16, 16385, 16), (4096, 512, wl.ROW_BF16, 32769, 16),
+          (40960, 512, wl.ROW_BF16, 12000, 8), (40961, 512, wl.ROW_BF16, 12000, 16), (4096, 512, wl.ROW_BF16, 32769, 16),
           (4000, 256, wl.ROW_FP32, 18433, 16), (12000, 516, wl.ROW_BF16, 9000, 16)]
 
 
