@@ -24,6 +24,7 @@ def _workload(V, d, n, dt, hot=()):
 @pytest.mark.parametrize("V,d,dt,n,piece", [
     (3000, 1024, wl.ROW_FP32, 4608, 8), (3000, 1024, wl.ROW_FP32, 4609, 16), (12288, 1024, wl.ROW_FP32, 500, 8),
     (12289, 1024, wl.ROW_FP32, 500, 16), (3000, 64, wl.ROW_FP32, 18432, 8), (3000, 64, wl.ROW_FP32, 18433, 16),
+    (1000, 260, wl.ROW_FP32, 9216, 8), (1000, 260, wl.ROW_FP32, 9217, 16), (1000, 516, wl.ROW_FP32, 6145, 16),
     (2000, 512, wl.ROW_BF16, 32768, 8), (2000, 512, wl.ROW_BF16, 32769, 16), (2000, 520, wl.ROW_BF16, 900, 16),
     (2000, 516, wl.ROW_BF16, 900, 16), (5000, 128, wl.ROW_FP32, 65536, 16), (5000, 128, wl.ROW_FP32, 65537, 16),
     (5000, 128, wl.ROW_BF16, 65537, 16), (5, 4, wl.ROW_FP32, 1, 8)])
