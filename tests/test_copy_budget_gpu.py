@@ -42,3 +42,20 @@ def test_one_work_group_per_compute_unit_instead_of_a_few_more(V, d, part, n):
     # a shard that begins inside a share: the copies that the longer sort has room for
     wgs = ((48 << 20) + (n - 16384) // 1024 * (10 << 18)) // (256 << 10)
     assert _rows_copied(V, d, [n // 2 + 1, n - n // 2 - 1]) == min(V, wgs * 32 * 1024 // d)
+
+
+@pytest.mark.parametrize("V,d,n", [(41900, 256, 65536), (32768, 512, 65536), (60000, 64, 58000), (60000, 64, 66000), (5000, 512, 60000)])
+def test_copies_beside_a_sliced_sort(V, d, n):
+    # 32 MiB beside each of the two launches up to four slices, 16 MiB up to six, but no more work-groups than
+    # there are compute units that don't sort, unless the sort takes them all
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    S = -(-n // 16384)
+    part = 2048 if -(-V // 2048) * S >= 256 else 1024
+    idle = cus - -(-V // part) * S
+    wgs = 128 if S <= 4 else 64
+    wgs = min(wgs, idle) if idle > 0 else wgs
+    w = wl.make_custom(V=V, d=d, n_list=[n], zipf_s=1.1, seed=V + d, integer_values=True)
+    g = run_gpu(w, mode="multi")
+    check(g, run_oracle(w), w, exact_bits=True)
+    assert g["info"]["sort_slices"] == S
+    assert g["info"]["sort_copy_rows_end"] == min(V, 2 * (wgs * 32768 // d))
