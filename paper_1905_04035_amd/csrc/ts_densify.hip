@@ -2056,14 +2056,15 @@ int densify_impl(const ShardTable& sh, int64_t n, int32_t row_dtype, int32_t d, 
     // one: fewer leave compute units idle, and a few more than one leave a second round of stragglers
     // (measured on 256 compute units, d = 1024: 192 copying work-groups beside 64 sorting ones take
     // 2048-12800 pairs 1-2 % faster than 136-178 do, and 208 cost 1.5 us more than 192 at 16384 pairs).  So it is made
-    // one too where the budget of a call with more than 16384 pairs comes to at most an eighth more, unless its sort is a
-    // longer one (above): V = 32768, 18500 pairs, with a few more / exactly one: d = 1024 64.1 / 62.0 us, d = 512 36.5 / 34.5,
-    // d = 256 27.6 / 26.2 (26.5 when the copies went by rows in smaller work-groups, which the stragglers cost nothing).
+    // one where it comes to more, too, unless the sort is a long one or the copies read nothing: us with more / exactly one,
+    // V = 32768, 18500 pairs, d = 1024 64.1 / 62.0, d = 512 36.5 / 34.5, d = 256 27.6 / 26.2; V = 60000, 5000 pairs, d = 512 47.3 / 44.7,
+    // d = 256 28.6 / 25.9; 21000 pairs 32.0 / 31.2, 26000 pairs V = 131072 54.6 / 55.5; without a dense operand V = 60000, d = 512, 5000 pairs
+    // 24.1 / 27.0.)
     if (pl.S == 1 && g_overlap_sort < 0 && copy_wgs > 0) {
         const int64_t cus = compute_units();
         const int64_t all = pl.G + copy_wgs;
-        const bool few_more = n > 16384 && !cut_share && all > cus && 8 * all <= 9 * cus;
-        if (cus > pl.G && ((4 * all >= 3 * cus && all < cus) || few_more)) copy_wgs = cus - pl.G;
+        const bool long_sort = n > (cut_share ? 16384 : 22528) || !dense_in;
+        if (cus > pl.G && 4 * all >= 3 * cus && (all < cus || !long_sort)) copy_wgs = cus - pl.G;
     }
     // Beside a sliced sort that leaves compute units idle: no more of them than that.  (More wait for the sort's, and the
     // two launches end late; where the sort fills the GPU anyway that costs nothing and copies are worth 1-5 %.)  us with

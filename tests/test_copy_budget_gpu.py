@@ -30,13 +30,25 @@ def test_a_shard_that_begins_inside_a_share(dt):
         assert _rows_copied(32768, 1024, lengths, dt) == budget(10)
 
 
+@pytest.mark.parametrize("V,d", [(60000, 64), (60000, 260), (45000, 128)])
+@pytest.mark.parametrize("n", [1024, 5000, 16384])
+def test_one_work_group_per_compute_unit_in_small_calls(V, d, n):
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    G = -(-V // 512)
+    wgs = (32 + n // 1024) * 4
+    if 4 * (G + wgs) >= 3 * cus:
+        wgs = cus - G
+    for lengths in ([n], [n // 2 + 1, n - n // 2 - 1]):
+        assert _rows_copied(V, d, lengths) == min(V, wgs * 32768 // d)
+
+
 @pytest.mark.parametrize("V,d,part", [(32768, 256, 512), (32768, 1024, 512), (9000, 1024, 128)])
 @pytest.mark.parametrize("n", [16385, 18500, 22528, 22529, 27000])
 def test_one_work_group_per_compute_unit_instead_of_a_few_more(V, d, part, n):
     cus = torch.cuda.get_device_properties(0).multi_processor_count
     G = -(-V // part)
     wgs = ((48 << 20) + (n - 16384) // 1024 * (5 << 18)) // (256 << 10)
-    if G + wgs > cus and 8 * (G + wgs) <= 9 * cus:
+    if G + wgs > cus and n <= 22528:
         wgs = cus - G
     assert _rows_copied(V, d, [n]) == min(V, wgs * 32 * 1024 // d)
     # a shard that begins inside a share: the copies that the longer sort has room for
