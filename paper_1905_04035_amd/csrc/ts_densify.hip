@@ -1756,10 +1756,15 @@ bool pieces_of_8(int64_t n, int32_t d, int32_t V_total, int32_t row_dtype, bool 
 // of 32, 4.2 / 7 / 16 / 25: d = 256, 140000 pairs 72.3 / 75.6, 59.4 / 61.7, 60.8 / 61.1, 62.2 / 62.7; d = 384 at 5 / 16 / 25 / 50 83.3 / 84.8,
 // 79.0 / 79.5, 81.8 / 81.1, 86.1 / 85.1.  bf16 rows, 4.2 / 7 / 10 / 16 / 50: d = 256, 140000 pairs 62.9 / 64.2, 49.9 / 50.7,
 // 49.9 / 49.7, 50.6 / 49.3, 61.3 / 59.0; d = 384 72.1 / 76.4, 58.9 / 62.4, 57.3 / 59.6, 56.8 / 58.0, 65.9 / 65.5.
+// A launch that writes bf16 is mostly rows without pairs, in half the bytes: fewer wavefronts lose there.  fp32 rows to a bf16
+// result, V = 100000, 8000 pairs: d = 768 with a dense operand 90.8 / 79.1, without 50.0 / 41.0, d = 512 60.6 / 54.6; V = 33801,
+// d = 768 37.2 / 33.9, d = 512 26.9 / 26.6.  bf16 rows: d = 768 with one, V = 33801 34.1 / 35.2, V = 100000 81.3 / 79.3, without one 43.4 / 39.2,
+// d = 512 without one 32.4 / 34.8.
 // A range is taken to own its share of the pairs: one eighth of 32768 ids, d = 1024, 131072 fp32 pairs 38.2 / 40.7 us, with the
 // hottest id in it 53.5 / 55.3, with all hot ids in it 126.8 / 125.0; bf16 rows 36.6 / 37.7, 46.5 / 48.0, 94.2 / 94.0.
-bool deep_batches(int64_t n, int32_t d, int32_t V, int32_t row_dtype, int32_t C, bool in_place)
+bool deep_batches(int64_t n, int32_t d, int32_t V, int32_t row_dtype, int32_t C, bool in_place, bool to_bf16, bool dense)
 {
+    if (to_bf16 && (row_dtype == TS_ROW_FP32 || (V > 65536 && (d > 512 || dense)))) return false;
     if (d < kColBlock && n > (row_dtype == TS_ROW_FP32 && d <= 128 ? 49152 : 65536)) return false;
     if (n * d <= 8 << 20) return true;
     if (in_place) return false;
@@ -1989,7 +1994,7 @@ int densify_impl(const ShardTable& sh, int64_t n, int32_t row_dtype, int32_t d, 
     int32_t C = piece_tokens_for(n, wide);
     const int32_t group = C * group_pieces(C);
     if (!g_piece_override && group == 64 && pieces_of_8(n, d, V_total, row_dtype, wide)) C = 8;
-    const bool deep = deep_batches(n_own, d, V, row_dtype, C, in_place);
+    const bool deep = deep_batches(n_own, d, V, row_dtype, C, in_place, epi == EPI_SCALE_BF16, dense_in != nullptr);
     Plan pl;
     make_plan(n, d, V, C, &pl, false, group, range ? compute_units() : 0);
     if (!ws_v || (int64_t)pl.total > ws_bytes) return TS_ERR_WORKSPACE;

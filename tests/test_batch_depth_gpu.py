@@ -7,6 +7,7 @@ from paper_1905_04035_amd import binding as ts
 from paper_1905_04035_amd import workloads as wl
 
 from parity import check, run_gpu, run_oracle
+from test_epilogue_gpu import check_scaled
 from test_range_gpu import check_range
 
 pytestmark = pytest.mark.gpu
@@ -35,6 +36,17 @@ def test_in_place_and_small_gathers(d, n):
         assert _depth(700, d, pairs, wl.ROW_FP32) == deep             # many pairs per row
         assert _depth(4000, d, pairs, wl.ROW_FP32, in_place=True) == deep
         assert _depth(4000, d, pairs, wl.ROW_FP32) == 1
+
+
+@pytest.mark.parametrize("V,d,dt,dense,deep", [
+    (3000, 520, wl.ROW_FP32, True, 0), (3000, 520, wl.ROW_FP32, False, 0), (3000, 520, wl.ROW_BF16, True, 1), (65536, 384, wl.ROW_BF16, True, 1),
+    (65537, 384, wl.ROW_BF16, True, 0), (65537, 512, wl.ROW_BF16, False, 1), (65537, 520, wl.ROW_BF16, False, 0)])
+def test_a_bf16_result(monkeypatch, V, d, dt, dense, deep):
+    seen, read_views = {}, ts.ts_read_views
+    monkeypatch.setattr(ts, "ts_read_views", lambda *a: (seen.update(ts.ts_last_launch_info()), read_views(*a))[1])
+    w = wl.make_custom(V=V, d=d, n_list=[5000, 4900], zipf_s=1.1, seed=V + d, row_dtype=dt, integer_values=True)
+    check_scaled(w, 0.5, ts.TS_OUT_BF16, exact_bits=True, dense=dense)
+    assert (seen["piece_tokens"], seen["short_rows"], seen["deep_batches"]) == (16, 0, deep)
 
 
 # a range is taken to own its share of the pairs (rounded down), whatever it really owns
