@@ -2053,9 +2053,13 @@ int densify_impl(const ShardTable& sh, int64_t n, int32_t row_dtype, int32_t d, 
     // The budget counts the bytes that a copied row really moves: without a dense operand it is only
     // written, and a bf16 result is half as long (V = 33801, d = 1024, without a dense operand: 4987 pairs
     // 33.0 -> 32.0 us, 16384 pairs 42.8 -> 40.5; two or three times the rows per work-group 32.4-32.8 / 41.2-43.9).
-    const int64_t row_bytes = (int64_t)d * ((dense_in ? 4 : 0) + (epi == EPI_SCALE_BF16 ? 2 : 4));
+    // A bf16 result without one counts as an fp32 one beside a short sort: half the bytes again per work-group would
+    // make three times as many of them as compute units (V = 20000 / 33801, d = 1024, 12000 pairs 28.8 -> 27.0 us, 31.6 -> 28.8;
+    // 40000 pairs, a long sort, 57.4 with all of them, 59.9 with half).
+    int64_t elem_bytes = (dense_in ? 4 : 0) + (epi == EPI_SCALE_BF16 ? 2 : 4);
+    if (elem_bytes < 4 && n <= 22528 && g_overlap_sort < 0) elem_bytes = 4;
     const int64_t wg_elems = (int64_t)kBlindElems * kSortWaves;
-    int64_t copy_wgs = in_place ? 0 : budget / (row_bytes / d * wg_elems);
+    int64_t copy_wgs = in_place ? 0 : budget / (elem_bytes * wg_elems);
     // A work-group of these launches holds a compute unit (1024 threads, most of the LDS).  Where the
     // default budget comes to a little less than one work-group per compute unit in all, make it exactly
     // one: fewer leave compute units idle, and a few more than one leave a second round of stragglers

@@ -8,6 +8,7 @@ from paper_1905_04035_amd import binding as ts
 from paper_1905_04035_amd import workloads as wl
 
 from parity import check, run_gpu, run_oracle
+from test_epilogue_gpu import check_scaled
 
 pytestmark = pytest.mark.gpu
 
@@ -71,3 +72,24 @@ def test_copies_beside_a_sliced_sort(V, d, n):
     check(g, run_oracle(w), w, exact_bits=True)
     assert g["info"]["sort_slices"] == S
     assert g["info"]["sort_copy_rows_end"] == min(V, 2 * (wgs * 32768 // d))
+
+
+@pytest.mark.parametrize("dense,out,elem_bytes", [(True, ts.TS_OUT_FP32, 8), (True, ts.TS_OUT_BF16, 6), (False, ts.TS_OUT_FP32, 4),
+                                                  (False, ts.TS_OUT_BF16, 4)])
+@pytest.mark.parametrize("n", [3000, 22528, 22529])
+def test_the_budget_counts_bytes_that_move(monkeypatch, n, dense, out, elem_bytes):
+    # a bf16 result without a dense operand counts as an fp32 one, except beside a long sort
+    V, d = 40000, 1024
+    seen, read_views = {}, ts.ts_read_views
+    monkeypatch.setattr(ts, "ts_read_views", lambda *a: (seen.update(ts.ts_last_launch_info()), read_views(*a))[1])
+    w = wl.make_custom(V=V, d=d, n_list=[n], zipf_s=1.1, seed=n, integer_values=True)
+    check_scaled(w, 0.5, out, exact_bits=True, dense=dense)
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    G = -(-V // 512)
+    if n > 22528 and not dense and out == ts.TS_OUT_BF16:
+        elem_bytes = 2
+    budget = (32 << 20) + (n // 1024 << 20) if n <= 16384 else (48 << 20) + (n - 16384) // 1024 * (5 << 18)
+    wgs = budget // (elem_bytes * 32768)
+    if 4 * (G + wgs) >= 3 * cus and (G + wgs < cus or (dense and n <= 22528)):
+        wgs = cus - G
+    assert seen["sort_copy_rows_end"] == min(V, wgs * 32)
