@@ -2068,11 +2068,11 @@ int densify_impl(const ShardTable& sh, int64_t n, int32_t row_dtype, int32_t d, 
     // one where it comes to more, too, unless the sort is a long one or the copies read nothing: us with more / exactly one,
     // V = 32768, 18500 pairs, d = 1024 64.1 / 62.0, d = 512 36.5 / 34.5, d = 256 27.6 / 26.2; V = 60000, 5000 pairs, d = 512 47.3 / 44.7,
     // d = 256 28.6 / 25.9; 21000 pairs 32.0 / 31.2, 26000 pairs V = 131072 54.6 / 55.5; without a dense operand V = 60000, d = 512, 5000 pairs
-    // 24.1 / 27.0.)
+    // 24.1 / 27.0; 16000 pairs in 16 shards that begin inside shares, V = 57566, d = 512 51.8 / 53.3, V = 131072, d = 128 32.3 / 34.5.)
     if (pl.S == 1 && g_overlap_sort < 0 && copy_wgs > 0) {
         const int64_t cus = compute_units();
         const int64_t all = pl.G + copy_wgs;
-        const bool long_sort = n > (cut_share ? 16384 : 22528) || !dense_in;
+        const bool long_sort = n > 22528 || cut_share || !dense_in;
         if (cus > pl.G && 4 * all >= 3 * cus && (all < cus || !long_sort)) copy_wgs = cus - pl.G;
     }
     // Beside a sliced sort that leaves compute units idle: no more of them than that.  (More wait for the sort's, and the

@@ -36,10 +36,10 @@ def test_a_shard_that_begins_inside_a_share(dt):
 def test_one_work_group_per_compute_unit_in_small_calls(V, d, n):
     cus = torch.cuda.get_device_properties(0).multi_processor_count
     G = -(-V // 512)
-    wgs = (32 + n // 1024) * 4
-    if 4 * (G + wgs) >= 3 * cus:
-        wgs = cus - G
-    for lengths in ([n], [n // 2 + 1, n - n // 2 - 1]):
+    for lengths in ([n], [n // 2 + 1, n - n // 2 - 1]):         # the second begins inside a share
+        wgs = (32 + n // 1024) * 4
+        if 4 * (G + wgs) >= 3 * cus and (len(lengths) == 1 or G + wgs < cus):
+            wgs = cus - G
         assert _rows_copied(V, d, lengths) == min(V, wgs * 32768 // d)
 
 
