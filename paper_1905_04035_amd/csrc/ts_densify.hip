@@ -2078,8 +2078,9 @@ int densify_impl(const ShardTable& sh, int64_t n, int32_t row_dtype, int32_t d, 
     // Beside a sliced sort that leaves compute units idle: no more of them than that.  (More wait for the sort's, and the
     // two launches end late; where the sort fills the GPU anyway that costs nothing and copies are worth 1-5 %.)  us with
     // the budget / the idle ones: V = 41900, d = 256, 65536 pairs 49.8 / 44.8, uniform ids 53.6 / 46.8; d = 512, 97000 pairs 92.2 / 86.9;
-    // V = 60000, d = 512, 58000 pairs 84.5 / 80.3, bf16 rows 77.8 / 73.0.
-    if (pl.S > 1 && g_overlap_sort < 0) {
+    // V = 60000, d = 512, 58000 pairs 84.5 / 80.3, bf16 rows 77.8 / 73.0.  An fp32 result without a dense operand is written at
+    // the same rate wherever it is: V = 33801, d = 512, 58000 pairs 51.9 / 54.9 (a bf16 one 53.0 / 50.0).
+    if (pl.S > 1 && g_overlap_sort < 0 && (dense_in || epi == EPI_SCALE_BF16)) {
         const int64_t idle = (int64_t)compute_units() - (int64_t)pl.G * pl.S;
         if (idle > 0 && copy_wgs > idle) copy_wgs = idle;
     }

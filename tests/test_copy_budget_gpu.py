@@ -72,6 +72,10 @@ def test_copies_beside_a_sliced_sort(V, d, n):
     check(g, run_oracle(w), w, exact_bits=True)
     assert g["info"]["sort_slices"] == S
     assert g["info"]["sort_copy_rows_end"] == min(V, 2 * (wgs * 32768 // d))
+    # an fp32 result without a dense operand: the whole budget, in half the bytes per row
+    g = run_gpu(w, mode="multi", dense=False)
+    check(g, run_oracle(w, dense=False), w, exact_bits=True)
+    assert g["info"]["sort_copy_rows_end"] == min(V, 2 * ((256 if S <= 4 else 128) * 32768 // d))
 
 
 @pytest.mark.parametrize("dense,out,elem_bytes", [(True, ts.TS_OUT_FP32, 8), (True, ts.TS_OUT_BF16, 6), (False, ts.TS_OUT_FP32, 4),
