@@ -1728,7 +1728,9 @@ int piece_tokens_for(int64_t n, bool wide_bf16)
 // either way).  A piece's window is then 16 positions, and all its value rows are in flight at once: the launch of
 // a call with few pairs is as long as a wavefront's chain of batches.  But work-groups of eight wavefronts (and twice
 // as many of them) suit a launch that mostly copies or mostly gathers less.  fp32 rows, us with 8 / 16: V = 4000, d = 256,
-// 2000 pairs 13.1 / 14.9, 20000 pairs 24.0 / 22.9; V = 1000, d = 272, 8000 pairs 18.9 / 19.6, 12000 pairs 24.0 / 22.6; V = 16000, d = 512, 8000 pairs 23.8 / 25.5; V = 32768, d = 512, 8192 pairs
+// 2000 pairs 13.1 / 14.9, 20000 pairs 24.0 / 22.9; V = 1000, d = 272, 8000 pairs 18.9 / 19.6, 12000 pairs 24.0 / 22.6; V = 3000, d = 256,
+// 16000 pairs 19.3 / 20.0, 17500 pairs 23.2 / 22.2 (uniform ids 21.1 / 18.4); V = 9000, d = 512, 9200 pairs 21.1 / 21.0; V = 32768, d = 256,
+// 17500 pairs 24.1 / 24.8 (uniform ids 23.2 / 24.9); V = 16000, d = 512, 8000 pairs 23.8 / 25.5; V = 32768, d = 512, 8192 pairs
 // 30.1 / 28.0.  bf16 rows (half the bytes per row, half the work-groups), V = 32768: d = 512, 12000 pairs 30.7 / 33.9, 24000
 // pairs 38.5 / 41.3; d = 1024, 24000 pairs 63.9 / 63.3; d = 256, 100000 pairs 49.7 / 45.6.  The limits on the vocabulary cost
 // calls in place that touch little of a large one (fp32, V = 74365, d = 256, 3280 pairs 13.8 / 15.5; bf16, V = 131072, d = 512, 5000 pairs
@@ -1741,7 +1743,8 @@ bool pieces_of_8(int64_t n, int32_t d, int32_t V_total, int32_t row_dtype, bool 
 {
     const int64_t cols = (d + kColBlock - 1) / kColBlock * kColBlock;      // a piece has a wavefront per block
     if (wide) return d <= 512 && n <= 32768 && (int64_t)V_total * d <= 20 << 20;
-    return row_dtype == TS_ROW_FP32 && n * cols <= 9 << 19 && (int64_t)V_total * d <= 12 << 20;
+    // 8 << 19: 256 work-groups.  A few more are a second round, which only a launch with something to copy hides.
+    return row_dtype == TS_ROW_FP32 && n * cols <= ((int64_t)V_total * d < 5 << 20 ? 8 : 9) << 19 && (int64_t)V_total * d <= 12 << 20;
 }
 
 // Twice as many value rows in flight per wavefront (32-64 registers more, so fewer wavefronts): not

@@ -22,9 +22,11 @@ def _workload(V, d, n, dt, hot=()):
 
 
 @pytest.mark.parametrize("V,d,dt,n,piece", [
-    (3000, 1024, wl.ROW_FP32, 4608, 8), (3000, 1024, wl.ROW_FP32, 4609, 16), (12288, 1024, wl.ROW_FP32, 500, 8),
-    (12289, 1024, wl.ROW_FP32, 500, 16), (3000, 64, wl.ROW_FP32, 18432, 8), (3000, 64, wl.ROW_FP32, 18433, 16),
-    (1000, 260, wl.ROW_FP32, 9216, 8), (1000, 260, wl.ROW_FP32, 9217, 16), (1000, 516, wl.ROW_FP32, 6145, 16),
+    (3000, 1024, wl.ROW_FP32, 4096, 8), (3000, 1024, wl.ROW_FP32, 4097, 16),
+    (5120, 1024, wl.ROW_FP32, 4608, 8), (5119, 1024, wl.ROW_FP32, 4608, 16), (5120, 1024, wl.ROW_FP32, 4609, 16), (12288, 1024, wl.ROW_FP32, 500, 8),
+    (12289, 1024, wl.ROW_FP32, 500, 16), (3000, 64, wl.ROW_FP32, 16384, 8), (3000, 64, wl.ROW_FP32, 16385, 16),
+    (1000, 260, wl.ROW_FP32, 8192, 8), (1000, 260, wl.ROW_FP32, 8193, 16), (20172, 260, wl.ROW_FP32, 9216, 8),
+    (20172, 260, wl.ROW_FP32, 9217, 16), (1000, 516, wl.ROW_FP32, 6145, 16),
     (2000, 512, wl.ROW_BF16, 32768, 8), (2000, 512, wl.ROW_BF16, 32769, 16), (2000, 520, wl.ROW_BF16, 900, 16),
     (2000, 516, wl.ROW_BF16, 900, 16), (5000, 128, wl.ROW_FP32, 65536, 16), (5000, 128, wl.ROW_FP32, 65537, 16),
     (5000, 128, wl.ROW_BF16, 65537, 16), (5, 4, wl.ROW_FP32, 1, 8)])
@@ -35,7 +37,7 @@ def test_around_the_limits(V, d, dt, n, piece):
     check(g, run_oracle(w), w, exact_bits=True)
 
 
-@pytest.mark.parametrize("V,d,n,dt", [(1000, 64, 2048, wl.ROW_FP32), (4000, 256, 18000, wl.ROW_FP32),
+@pytest.mark.parametrize("V,d,n,dt", [(1000, 64, 2048, wl.ROW_FP32), (4000, 256, 16000, wl.ROW_FP32),
                                       (2000, 512, 30000, wl.ROW_BF16), (300, 264, 30000, wl.ROW_BF16)])
 @pytest.mark.parametrize("s", [1.1, 1.8])
 def test_measured_error_stays_under_the_a_priori_bound(V, d, n, dt, s):
