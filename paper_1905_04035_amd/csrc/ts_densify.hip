@@ -81,7 +81,7 @@ struct alignas(32) SortedPair {
 };
 static_assert(sizeof(SortedPair) == 32, "two 16-byte accesses per record");
 
-constexpr int kMaxPart = 2048;     // most ids one sort work-group owns (LDS: 18 x part x 4 B + 8 KiB of lists = 152 KiB)
+constexpr int kMaxPart = 2048;     // most ids one sort work-group owns (LDS: 88 KiB of tables and 68 KiB of lists)
 constexpr int kMinPart = 128;
 constexpr int kSortWaves = 16;     // wavefronts per sort work-group
 constexpr int kColBlock = 256;     // fp32 columns per wavefront item (64 lanes x 4)
@@ -97,9 +97,10 @@ constexpr int kPieceSmallMax = 96256;  // up to here pieces of 16 positions, abo
 // ------------------------------------------------------------------ device helpers
 __device__ __forceinline__ uint64_t ballot64(bool p) { return __ballot(p); }
 
-__device__ __forceinline__ uint32_t lanes_below(uint64_t m)
+// Lanes of m below this one, plus more.
+__device__ __forceinline__ uint32_t lanes_below(uint64_t m, uint32_t more = 0u)
 {
-    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, more));
 }
 
 __device__ __forceinline__ uint32_t bcast(uint32_t x, int lane) { return __builtin_amdgcn_readlane(x, lane); }
@@ -423,18 +424,53 @@ struct ShardTable {
     const char* rows[TS_MAX_SHARDS];
 };
 
-// Where pair idx lives: its id and the address of its value row.  Only shards j0..j1
-// (those that overlap the wavefront's range) are looked at; j0, j1 are wave-uniform.
-__device__ __forceinline__ void locate(const ShardTable& sh, int j0, int j1, int idx, bool valid,
-                                       int row_bytes, const int32_t*& idp, uint64_t& row_addr)
+// A wavefront's view of the shard table: lane j holds where shard j begins and its two arrays, moved back
+// by that much, so that pair idx has its id at ids + 4 idx and its value row at rows + idx row_bytes.  One
+// load per array for all shards (a walk over the table, entry by entry, is a chain of scalar loads).  Pairs
+// [a, b) of the wavefront lie in shards j0 .. j1, mostly one and the same.
+struct ShardView {
+    int32_t off_l;
+    uint64_t ids_l, rows_l;
+    int32_t j0, j1;
+    uint64_t ids0, rows0;       // of shard j0
+};
+
+__device__ __forceinline__ ShardView view_shards(const ShardTable& sh, int a, int b, int row_bytes, int lane)
 {
-    for (int j = j0; j <= j1; ++j) {
-        const int lo = sh.off[j], hi = sh.off[j + 1];
-        if (valid && idx >= lo && idx < hi) {
-            idp = sh.ids[j] + (idx - lo);
-            row_addr = (uint64_t)(uintptr_t)sh.rows[j] + (uint64_t)(idx - lo) * (uint64_t)row_bytes;
-        }
+    ShardView v;
+    v.off_l = 0;
+    v.j0 = v.j1 = 0;
+    v.ids_l = v.ids0 = (uint64_t)(uintptr_t)sh.ids[0];
+    v.rows_l = v.rows0 = (uint64_t)(uintptr_t)sh.rows[0];
+    if (sh.k > 1) {
+        const int j = min(lane, sh.k - 1);
+        v.off_l = sh.off[j];
+        v.ids_l = (uint64_t)(uintptr_t)sh.ids[j] - (uint64_t)(uint32_t)v.off_l * 4u;
+        v.rows_l = (uint64_t)(uintptr_t)sh.rows[j] - (uint64_t)(uint32_t)v.off_l * (uint64_t)(uint32_t)row_bytes;
+        // the last shard that begins at or before a, and the last one that begins before b
+        v.j0 = (int)__popcll(ballot64(lane < sh.k && v.off_l <= a)) - 1;
+        v.j1 = max((int)__popcll(ballot64(lane < sh.k && v.off_l < b)) - 1, v.j0);
+        v.ids0 = bcast64(v.ids_l, v.j0);
+        v.rows0 = bcast64(v.rows_l, v.j0);
     }
+    return v;
+}
+
+// The array (ids_l or rows_l) of the shard that pair idx lies in, where the wavefront's pairs lie in several.
+__device__ __forceinline__ uint64_t shard_base(const ShardView& v, uint64_t base0, uint64_t base_l, int idx)
+{
+    uint64_t base = base0;
+    for (int j = v.j0 + 1; j <= v.j1; ++j) {
+        const uint64_t next = bcast64(base_l, j);
+        if (idx >= (int)bcast((uint32_t)v.off_l, j)) base = next;
+    }
+    return base;
+}
+
+__device__ __forceinline__ int32_t load_id(uint64_t base, int idx)
+{
+    typedef const int32_t __attribute__((address_space(1))) * global_i32;
+    return *reinterpret_cast<global_i32>(base + (uint64_t)(uint32_t)idx * 4u);
 }
 
 // ------------------------------------------------------------------ sort
@@ -445,12 +481,13 @@ struct SortParams {
     // call's range belong to another owner: skipped, but not counted as bad.
     int32_t id_base, V_total;
     int32_t part;       // ids owned by one work-group (power of two)
-    int32_t list_cap;   // entries in a wavefront's list of owned pairs (a multiple of 64, at least 128)
+    int32_t list_cap;   // entries in a wavefront's list of owned pairs
+    uint32_t list_full; // a list with more entries may not hold another 4 tiles' pairs
     int32_t row_bytes;
     int32_t* count;
     int32_t* row_start;
     SortedPair* sorted;
-    uint32_t* tot;      // [S][G * part]   pairs per (slice, id)
+    uint32_t* tot;      // [S][G * part]   pairs per (slice, id), 16 bits each (WIDE: 32)
     uint32_t* below;    // [S][G]          pairs of the slice with a valid id below the part
     uint32_t* bad;      // [S]             pairs of the slice with an id outside [0, V)
     int32_t* n_valid;
@@ -476,127 +513,233 @@ __device__ __forceinline__ void blind_copy(const SortParams& p, int cw, int w, i
     copy_flat<EPI>(p.copy_in, p.copy_out, e, p.copy_e1, lane, p.scale);
 }
 
-// One wavefront walks its sub-slice [a, b) in rounds of kRoundTiles tiles of 64 pairs.
-// All ids of a round are loaded before any is used, so a round costs one memory
-// latency; with a single round (slices of at most 16384 pairs) the ids stay in
-// registers between the counting and the ranking pass.
+// One wavefront walks its sub-slice [a, b) in rounds of kRoundTiles tiles of 64 pairs.  All ids of a round are
+// loaded before any is used, so a round costs one memory latency.
 constexpr int kRoundTiles = 16;
 constexpr int kRoundPairs = kRoundTiles * 64;
 
-// ids0 / off0 describe shard j0; when the whole range lies in that shard (j0 == j1, the
-// common case) no table look-up is needed per tile.
-__device__ __forceinline__ void load_round(const ShardTable& sh, int j0, int j1, const int32_t* ids0, int off0,
-                                           int a0, int b, int lane, int32_t (&idr)[kRoundTiles])
+__device__ __forceinline__ void load_round(const ShardView& v, int a0, int b, int lane, int32_t (&idr)[kRoundTiles])
 {
+    // lanes past the end re-read the last pair, so that every load is unconditional and all of them are
+    // in flight together; such lanes are masked where ids are used
+    if (v.j0 == v.j1) {
 #pragma unroll
-    for (int u = 0; u < kRoundTiles; ++u) {
-        // lanes past the end re-read the last pair, so that every load is unconditional
-        // and all of them are in flight together; such lanes are masked where ids are used
-        const int idx = min(a0 + u * 64 + lane, b - 1);
-        const int32_t* idp = ids0 + (idx - off0);
-        if (j0 != j1) {
-            uint64_t unused = 0;
-            locate(sh, j0, j1, idx, true, 0, idp, unused);
+        for (int u = 0; u < kRoundTiles; ++u) idr[u] = load_id(v.ids0, min(a0 + u * 64 + lane, b - 1));
+    } else {
+#pragma unroll
+        for (int u = 0; u < kRoundTiles; ++u) {
+            const int idx = min(a0 + u * 64 + lane, b - 1);
+            idr[u] = load_id(shard_base(v, v.ids0, v.ids_l, idx), idx);
         }
-        idr[u] = *idp;
     }
 }
 
-// Walks the tiles of a round and appends the pairs that this work-group owns to the
-// wavefront's list, in input order (tiles in order, lanes in order).  An entry is
-// (id - lo) << 21 | position of the pair in the wavefront's sub-slice (ids per part <= 2^11,
-// pairs per sub-slice <= 2^21).  Every work-group looks at every pair of its slice but owns
-// few of them: counting and ranking walk the short list, which is kept from round to round.
-// The list holds cap entries (1024 when LDS allows, kListCap otherwise); when the next tile
-// might not fit, flush(list, count) consumes what is listed and the list starts again
-// (flushed tells the caller that the list no longer holds all owned pairs).  nown is the
-// number of entries in the list, before and after.
-// With TALLY the pairs with a valid id below the part and those with an id outside [0, V)
-// are counted as well (wave-uniform counts).
-constexpr int kListCap = 128;
+// Which of the pairs that it looks at a work-group counts besides the ones it owns: those with id - off
+// below `below` (unsigned).  Part 0, below which there is no id, counts the ids inside the vocabulary
+// (what is left are the bad ones); every other part the ids of the call that lie below the part.
+struct Tally {
+    uint32_t off, below;
+};
+
+__device__ __forceinline__ Tally tally_of(int g, int lo, int id_base, int V_total)
+{
+    Tally t;
+    t.off = g == 0 ? 0u : (uint32_t)id_base;
+    t.below = g == 0 ? (uint32_t)V_total : (uint32_t)lo;
+    return t;
+}
+
+// No id: below no tally's limit and in no part (ids are below 2^31).
+constexpr int32_t kNoId = -1;
+
+// Lanes past the sub-slice's end hold no id.
+__device__ __forceinline__ void mask_tail(int32_t (&idr)[kRoundTiles], int a0, int b, int lane)
+{
+    if (a0 + kRoundPairs > b) {
+#pragma unroll
+        for (int u = 0; u < kRoundTiles; ++u) idr[u] = a0 + u * 64 + lane < b ? idr[u] : kNoId;
+    }
+}
+
+// Appends the pairs of a round that this work-group owns to the wavefront's list, in input order
+// (tiles in order, lanes in order).  An entry is (id - lo) << 21 | position of the pair in the
+// wavefront's sub-slice (ids per part <= 2^11, pairs per sub-slice <= 2^21).  Every work-group looks at every
+// pair of its slice but owns few of them: counting and ranking walk the short list.  first = id_base + lo.
+// A wavefront issues one instruction at a time whatever its kind, and 16 of them share a compute unit here,
+// so the pass is bound by its instruction count; the tally is kept per lane (a compare and an add-with-carry;
+// a ballot, a population count and a scalar add cost more) and added up over the wavefront at the end.
 constexpr int kLdsBytes = 160 * 1024;       // LDS of a compute unit, the most a work-group can have
-
 constexpr int kListPosBits = 21;
+constexpr int kGroupTiles = 4;              // tiles that are listed between two looks at how full the list is (room)
 
-template <bool TALLY, bool FULL, typename Flush>
-__device__ __forceinline__ void own_tiles(const int32_t (&idr)[kRoundTiles], int a0, int b, uint32_t pos0, int lane,
-                                          int lo, uint32_t span, uint32_t id_base, uint32_t V_total, uint32_t* list,
-                                          uint32_t cap, uint32_t& nown, uint32_t& below, uint32_t& bad,
-                                          bool& flushed, Flush&& flush)
+template <bool TALLY, typename Room>
+__device__ __forceinline__ void list_round(const int32_t (&idr)[kRoundTiles], int a0, int b, uint32_t pos0, int lane, uint32_t first,
+                                           uint32_t span, const Tally& t, uint32_t* list, uint32_t& nown, uint32_t& tally, Room&& room)
 {
-    // The tallies are kept per lane and added up over the wavefront once per round: a wavefront issues
-    // one instruction at a time whatever its kind, and 16 of them share a compute unit here, so the
-    // pass is bound by its instruction count (a ballot, a population count and a scalar add per tally
-    // and tile cost more than a compare and an add-with-carry per lane).
-    uint32_t below_l = 0, bad_l = 0;
+    const uint32_t pos_l = pos0 + (uint32_t)lane;
 #pragma unroll
-    for (int u = 0; u < kRoundTiles; ++u) {
-        if (FULL || a0 + u * 64 < b) {
-            const bool valid = FULL || a0 + u * 64 + lane < b;
-            const uint32_t idg = (uint32_t)idr[u];
-            const uint32_t id = idg - id_base;          // row of the call; wraps to a huge number below the range
-            const uint32_t rel = id - (uint32_t)lo;
-            const bool own = valid && rel < span;
-            const uint64_t m = ballot64(own);
-            if (TALLY) {
-                below_l += (valid && id < (uint32_t)lo) ? 1u : 0u;
-                bad_l += (valid && idg >= V_total) ? 1u : 0u;
-            }
-            if (m) {
-                if (nown > cap - 64u) {
-                    flush(list, nown);
-                    nown = 0;
-                    flushed = true;
+    for (int v = 0; v < kRoundTiles; v += kGroupTiles) {
+        if (a0 + v * 64 < b) {
+            room();
+#pragma unroll
+            for (int u = v; u < v + kGroupTiles; ++u) {
+                const uint32_t idg = (uint32_t)idr[u];
+                const uint32_t rel = idg - first;
+                const bool own = rel < span;
+                const uint64_t m = ballot64(own);
+                if (TALLY) tally += idg - t.off < t.below ? 1u : 0u;
+                if (m) {
+                    if (own) list[lanes_below(m, nown)] = (rel << kListPosBits) | (pos_l + (uint32_t)(u * 64));
+                    nown += (uint32_t)__popcll(m);
                 }
-                if (own) list[nown + lanes_below(m)] = (rel << kListPosBits) | (pos0 + (uint32_t)(u * 64 + lane));
-                nown += (uint32_t)__popcll(m);
             }
         }
     }
-    if (TALLY) {
-        below += wave_sum(below_l);
-        bad += wave_sum(bad_l);
-    }
 }
 
-// A round whose 16 tiles are all full (every round but a sub-slice's last) needs no test of the
-// lanes against the sub-slice's end.
-template <bool TALLY, typename Flush>
-__device__ __forceinline__ void own_pairs(const int32_t (&idr)[kRoundTiles], int a0, int b, uint32_t pos0, int lane,
-                                          int lo, uint32_t span, uint32_t id_base, uint32_t V_total, uint32_t* list,
-                                          uint32_t cap, uint32_t& nown, uint32_t& below, uint32_t& bad,
-                                          bool& flushed, Flush&& flush)
+// Bound by its chain of latencies and, in the listing and in the work-groups that own the hottest ids, by its
+// instructions.  Launch (launches: counting + scattering) in us before / after the shard table is looked up by
+// lanes, the tables hold 16 bits, the lists a whole round, a round's ids are loaded while the one before is listed,
+// one tally is kept instead of two, and only ids that really meet in 64 list entries are ranked in a loop:
+// 16384 pairs, d = 1024, in place 9.5 / 8.2; 51200 pairs (95 MB of copies beside) 22.3 / 20.0; 80011 pairs in 8 shards of
+// several lengths 10.1 + 14.0 / 7.0 + 10.6; 131072 pairs 7.1 + 12.3 / 5.4 + 9.9; 262144 pairs, 38 % on one id, 8.5 + 22.8 / 7.6 + 17.5.
+//
+// The tables of pairs per (wavefront, id) in LDS.  Two ids share a word as long as the pairs of a slice fit
+// 16 bits: half the LDS to clear and to scan, and a work-group of 2048 ids has room for lists that hold a
+// whole round.  Larger slices (calls of more than 4 million pairs): a word per id (WIDE).
+constexpr int kNarrowSlice = 65536 - 1024;
+
+template <bool WIDE>
+__device__ __forceinline__ uint32_t tab_word(uint32_t rel) { return WIDE ? rel : rel >> 1; }
+template <bool WIDE>
+__device__ __forceinline__ uint32_t tab_shift(uint32_t rel) { return WIDE ? 0u : (rel & 1u) << 4; }
+template <bool WIDE>
+__device__ __forceinline__ uint32_t tab_get(uint32_t word, uint32_t shift) { return WIDE ? word : (word >> shift) & 0xFFFFu; }
+
+// Adds the pairs of a tile (or of 64 list entries; a lane without one holds no id of the part) to a table.
+// The pairs of the first lane's id are counted by that lane alone: a hot id would otherwise be one LDS
+// atomic per pair, all on one address.
+template <bool WIDE>
+__device__ __forceinline__ void count_ids(uint32_t* tab, uint32_t rel, int ll, int lane)
 {
-    if (a0 + kRoundPairs <= b)
-        own_tiles<TALLY, true>(idr, a0, b, pos0, lane, lo, span, id_base, V_total, list, cap, nown, below, bad, flushed, flush);
-    else
-        own_tiles<TALLY, false>(idr, a0, b, pos0, lane, lo, span, id_base, V_total, list, cap, nown, below, bad, flushed, flush);
+    const uint32_t rl = bcast(rel, ll);
+    const uint64_t sm = ballot64(rel == rl);
+    if (lane == ll) atomicAdd(&tab[tab_word<WIDE>(rl)], (uint32_t)__popcll(sm) << tab_shift<WIDE>(rl));
+    if (rel != rl && rel != 0xFFFFFFFFu) atomicAdd(&tab[tab_word<WIDE>(rel)], 1u << tab_shift<WIDE>(rel));
 }
 
 // The counting launch of a sort that takes several slices: work-group (g, s) counts the pairs of
-// slice s per id of part g (p.tot), those with a valid id below the part (p.below) and those
-// with an id outside the vocabulary (p.bad).  One LDS table for the whole work-group: the order
+// slice s per id of part g (p.tot: 16 bits each, WIDE 32), those with a valid id below the part (p.below) and
+// those with an id outside the vocabulary (p.bad).  One LDS table for the whole work-group: the order
 // of the pairs does not matter here.  It also clears the arrival counters of the reduce kernel,
 // and the work-groups past the counting ones copy dense rows like those of sort_kernel.
-template <int EPI>
+template <bool WIDE, int EPI>
 __global__ __launch_bounds__(1024) void count_kernel(SortParams p, ShardTable sh)
 {
-    extern __shared__ __align__(16) uint32_t tab[];     // [part]
+    extern __shared__ __align__(16) uint32_t tab[];     // [part] counts
+    __shared__ uint32_t red[kSortWaves];
+
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int nsort = p.G * p.S;
+    // what the sort's chain begins with, asked for in one go with the sizes above (else one more latency behind them)
+    asm volatile("" ::"s"(p.n), "s"(p.V), "s"(p.SL), "s"(p.id_base), "s"(p.part), "s"(sh.k), "s"(sh.ids[0]), "s"(sh.rows[0]));
+    if ((int)blockIdx.x >= nsort) {
+        blind_copy<EPI>(p, (int)blockIdx.x - nsort, w, lane);
+        return;
+    }
+    const int g = (int)blockIdx.x % p.G;
+    const int sl = (int)blockIdx.x / p.G;
+    const int part = p.part;
+    const int lo = g * part;
+    const uint32_t span = (uint32_t)min(part, p.V - lo);
+    const uint32_t first = (uint32_t)p.id_base + (uint32_t)lo;
+    const Tally t = tally_of(g, lo, p.id_base, p.V_total);
+
+    const int t0 = sl * p.SL;
+    const int t1 = (int)min((int64_t)p.n, (int64_t)t0 + p.SL);
+    const int L = p.SL / kSortWaves;
+    const int a = (int)min((int64_t)t1, (int64_t)t0 + (int64_t)w * L);
+    const int b = (int)min((int64_t)t1, (int64_t)a + L);
+    const int rounds = (b - a + kRoundPairs - 1) / kRoundPairs;
+    const ShardView v = view_shards(sh, a, b, 0, lane);
+
+    int32_t idr[kRoundTiles];
+    if (rounds > 0) load_round(v, a, b, lane, idr);
+    {
+        u4* const z = reinterpret_cast<u4*>(p.arrive);
+        for (int i = (int)blockIdx.x * 1024 + tid; i < p.arrive_vec; i += nsort * 1024) z[i] = (u4)(0u);
+    }
+    const int words = WIDE ? part : part / 2;
+    for (int i = tid; i < words; i += 1024) tab[i] = 0u;
+    __syncthreads();
+
+    uint32_t tally = 0;
+    for (int r = 0; r < rounds; ++r) {
+        const int a0 = a + r * kRoundPairs;
+        if (r > 0) load_round(v, a0, b, lane, idr);
+        mask_tail(idr, a0, b, lane);
+#pragma unroll
+        for (int u = 0; u < kRoundTiles; ++u) {
+            const uint32_t idg = (uint32_t)idr[u];
+            const uint32_t rel = idg - first;
+            const uint64_t m = ballot64(rel < span);
+            tally += idg - t.off < t.below ? 1u : 0u;
+            // many owned pairs in a tile: a hot id among them, most likely
+            if (__popcll(m) > 12) {
+                count_ids<WIDE>(tab, rel < span ? rel : 0xFFFFFFFFu, (int)__builtin_ctzll(m), lane);
+            } else if (rel < span) {
+                atomicAdd(&tab[tab_word<WIDE>(rel)], 1u << tab_shift<WIDE>(rel));
+            }
+        }
+    }
+    tally = wave_sum(tally);
+    if (lane == 0) red[w] = tally;
+    __syncthreads();
+    const size_t GW = (size_t)p.G * words;
+    for (int i = tid; i < words; i += 1024) p.tot[(size_t)sl * GW + (size_t)g * words + i] = tab[i];
+    if (w == 0) {
+        const uint32_t all = wave_sum(lane < kSortWaves ? red[lane] : 0u);
+        if (lane == 0) {
+            p.below[sl * p.G + g] = g == 0 ? 0u : all;
+            if (g == 0) p.bad[sl] = (uint32_t)(t1 - t0) - all;
+        }
+    }
+}
+
+// DEEP (a one-launch sort of more than one round): the ids of a round are loaded while the round before it is
+// listed.
+template <int MODE, bool WIDE, bool DEEP, int EPI>
+__global__ __launch_bounds__(1024) void sort_kernel(SortParams p, ShardTable sh)
+{
+    // [kSortWaves][words] counts, then per-id totals, starts and (with several slices) first positions of
+    // the slice's pairs, then [kSortWaves][list_cap] lists of owned pairs
+    extern __shared__ __align__(16) uint32_t cnt[];
     __shared__ uint32_t red[2 * kSortWaves];
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int nsort = p.G * p.S;
+    // what the sort's chain begins with, asked for in one go with the sizes above (else one more latency behind them)
+    asm volatile("" ::"s"(p.n), "s"(p.V), "s"(p.SL), "s"(p.id_base), "s"(p.part), "s"(sh.k), "s"(sh.ids[0]), "s"(sh.rows[0]));
     if ((int)blockIdx.x >= nsort) {
         blind_copy<EPI>(p, (int)blockIdx.x - nsort, w, lane);
         return;
     }
+    constexpr int E = WIDE ? 1 : 2;         // ids per word of a table
     const int g = (int)blockIdx.x % p.G;
     const int sl = (int)blockIdx.x / p.G;
     const int part = p.part;
+    const int words = part / E;
     const int lo = g * part;
     const uint32_t span = (uint32_t)min(part, p.V - lo);
+    const uint32_t first = (uint32_t)p.id_base + (uint32_t)lo;
+    uint32_t* const mycnt = cnt + w * words;
+    u2* const id_info = reinterpret_cast<u2*>(cnt + kSortWaves * words);       // pairs of the id, its first sorted position
+    uint32_t* const id_pos = reinterpret_cast<uint32_t*>(id_info + part);      // several slices: where this slice's begin
+    uint32_t* const list = id_pos + (MODE == SORT_SCATTER ? part : 0) + w * p.list_cap;
 
     const int t0 = sl * p.SL;
     const int t1 = (int)min((int64_t)p.n, (int64_t)t0 + p.SL);
@@ -604,187 +747,10 @@ __global__ __launch_bounds__(1024) void count_kernel(SortParams p, ShardTable sh
     const int a = (int)min((int64_t)t1, (int64_t)t0 + (int64_t)w * L);
     const int b = (int)min((int64_t)t1, (int64_t)a + L);
     const int rounds = (b - a + kRoundPairs - 1) / kRoundPairs;
-    int j0 = 0;
-    while (j0 < sh.k - 1 && sh.off[j0 + 1] <= a) ++j0;
-    int j1 = j0;
-    while (j1 < sh.k - 1 && sh.off[j1 + 1] < b) ++j1;
-    const int32_t* const ids0 = sh.ids[j0];
-    const int off0 = sh.off[j0];
+    const ShardView v = view_shards(sh, a, b, p.row_bytes, lane);
 
     int32_t idr[kRoundTiles];
-    if (rounds > 0) load_round(sh, j0, j1, ids0, off0, a, b, lane, idr);
-    {
-        u4* const z = reinterpret_cast<u4*>(p.arrive);
-        for (int i = (int)blockIdx.x * 1024 + tid; i < p.arrive_vec; i += nsort * 1024) z[i] = (u4)(0u);
-    }
-    for (int i = tid; i < part; i += 1024) tab[i] = 0u;
-    __syncthreads();
-
-    uint32_t below = 0, bad = 0;
-    // (tallies per lane, full rounds without the test against the sub-slice's end: as in own_tiles)
-    uint32_t below_l = 0, bad_l = 0;
-    auto count_tiles = [&](auto full_tag, int a0) {
-        constexpr bool FULL = decltype(full_tag)::value;
-#pragma unroll
-        for (int u = 0; u < kRoundTiles; ++u) {
-            if (FULL || a0 + u * 64 < b) {
-                const bool valid = FULL || a0 + u * 64 + lane < b;
-                const uint32_t idg = (uint32_t)idr[u];
-                const uint32_t id = idg - (uint32_t)p.id_base;      // row of the call; wraps to a huge number below the range
-                // a lane without a pair, or with another part's, holds no id of the part
-                const uint32_t rel = (valid && id - (uint32_t)lo < span) ? id - (uint32_t)lo : 0xFFFFFFFFu;
-                below_l += (valid && id < (uint32_t)lo) ? 1u : 0u;
-                bad_l += (valid && idg >= (uint32_t)p.V_total) ? 1u : 0u;
-                const uint64_t m = ballot64(rel != 0xFFFFFFFFu);
-                if (m) {
-                    // the pairs of the id that the first owning lane holds are counted by that lane
-                    // alone (a hot id would otherwise be one LDS atomic per pair), the others one by one
-                    const int ll = __builtin_ctzll(m);
-                    const uint32_t rl = bcast(rel, ll);
-                    const uint64_t sm = ballot64(rel == rl);
-                    if (lane == ll) atomicAdd(&tab[rl], (uint32_t)__popcll(sm));
-                    if (rel != rl && rel != 0xFFFFFFFFu) atomicAdd(&tab[rel], 1u);
-                }
-            }
-        }
-    };
-    for (int r = 0; r < rounds; ++r) {
-        const int a0 = a + r * kRoundPairs;
-        if (r > 0) load_round(sh, j0, j1, ids0, off0, a0, b, lane, idr);
-        if (a0 + kRoundPairs <= b)
-            count_tiles(std::true_type{}, a0);
-        else
-            count_tiles(std::false_type{}, a0);
-    }
-    below += wave_sum(below_l);
-    bad += wave_sum(bad_l);
-    if (lane == 0) {
-        red[w] = below;
-        red[kSortWaves + w] = bad;
-    }
-    __syncthreads();
-    const size_t GV = (size_t)p.G * part;
-    for (int i = tid; i < part; i += 1024) p.tot[(size_t)sl * GV + lo + i] = tab[i];
-    if (tid == 0) {
-        uint32_t bl = 0, bd = 0;
-#pragma unroll
-        for (int ww = 0; ww < kSortWaves; ++ww) {
-            bl += red[ww];
-            bd += red[kSortWaves + ww];
-        }
-        p.below[sl * p.G + g] = bl;
-        if (g == 0) p.bad[sl] = bd;
-    }
-}
-
-// The scan phase of sort_kernel for one work-group (see there).  E: consecutive ids per thread.
-constexpr uint32_t kSeveral = 0x80000000u;
-
-template <int MODE, int E>
-__device__ __forceinline__ void scan_part(const SortParams& p, uint32_t* cnt, uint32_t* id_total, uint32_t* id_start,
-                                          uint32_t* wsum, uint32_t base, int part, int lo, uint32_t span, int sl,
-                                          int tid, int lane, int w)
-{
-    typedef uint32_t vec __attribute__((ext_vector_type(E)));
-    const int i = tid * E;                  // first of this thread's ids; part is a multiple of E
-    const bool idt = i < part;
-    vec c[kSortWaves];
-    vec total = (vec)(0u), pre = (vec)(0u);
-    if (idt) {
-#pragma unroll
-        for (int ww = 0; ww < kSortWaves; ++ww) {
-            c[ww] = *reinterpret_cast<const vec*>(cnt + ww * part + i);
-            total += c[ww];
-        }
-        if (MODE == SORT_SCATTER) {
-            total = *reinterpret_cast<const vec*>(id_total + i);     // over all slices, fetched at the start of the kernel
-            pre = *reinterpret_cast<const vec*>(id_start + i);
-        }
-    }
-    uint32_t mine = 0;
-#pragma unroll
-    for (int e = 0; e < E; ++e) mine += total[e];
-    const uint32_t incl = wave_inclusive_scan(mine, lane);
-    if (lane == 63) wsum[w] = incl;
-    __syncthreads();
-    // what the wavefronts before this one hold: their sums, one per lane, added up
-    const uint32_t woff = wave_sum(lane < w ? wsum[lane] : 0u);
-    uint32_t rs = base + woff + incl - mine;        // first sorted position of this thread's first id
-    if (idt) {
-        vec start;
-#pragma unroll
-        for (int e = 0; e < E; ++e) {
-            start[e] = rs;
-            if (sl == 0 && (uint32_t)(i + e) < span) {
-                p.count[lo + i + e] = (int32_t)total[e];
-                p.row_start[lo + i + e] = (int32_t)rs;
-                if (lo + i + e == p.V - 1) {
-                    p.row_start[p.V] = (int32_t)(rs + total[e]);
-                    *p.n_valid = (int32_t)(rs + total[e]);
-                }
-            }
-            rs += total[e];
-        }
-        *reinterpret_cast<vec*>(id_total + i) = total;
-        *reinterpret_cast<vec*>(id_start + i) = start;
-        // a wavefront's running position of an id, with kSeveral set if the wavefront holds the id more
-        // than once (sorted positions stay below 2^31); the ranking pass only has to work on those
-        vec o = start + pre;
-#pragma unroll
-        for (int ww = 0; ww < kSortWaves; ++ww) {
-            vec several;
-#pragma unroll
-            for (int e = 0; e < E; ++e) several[e] = c[ww][e] > 1u ? kSeveral : 0u;
-            *reinterpret_cast<vec*>(cnt + ww * part + i) = o | several;
-            o += c[ww];
-        }
-    }
-    __syncthreads();
-}
-
-template <int MODE, int EPI>
-__global__ __launch_bounds__(1024) void sort_kernel(SortParams p, ShardTable sh)
-{
-    // [kSortWaves][part] counts, then [2][part] per-id totals and starts, then
-    // [kSortWaves][list_cap] lists of owned pairs
-    extern __shared__ __align__(16) uint32_t cnt[];
-    __shared__ uint32_t red[3 * kSortWaves];
-
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int nsort = p.G * p.S;
-    if ((int)blockIdx.x >= nsort) {
-        blind_copy<EPI>(p, (int)blockIdx.x - nsort, w, lane);
-        return;
-    }
-    const int g = (int)blockIdx.x % p.G;
-    const int sl = (int)blockIdx.x / p.G;
-    const int part = p.part;
-    const int lo = g * part;
-    const uint32_t span = (uint32_t)min(part, p.V - lo);
-    uint32_t* const mycnt = cnt + w * part;
-    uint32_t* const id_total = cnt + kSortWaves * part;
-    uint32_t* const id_start = id_total + part;
-    uint32_t* const list = id_start + part + w * p.list_cap;
-
-    const int t0 = sl * p.SL;
-    const int t1 = (int)min((int64_t)p.n, (int64_t)t0 + p.SL);
-    const int L = p.SL / kSortWaves;
-    const int a = (int)min((int64_t)t1, (int64_t)t0 + (int64_t)w * L);
-    const int b = (int)min((int64_t)t1, (int64_t)a + L);
-    const int rounds = (b - a + kRoundPairs - 1) / kRoundPairs;
-    int j0 = 0;
-    while (j0 < sh.k - 1 && sh.off[j0 + 1] <= a) ++j0;
-    int j1 = j0;
-    while (j1 < sh.k - 1 && sh.off[j1 + 1] < b) ++j1;
-
-    const int32_t* const ids0 = sh.ids[j0];
-    const char* const rows0 = sh.rows[j0];
-    const int off0 = sh.off[j0];
-
-    int32_t idr[kRoundTiles];
-    if (rounds > 0) load_round(sh, j0, j1, ids0, off0, a, b, lane, idr);
+    if (rounds > 0) load_round(v, a, b, lane, idr);
 
     if (MODE == SORT_FUSED) {
         // the first launch of a call clears the arrival counters of the reduce kernel
@@ -792,150 +758,216 @@ __global__ __launch_bounds__(1024) void sort_kernel(SortParams p, ShardTable sh)
         for (int i = (int)blockIdx.x * 1024 + tid; i < p.arrive_vec; i += nsort * 1024) z[i] = (u4)(0u);
     }
 
-    const size_t GV = (size_t)p.G * part;
-    uint32_t base_fetched = 0, nbad_fetched = 0;
+    uint32_t base = 0, nbad = 0;            // first sorted position of the part; bad ids
     if (MODE == SORT_SCATTER) {
         // Everything the counting launch has left, fetched here so that the latency runs beside
         // the ids'.  Per slice (lane s2 speaks for slice s2, at most 64 slices): the pairs below
-        // the part and the bad ids.  Per id (thread tid speaks for ids lo + tid, lo + tid + 1024,
-        // ...): its count in all slices and in the slices before this one, sixteen loads in flight
-        // at a time, kept where the scan below finds them.  (Measured: issuing more of these loads
-        // at once, or issuing them before the tables are cleared, lengthens the launch by 2-3 us.)
+        // the part and the bad ids.  Per id: its count in all slices and in the slices before this one,
+        // sixteen loads in flight at a time, kept where the scan below finds them.  (Measured: issuing
+        // more of these loads at once, or issuing them before the tables are cleared, lengthens the launch
+        // by 2-3 us.)
         const uint32_t bl = lane < p.S ? p.below[lane * p.G + g] : 0u;
         const uint32_t bd = lane < p.S ? p.bad[lane] : 0u;
-        for (int i = tid; i < part; i += 1024) {
-            uint32_t total = 0, pre = 0;
+        const size_t GW = (size_t)p.G * words;
+        if (tid < words) {
+            uint32_t total[E], pre[E];
+#pragma unroll
+            for (int e = 0; e < E; ++e) total[e] = pre[e] = 0u;
             for (int sb = 0; sb < p.S; sb += 16) {
                 uint32_t x[16];
 #pragma unroll
-                for (int q = 0; q < 16; ++q)
-                    x[q] = sb + q < p.S ? p.tot[(size_t)(sb + q) * GV + lo + i] : 0u;
+                for (int q = 0; q < 16; ++q) x[q] = sb + q < p.S ? p.tot[(size_t)(sb + q) * GW + (size_t)g * words + tid] : 0u;
 #pragma unroll
-                for (int q = 0; q < 16; ++q) {
-                    total += x[q];
-                    if (sb + q < sl) pre += x[q];
-                }
+                for (int q = 0; q < 16; ++q)
+#pragma unroll
+                    for (int e = 0; e < E; ++e) {
+                        const uint32_t c = tab_get<WIDE>(x[q], 16u * e);
+                        total[e] += c;
+                        if (sb + q < sl) pre[e] += c;
+                    }
             }
-            id_total[i] = total;
-            id_start[i] = pre;
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                id_info[tid * E + e].x = total[e];
+                id_pos[tid * E + e] = pre[e];
+            }
         }
-        base_fetched = wave_sum(bl);
-        nbad_fetched = wave_sum(bd);
+        base = wave_sum(bl);
+        nbad = wave_sum(bd);
     }
     // every wavefront clears its own table of counts, so none has to wait for the others before it
     // starts to list and count (the tables meet at the barrier before the scan)
     {
         u4* const c4 = reinterpret_cast<u4*>(mycnt);
-        for (int i = lane; i < part / 4; i += 64) c4[i] = (u4)(0u);
+        for (int i = lane; i < words / 4; i += 64) c4[i] = (u4)(0u);
     }
 
-    // pass 1: list the owned pairs, count them per (wavefront, id); count what lies below the part
-    uint32_t below = 0, bad = 0, nown = 0;
+    // pass 1: list the owned pairs, count them per (wavefront, id); tally the others.  A list that might not
+    // hold another four tiles' pairs (list_full: more entries than that; never, if it holds the whole sub-slice)
+    // is counted and started again, and the sub-slice walked again for the ranking.
+    const Tally t = tally_of(g, lo, p.id_base, p.V_total);
+    uint32_t tally = 0, nown = 0;
     bool flushed = false;
-    auto count_listed = [&](const uint32_t* l, uint32_t cnt_l) {
-        // the pairs of the id that the first entry holds are counted by one lane (a hot id
-        // would otherwise be one LDS atomic per pair, all on one address), the others one by one
-        for (uint32_t t0 = 0; t0 < cnt_l; t0 += 64) {
-            // a lane without an entry holds no id of the part; ballots of bare comparisons (one of a
-            // condition put together from several costs two more vector instructions)
-            const uint32_t rel = t0 + lane < cnt_l ? l[t0 + lane] >> kListPosBits : 0xFFFFFFFFu;
-            const uint32_t rl = bcast(rel, 0);
-            const uint64_t sm = ballot64(rel == rl);
-            if (lane == 0) atomicAdd(&mycnt[rl], (uint32_t)__popcll(sm));
-            if (rel != rl && rel != 0xFFFFFFFFu) atomicAdd(&mycnt[rel], 1u);
-        }
+    auto count_listed = [&]() {
+        for (uint32_t e0 = 0; e0 < nown; e0 += 64)
+            count_ids<WIDE>(mycnt, e0 + lane < nown ? list[e0 + lane] >> kListPosBits : 0xFFFFFFFFu, 0, lane);
     };
-    for (int r = 0; r < rounds; ++r) {
-        const int a0 = a + r * kRoundPairs;
-        if (r > 0) load_round(sh, j0, j1, ids0, off0, a0, b, lane, idr);
-        own_pairs<MODE == SORT_FUSED>(idr, a0, b, (uint32_t)(r * kRoundPairs), lane, lo, span, (uint32_t)p.id_base,
-                                      (uint32_t)p.V_total, list, (uint32_t)p.list_cap, nown, below, bad, flushed,
-                                      count_listed);
+    auto pass1 = [&](int32_t (&ids)[kRoundTiles], int rd) {
+        const int a0 = a + rd * kRoundPairs;
+        mask_tail(ids, a0, b, lane);
+        list_round<MODE == SORT_FUSED>(ids, a0, b, (uint32_t)(rd * kRoundPairs), lane, first, span, t, list, nown, tally, [&] {
+            if (nown > p.list_full) {
+                count_listed();
+                nown = 0;
+                flushed = true;
+            }
+        });
+    };
+    if constexpr (DEEP) {
+        // every load is unconditional (beyond the last round it reads the last pair again): a load that may or may
+        // not have been issued would be waited for with the ids of the round at hand
+        int32_t other[kRoundTiles];
+        for (int rd = 0; rd < rounds; rd += 2) {
+            load_round(v, a + (rd + 1) * kRoundPairs, b, lane, other);
+            pass1(idr, rd);
+            load_round(v, a + (rd + 2) * kRoundPairs, b, lane, idr);
+            if (rd + 1 < rounds) pass1(other, rd + 1);
+        }
+    } else {
+        for (int rd = 0; rd < rounds; ++rd) {
+            if (rd > 0) load_round(v, a + rd * kRoundPairs, b, lane, idr);
+            pass1(idr, rd);
+        }
     }
-    count_listed(list, nown);
-    if (lane == 0) {
-        red[w] = below;
-        red[kSortWaves + w] = bad;
+    count_listed();
+    if (MODE == SORT_FUSED) {
+        tally = wave_sum(tally);
+        if (lane == 0) red[w] = tally;
     }
     __syncthreads();
-    // the wavefronts' tallies, one per lane, added up across the wavefront (not 32 reads per thread)
-    uint32_t below_wg = 0, bad_wg = 0;
     if (MODE == SORT_FUSED) {
-        const uint32_t t = lane < 2 * kSortWaves ? red[lane] : 0u;
-        below_wg = wave_sum(lane < kSortWaves ? t : 0u);
-        bad_wg = wave_sum(lane < kSortWaves ? 0u : t);
-    }
-
-    uint32_t base = below_wg, nbad = bad_wg;       // first sorted position of the part; bad ids
-    if (MODE == SORT_SCATTER) {
-        base = base_fetched;
-        nbad = nbad_fetched;
+        // the wavefronts' tallies, one per lane, added up across the wavefront
+        const uint32_t all = wave_sum(lane < kSortWaves ? red[lane] : 0u);
+        base = g == 0 ? 0u : all;
+        nbad = (uint32_t)p.n - all;
     }
     if (sl == 0 && g == 0 && tid == 0) *p.n_bad = (int32_t)nbad;
 
-    // The ids of the part in one sweep: thread tid speaks for E = part / 1024 (at least 1)
-    // consecutive ids lo + E*tid .., read and written with one LDS access per table (8 bytes
-    // when E = 2).  Totals over the wavefronts (and slices), exclusive scan into first
-    // positions, running positions per wavefront; each id's count and first position are kept
-    // where the ranking pass reads them.
-    if (part > 1024) {
-        scan_part<MODE, 2>(p, cnt, id_total, id_start, red + 2 * kSortWaves, base, part, lo, span, sl, tid, lane, w);
-    } else {
-        scan_part<MODE, 1>(p, cnt, id_total, id_start, red + 2 * kSortWaves, base, part, lo, span, sl, tid, lane, w);
+    // The ids of the part in one sweep: thread tid speaks for the ids of word tid.  Totals over the
+    // wavefronts (and slices), exclusive scan into first positions, and per wavefront the pairs of the id that
+    // earlier wavefronts hold, packed as the counts are.  Each id's count and first position are kept where the
+    // ranking pass reads them.
+    {
+        typedef uint32_t vec __attribute__((ext_vector_type(E)));
+        const int i = tid * E;
+        const bool idt = tid < words;
+        uint32_t c[kSortWaves];
+        vec total = (vec)(0u), pre = (vec)(0u);
+        if (idt) {
+            uint32_t sum = 0;
+#pragma unroll
+            for (int ww = 0; ww < kSortWaves; ++ww) {
+                c[ww] = cnt[ww * words + tid];
+                sum += c[ww];
+            }
+            if (MODE == SORT_SCATTER) {
+                // over all slices, fetched at the start of the kernel
+#pragma unroll
+                for (int e = 0; e < E; ++e) total[e] = id_info[i + e].x;
+                pre = *reinterpret_cast<const vec*>(id_pos + i);
+            } else {
+#pragma unroll
+                for (int e = 0; e < E; ++e) total[e] = tab_get<WIDE>(sum, 16u * e);
+            }
+        }
+        uint32_t mine = 0;
+#pragma unroll
+        for (int e = 0; e < E; ++e) mine += total[e];
+        const uint32_t incl = wave_inclusive_scan(mine, lane);
+        if (lane == 63) red[kSortWaves + w] = incl;
+        __syncthreads();
+        // what the wavefronts before this one hold: their sums, one per lane, added up
+        const uint32_t woff = wave_sum(lane < w ? red[kSortWaves + lane] : 0u);
+        uint32_t rs = base + woff + incl - mine;        // first sorted position of this thread's first id
+        if (idt) {
+            vec start;
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                start[e] = rs;
+                if (sl == 0 && (uint32_t)(i + e) < span) {
+                    p.count[lo + i + e] = (int32_t)total[e];
+                    p.row_start[lo + i + e] = (int32_t)rs;
+                    if (lo + i + e == p.V - 1) {
+                        p.row_start[p.V] = (int32_t)(rs + total[e]);
+                        *p.n_valid = (int32_t)(rs + total[e]);
+                    }
+                }
+                rs += total[e];
+            }
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                u2 info;
+                info.x = total[e];
+                info.y = start[e];
+                id_info[i + e] = info;
+            }
+            if (MODE == SORT_SCATTER) *reinterpret_cast<vec*>(id_pos + i) = start + pre;
+            uint32_t o = 0;
+#pragma unroll
+            for (int ww = 0; ww < kSortWaves; ++ww) {
+                cnt[ww * words + tid] = o;
+                o += c[ww];
+            }
+        }
+        __syncthreads();
     }
 
     // pass 2: every owned pair takes the next position of its id.  The list keeps the pairs in
-    // input order and wavefronts own consecutive sub-slices, so the sort is stable.  Per 64
-    // list entries: one LDS read of the running positions, a scalar loop over the distinct
-    // ids among them (pairs of one id are ranked by lane), one LDS write by the last lane of
-    // each id.  If the owned pairs fitted the list, the list of pass 1 is still there; otherwise
-    // the sub-slice is walked again.
-    auto rank_listed = [&](const uint32_t* l, uint32_t cnt_l) {
-        for (uint32_t e0 = 0; e0 < cnt_l; e0 += 64) {
-            const bool own = e0 + lane < cnt_l;
-            const uint32_t ent = own ? l[e0 + lane] : 0u;
-            const uint32_t rel = ent >> kListPosBits;
+    // input order and wavefronts own consecutive sub-slices, so the sort is stable.  64 list entries at a time
+    // take numbers from the table, those of the first entry's id together (a hot id would be 64 LDS atomics on one
+    // address, one after the other: of 51200 pairs, 14 % on one id, its work-group ended 2 us later), the others with one
+    // LDS atomic each.  Entries of one id take theirs in no order that could be relied on, so what the table holds afterwards is
+    // read back: an id is among the 64 several times if and only if one of its entries finds more there than
+    // its own number and one.  The entries of such ids, and only those, are numbered again, by lane.
+    auto rank_listed = [&]() {
+        for (uint32_t e0 = 0; e0 < nown; e0 += 64) {
+            const bool own = e0 + lane < nown;
+            const uint32_t ent = own ? list[e0 + lane] : 0u;
+            const uint32_t rel = ent >> kListPosBits;       // (a lane without an entry looks where id 0 of the part stands)
             const int idx = a + (int)(ent & ((1u << kListPosBits) - 1u));
-            // An id that the wavefront holds once takes the table's position as it is.  Only ids it
-            // holds several times (flagged by the scan) go through the loop over distinct ids, which is
-            // what this pass spends its time on (13 instructions per distinct id).
-            const uint32_t tabv = own ? mycnt[rel] : 0u;
-            const uint32_t basev = tabv & ~kSeveral;
-            const uint32_t relx = tabv >= kSeveral ? rel : 0xFFFFFFFFu;     // no id to rank: equal to none
-            uint64_t m = ballot64(tabv >= kSeveral);
-            const uint32_t tot_l = own ? id_total[rel] : 0u;
-            const uint32_t rs_l = own ? id_start[rel] : 0u;
-            uint32_t pos = basev, next = 0;
-            bool leader = false;
+            uint32_t* const word = mycnt + tab_word<WIDE>(rel);
+            const uint32_t shift = tab_shift<WIDE>(rel);
+            const u2 info = id_info[rel];
+            const uint32_t pos = MODE == SORT_SCATTER ? id_pos[rel] : info.y;
+            const uint32_t relx = own ? rel : 0xFFFFFFFFu;
+            const uint32_t rel0 = bcast(relx, 0);
+            const uint64_t sm0 = ballot64(relx == rel0);
+            uint32_t number = 0, after = 1;
+            if (lane == 0 || (own && rel != rel0)) {
+                const uint32_t add = lane == 0 ? (uint32_t)__popcll(sm0) : 1u;
+                number = tab_get<WIDE>(__hip_atomic_fetch_add(word, add << shift, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP), shift);
+                after = tab_get<WIDE>(__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP), shift);
+            }
+            const uint32_t number0 = bcast(number, 0);
+            uint64_t m = ballot64(after != number + 1u) & ~sm0;
+            if (relx == rel0) number = number0 + lanes_below(sm0);
             while (m) {
-                const int ll = __builtin_ctzll(m);
-                const uint32_t rl = bcast(rel, ll);
+                const uint32_t rl = bcast(rel, (int)__builtin_ctzll(m));
                 const uint64_t sm = ballot64(relx == rl);
-                if (relx == rl) pos = basev + lanes_below(sm);
-                if (lane == ll) {
-                    leader = true;
-                    next = (basev + (uint32_t)__popcll(sm)) | kSeveral;
-                }
+                if (relx == rl) number = after - (uint32_t)__popcll(sm) + lanes_below(sm);
                 m &= ~sm;
             }
-            if (leader) mycnt[rel] = next;
-            // lanes exchange running positions through LDS from one step to the next: the
-            // hardware keeps a wavefront's LDS accesses in order, the compiler must too
-            asm volatile("" ::: "memory");
+            const uint64_t rows = v.j0 == v.j1 ? v.rows0 : shard_base(v, v.rows0, v.rows_l, idx);
             if (own) {
-                uint64_t row_addr = (uint64_t)(uintptr_t)rows0 + (uint64_t)(idx - off0) * (uint64_t)p.row_bytes;
-                if (j0 != j1) {
-                    const int32_t* idp = nullptr;
-                    locate(sh, j0, j1, idx, true, p.row_bytes, idp, row_addr);
-                }
-                u4* rec = reinterpret_cast<u4*>(p.sorted + pos);
+                const uint64_t row_addr = rows + (uint64_t)(uint32_t)idx * (uint64_t)(uint32_t)p.row_bytes;
+                u4* rec = reinterpret_cast<u4*>(p.sorted + (pos + number));
                 u4 r0, r1;
                 r0.x = (uint32_t)row_addr;
                 r0.y = (uint32_t)(row_addr >> 32);
                 r0.z = (uint32_t)lo + rel;
                 r0.w = (uint32_t)idx;
-                r1.x = tot_l;
-                r1.y = rs_l;
+                r1.x = info.x;
+                r1.y = info.y;
                 r1.z = 0u;
                 r1.w = 0u;
                 rec[0] = r0;
@@ -944,19 +976,18 @@ __global__ __launch_bounds__(1024) void sort_kernel(SortParams p, ShardTable sh)
         }
     };
     if (!flushed) {
-        rank_listed(list, nown);
+        rank_listed();
         return;
     }
-    nown = 0;
-    for (int r = 0; r < rounds; ++r) {
-        const int a0 = a + r * kRoundPairs;
-        if (rounds > 1) load_round(sh, j0, j1, ids0, off0, a0, b, lane, idr);
-        uint32_t unused0 = 0, unused1 = 0;
-        bool unused2 = false;
-        own_pairs<false>(idr, a0, b, (uint32_t)(r * kRoundPairs), lane, lo, span, (uint32_t)p.id_base,
-                         (uint32_t)p.V_total, list, (uint32_t)p.list_cap, nown, unused0, unused1, unused2, rank_listed);
+    // the list did not hold all owned pairs: the sub-slice once more, round by round
+    for (int rd = 0; rd < rounds; ++rd) {
+        const int a0 = a + rd * kRoundPairs;
+        load_round(v, a0, b, lane, idr);
+        mask_tail(idr, a0, b, lane);
+        nown = 0;
+        list_round<false>(idr, a0, b, (uint32_t)(rd * kRoundPairs), lane, first, span, t, list, nown, tally, [] {});
+        rank_listed();
     }
-    rank_listed(list, nown);
 }
 
 // ------------------------------------------------------------------ reduce
@@ -1672,6 +1703,9 @@ __global__ __launch_bounds__(1024) void unique_kernel(const int32_t* count, int 
 
 // ------------------------------------------------------------------ host side
 struct Plan {
+    bool wide_tab;              // tables of the sort: a word per id
+    uint32_t list_full;
+    size_t sort_lds;
     int32_t S, SL, G, part, list_cap, C, NB, NBG, levels, ncb;   // NB pieces in NBG groups   // ncb: 256-column blocks of a row; levels of the combine tree
     size_t off_nvalid, off_nbad, off_arrive, arrive_bytes, off_count, off_row_start, off_sorted, off_tot,
         off_below, off_bad, off_partial, total;
@@ -1774,6 +1808,18 @@ bool deep_batches(int64_t n, int32_t d, int32_t V, int32_t row_dtype, int32_t C,
     return n <= (row_dtype == TS_ROW_BF16 ? 8 : C >= 32 ? 16 : 4) * (int64_t)V;
 }
 
+// The lists of owned pairs: a wavefront's whole share where the LDS has room for it beside the tables, at least the
+// 1024 pairs of a round.
+void set_lists(Plan* pl)
+{
+    const int64_t share = pl->SL / kSortWaves;
+    const int64_t tables = ((int64_t)kSortWaves * pl->part / (pl->wide_tab ? 1 : 2) + (pl->S > 1 ? 3 : 2) * (int64_t)pl->part) * 4;
+    const int64_t room = (kLdsBytes - 256 - tables) / (kSortWaves * 4) / 64 * 64;
+    pl->list_cap = (int32_t)(share < room ? share : room);
+    pl->list_full = share <= room ? 0xFFFFFFFFu : (uint32_t)(pl->list_cap - kGroupTiles * 64);
+    pl->sort_lds = (size_t)tables + (size_t)kSortWaves * pl->list_cap * 4;
+}
+
 // bound: size the arrays that depend on how the sort is split (slices, parts) for the largest
 // split any call of at most n pairs and at most V rows can choose, so that the total never
 // shrinks when n or V grows.
@@ -1804,19 +1850,11 @@ void make_plan(int64_t n, int32_t d, int32_t V, int32_t C, Plan* pl, bool bound 
     int part = (pl->S > 1 && (int64_t)((V + kMaxPart - 1) / kMaxPart) * pl->S >= 256) ? kMaxPart : 1024;
     while (pl->S == 1 && part > kMinPart && (int64_t)((V + part - 1) / part) < 64) part >>= 1;
     if (g_part_override) part = g_part_override;
+    // the tables hold 16 bits per (wavefront, id) where the pairs of a slice fit, else 32
+    pl->wide_tab = pl->SL > kNarrowSlice;
+    if (pl->wide_tab && part > 1024) part = 1024;
     pl->part = part;
-    // a list that holds a whole round never has to be rebuilt; parts of 2048 ids leave room
-    // for short lists only
-    pl->list_cap = part <= 1024 ? kRoundPairs : kListCap;
-    // One launch that walks several rounds: a wavefront whose work-group owns more of its pairs than the
-    // list holds (a dominating id) would have to walk its share a second time to rank them; give the
-    // lists what the LDS has left, up to the wavefront's whole share.
-    if (pl->S == 1 && n > (int64_t)kSortWaves * kRoundPairs && part <= 1024) {
-        const int64_t share = (pl->SL / kSortWaves + 63) / 64 * 64;
-        const int64_t room = (kLdsBytes - 256 - (int64_t)(kSortWaves + 2) * part * 4) / (kSortWaves * 4) / 64 * 64;
-        const int64_t cap = share < room ? share : room;
-        if (cap > pl->list_cap) pl->list_cap = (int32_t)cap;
-    }
+    set_lists(pl);
     pl->G = (V + part - 1) / part;
     pl->C = C;
     pl->NB = (int32_t)((n + pl->C - 1) / pl->C);
@@ -1871,6 +1909,7 @@ void make_plan(int64_t n, int32_t d, int32_t V, int32_t C, Plan* pl, bool bound 
             pl->SL = kRangeSliceTokens;
             pl->off_below = below;
             pl->off_bad = bad;
+            set_lists(pl);
         }
     }
 }
@@ -1913,21 +1952,32 @@ int static_scratch(void** out)
 // The three kinds of launches, one instantiation per epilogue (the epilogue is a template
 // argument so that the plain path keeps its code).
 template <int EPI>
-void launch_count(dim3 grid, size_t lds, hipStream_t stream, const SortParams& sp, const ShardTable& sh)
+void launch_count(dim3 grid, const Plan& pl, hipStream_t stream, const SortParams& sp, const ShardTable& sh)
 {
-    hipLaunchKernelGGL((count_kernel<EPI>), grid, dim3(1024), lds, stream, sp, sh);
+    const size_t lds = (size_t)pl.part * (pl.wide_tab ? 4 : 2);
+    if (pl.wide_tab)
+        hipLaunchKernelGGL((count_kernel<true, EPI>), grid, dim3(1024), lds, stream, sp, sh);
+    else
+        hipLaunchKernelGGL((count_kernel<false, EPI>), grid, dim3(1024), lds, stream, sp, sh);
 }
 
 template <int EPI>
-void launch_sort_scatter(dim3 grid, size_t lds, hipStream_t stream, const SortParams& sp, const ShardTable& sh)
+void launch_sort_scatter(dim3 grid, const Plan& pl, hipStream_t stream, const SortParams& sp, const ShardTable& sh)
 {
-    hipLaunchKernelGGL((sort_kernel<SORT_SCATTER, EPI>), grid, dim3(1024), lds, stream, sp, sh);
+    if (pl.wide_tab)
+        hipLaunchKernelGGL((sort_kernel<SORT_SCATTER, true, false, EPI>), grid, dim3(1024), pl.sort_lds, stream, sp, sh);
+    else
+        hipLaunchKernelGGL((sort_kernel<SORT_SCATTER, false, false, EPI>), grid, dim3(1024), pl.sort_lds, stream, sp, sh);
 }
 
 template <int EPI>
-void launch_sort_fused(dim3 grid, size_t lds, hipStream_t stream, const SortParams& sp, const ShardTable& sh)
+void launch_sort_fused(dim3 grid, const Plan& pl, hipStream_t stream, const SortParams& sp, const ShardTable& sh)
 {
-    hipLaunchKernelGGL((sort_kernel<SORT_FUSED, EPI>), grid, dim3(1024), lds, stream, sp, sh);
+    static_assert(kFusedSortMax <= kNarrowSlice, "16 bits per id");
+    if (pl.SL <= kSortWaves * kRoundPairs)
+        hipLaunchKernelGGL((sort_kernel<SORT_FUSED, false, false, EPI>), grid, dim3(1024), pl.sort_lds, stream, sp, sh);
+    else
+        hipLaunchKernelGGL((sort_kernel<SORT_FUSED, false, true, EPI>), grid, dim3(1024), pl.sort_lds, stream, sp, sh);
 }
 
 // With events (benchmarks only) the launch goes through the variant that stamps them with the
@@ -2100,15 +2150,15 @@ int densify_impl(const ShardTable& sh, int64_t n, int32_t row_dtype, int32_t d, 
     sp.copy_out = dense_out;
     sp.scale = scale;
     sp.list_cap = pl.list_cap;
-    const size_t lds = ((size_t)(kSortWaves + 2) * pl.part + (size_t)kSortWaves * sp.list_cap) * sizeof(uint32_t);
+    sp.list_full = pl.list_full;
     if (pl.S == 1) {
         const dim3 g1 = sort_grid(sp);
-        TS_DISPATCH_EPI(epi, launch_sort_fused, g1, lds, stream, sp, sh);
+        TS_DISPATCH_EPI(epi, launch_sort_fused, g1, pl, stream, sp, sh);
     } else {
         const dim3 g1 = sort_grid(sp);
-        TS_DISPATCH_EPI(epi, launch_count, g1, (size_t)pl.part * sizeof(uint32_t), stream, sp, sh);
+        TS_DISPATCH_EPI(epi, launch_count, g1, pl, stream, sp, sh);
         const dim3 g2 = sort_grid(sp);
-        TS_DISPATCH_EPI(epi, launch_sort_scatter, g2, lds, stream, sp, sh);
+        TS_DISPATCH_EPI(epi, launch_sort_scatter, g2, pl, stream, sp, sh);
     }
     if (hipGetLastError() != hipSuccess) return TS_ERR_HIP;
 
