@@ -1,14 +1,16 @@
 """ctypes binding of libts_densify.so: the same names as include/ts_densify.h and
 include/ts_densify_tools.h (the calls for tests, benchmarks and tuning).
 
-Argument marshalling only.  Tensors are PyTorch tensors on the GPU (PyTorch is
-used for device memory and streams, nothing else); every step of the path runs
-in the library's kernels.  There is no fallback: if the library is missing or a
+Argument marshalling only, for the calls of a training step in native code
+(csrc/marshal.cpp, an extension module next to the library).  Tensors are PyTorch tensors on
+the GPU (PyTorch is used for device memory and streams, nothing else); every step of the path
+runs in the library's kernels.  There is no fallback: if the library or the module is missing or a
 call fails, an exception is raised.
 """
 from __future__ import annotations
 
 import ctypes as C
+import importlib.util
 import os
 from typing import Optional, Sequence
 
@@ -27,7 +29,10 @@ TS_MAX_SHARDS = 64
 LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)),
                         "libts_densify_san.so" if os.environ.get("TS_SANITIZE") == "1" else "libts_densify.so")
 
+MARSHAL_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "_marshal.so")
+
 _lib = None
+_marshal = None     # the extension module, loaded with the library
 
 
 class TsGrad(C.Structure):
@@ -83,8 +88,25 @@ def lib():
                      "ts_last_launch_info",
                      "ts_profile_begin", "ts_profile_end", "ts_set_piece_tokens", "ts_set_overlap_bytes", "ts_set_sort_part", "ts_set_short_rows"):
             getattr(l, name).restype = C.c_int
+        # what the extension module calls: addresses of the entry points
+        for name in ("ts_densify", "ts_densify_static", "ts_densify_bf16", "ts_densify_multi", "ts_densify_scaled",
+                     "ts_densify_range", "ts_accumulate"):
+            setattr(l, "at_" + name, C.cast(getattr(l, name), C.c_void_p).value)
+        _load_marshal()
         _lib = l
     return _lib
+
+
+def _load_marshal():
+    global _marshal
+    if _marshal is None:
+        if not os.path.exists(MARSHAL_PATH):
+            raise FileNotFoundError(
+                f"{MARSHAL_PATH} is missing: build it with `python -m paper_1905_04035_amd.build`")
+        spec = importlib.util.spec_from_file_location("_marshal", MARSHAL_PATH)
+        module = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(module)
+        _marshal = module
 
 
 def status_string(status: int) -> str:
@@ -106,32 +128,18 @@ def _stream(stream) -> C.c_void_p:
     return C.c_void_p(stream.cuda_stream)
 
 
-def _check_dense(d: int, V: int, dense_in, dense_out):
-    assert dense_out.is_cuda and dense_out.dtype == torch.float32 and dense_out.is_contiguous()
-    assert tuple(dense_out.shape) == (V, d)
-    if dense_in is not None:
-        assert dense_in.is_cuda and dense_in.dtype == torch.float32 and dense_in.is_contiguous()
-        assert tuple(dense_in.shape) == (V, d)
-
-
-def _check_pair(ids, rows, d: int, dtype):
-    assert ids.is_cuda and ids.dtype == torch.int32 and ids.is_contiguous()
-    assert rows.is_cuda and rows.dtype == dtype and rows.is_contiguous()
-    assert rows.numel() == ids.numel() * d
-
-
 # ---- raw calls (return the status; used by the error-path tests) -------------------------------
 def ts_densify_raw(ids_ptr, rows_ptr, n, d, V, dense_in_ptr, dense_out_ptr, stream_ptr=None) -> int:
     return lib().ts_densify(ids_ptr, rows_ptr, n, d, V, dense_in_ptr, dense_out_ptr, stream_ptr)
 
 
 # ---- the entry points ----------------------------------------------------------------------------
+# The extension module checks device, type, contiguity and lengths of the tensors (AssertionError) and
+# calls the entry point; stream None is PyTorch's current stream.
 def ts_densify(ids: torch.Tensor, rows: torch.Tensor, d: int, V: int,
                dense_in: Optional[torch.Tensor], dense_out: torch.Tensor, stream=None) -> None:
-    _check_pair(ids, rows, d, torch.float32)
-    _check_dense(d, V, dense_in, dense_out)
-    _check(lib().ts_densify(_p(ids), _p(rows), ids.numel(), d, V, _p(dense_in), _p(dense_out),
-                            _stream(stream)), "ts_densify")
+    l = lib()
+    _check(_marshal.densify(l.at_ts_densify, 4, ids, rows, d, V, dense_in, dense_out, stream), "ts_densify")
 
 
 TS_STATIC_SCRATCH_BYTES = 16 << 20
@@ -140,36 +148,24 @@ TS_STATIC_SCRATCH_BYTES = 16 << 20
 def ts_densify_static(ids: torch.Tensor, rows: torch.Tensor, d: int, V: int,
                       dense_in: Optional[torch.Tensor], dense_out: torch.Tensor, stream=None) -> None:
     """ts_densify on the library's built-in workspace: nothing is allocated or bound."""
-    _check_pair(ids, rows, d, torch.float32)
-    _check_dense(d, V, dense_in, dense_out)
-    _check(lib().ts_densify_static(_p(ids), _p(rows), ids.numel(), d, V, _p(dense_in), _p(dense_out),
-                                   _stream(stream)), "ts_densify_static")
+    l = lib()
+    _check(_marshal.densify(l.at_ts_densify_static, 4, ids, rows, d, V, dense_in, dense_out, stream),
+           "ts_densify_static")
 
 
 def ts_densify_bf16(ids: torch.Tensor, rows: torch.Tensor, d: int, V: int,
                     dense_in: Optional[torch.Tensor], dense_out: torch.Tensor, stream=None) -> None:
     """rows: uint16 / int16 / bfloat16 tensor holding bf16 bit patterns."""
-    assert rows.element_size() == 2
-    _check_pair(ids, rows, d, rows.dtype)
-    _check_dense(d, V, dense_in, dense_out)
-    _check(lib().ts_densify_bf16(_p(ids), _p(rows), ids.numel(), d, V, _p(dense_in), _p(dense_out),
-                                 _stream(stream)), "ts_densify_bf16")
+    l = lib()
+    _check(_marshal.densify(l.at_ts_densify_bf16, 2, ids, rows, d, V, dense_in, dense_out, stream), "ts_densify_bf16")
 
 
 def ts_densify_multi(ids_k: Sequence[torch.Tensor], rows_k: Sequence[torch.Tensor], row_dtype: int,
                      d: int, V: int, dense_in: Optional[torch.Tensor], dense_out: torch.Tensor,
                      stream=None) -> None:
-    k = len(ids_k)
-    assert k == len(rows_k)
-    for i, r in zip(ids_k, rows_k):
-        assert r.element_size() == (2 if row_dtype == TS_ROW_BF16 else 4)
-        _check_pair(i, r, d, r.dtype)
-    _check_dense(d, V, dense_in, dense_out)
-    ids_arr = (C.c_void_p * max(k, 1))(*[i.data_ptr() for i in ids_k])
-    rows_arr = (C.c_void_p * max(k, 1))(*[r.data_ptr() for r in rows_k])
-    n_arr = (C.c_int64 * max(k, 1))(*[i.numel() for i in ids_k])
-    _check(lib().ts_densify_multi(ids_arr, rows_arr, n_arr, k, row_dtype, d, V, _p(dense_in),
-                                  _p(dense_out), _stream(stream)), "ts_densify_multi")
+    l = lib()
+    _check(_marshal.multi(l.at_ts_densify_multi, ids_k, rows_k, row_dtype, d, V, dense_in, dense_out, stream),
+           "ts_densify_multi")
 
 
 def ts_densify_scaled(ids_k: Sequence[torch.Tensor], rows_k: Sequence[torch.Tensor], row_dtype: int,
@@ -177,39 +173,18 @@ def ts_densify_scaled(ids_k: Sequence[torch.Tensor], rows_k: Sequence[torch.Tens
                       stream=None) -> None:
     """out: [V, d] float32, or a 2-byte dtype (bfloat16 / int16 / uint16) for bf16 output; it may
     be a view into a larger buffer (a fusion buffer at the offset ts_fusion_place gives)."""
-    k = len(ids_k)
-    assert k == len(rows_k)
-    for i, r in zip(ids_k, rows_k):
-        assert r.element_size() == (2 if row_dtype == TS_ROW_BF16 else 4)
-        _check_pair(i, r, d, r.dtype)
-    assert out.is_cuda and out.is_contiguous() and out.numel() == V * d
-    assert out.dtype == torch.float32 or out.element_size() == 2
-    out_dtype = TS_OUT_FP32 if out.dtype == torch.float32 else TS_OUT_BF16
-    if dense_in is not None:
-        assert dense_in.is_cuda and dense_in.dtype == torch.float32 and dense_in.is_contiguous()
-        assert tuple(dense_in.shape) == (V, d)
-    ids_arr = (C.c_void_p * max(k, 1))(*[i.data_ptr() for i in ids_k])
-    rows_arr = (C.c_void_p * max(k, 1))(*[r.data_ptr() for r in rows_k])
-    n_arr = (C.c_int64 * max(k, 1))(*[i.numel() for i in ids_k])
-    _check(lib().ts_densify_scaled(ids_arr, rows_arr, n_arr, k, row_dtype, d, V, _p(dense_in), _p(out),
-                                   out_dtype, C.c_float(scale), _stream(stream)), "ts_densify_scaled")
+    l = lib()
+    _check(_marshal.scaled(l.at_ts_densify_scaled, ids_k, rows_k, row_dtype, d, V, dense_in, out, scale, stream),
+           "ts_densify_scaled")
 
 
 def ts_densify_range(ids_k: Sequence[torch.Tensor], rows_k: Sequence[torch.Tensor], row_dtype: int,
                      d: int, V: int, v_begin: int, v_end: int, dense_in: Optional[torch.Tensor],
                      dense_out: torch.Tensor, stream=None) -> None:
     """dense_in / dense_out: the [v_end - v_begin, d] slice of the owner of rows v_begin .. v_end - 1."""
-    k = len(ids_k)
-    assert k == len(rows_k)
-    for i, r in zip(ids_k, rows_k):
-        assert r.element_size() == (2 if row_dtype == TS_ROW_BF16 else 4)
-        _check_pair(i, r, d, r.dtype)
-    _check_dense(d, v_end - v_begin, dense_in, dense_out)
-    ids_arr = (C.c_void_p * max(k, 1))(*[i.data_ptr() for i in ids_k])
-    rows_arr = (C.c_void_p * max(k, 1))(*[r.data_ptr() for r in rows_k])
-    n_arr = (C.c_int64 * max(k, 1))(*[i.numel() for i in ids_k])
-    _check(lib().ts_densify_range(ids_arr, rows_arr, n_arr, k, row_dtype, d, V, v_begin, v_end, _p(dense_in),
-                                  _p(dense_out), _stream(stream)), "ts_densify_range")
+    l = lib()
+    _check(_marshal.range(l.at_ts_densify_range, ids_k, rows_k, row_dtype, d, V, v_begin, v_end, dense_in, dense_out,
+                          stream), "ts_densify_range")
 
 
 def ts_fusion_place(capacity_bytes: int, used_bytes: int, d: int, V: int, out_dtype: int = TS_OUT_FP32):
@@ -246,13 +221,11 @@ def ts_accumulate_strategy(grads, rule: int) -> int:
 def ts_accumulate(grads, rule: int, d: int, V: int, dense_out: Optional[torch.Tensor] = None,
                   ids_out: Optional[torch.Tensor] = None, rows_out: Optional[torch.Tensor] = None, stream=None):
     """Returns (strategy, n_slices); n_slices is None when the result is dense."""
-    cap = 0 if ids_out is None else ids_out.numel()
-    if rows_out is not None:
-        assert rows_out.is_cuda and rows_out.dtype == torch.float32 and rows_out.numel() >= cap * d
-    n_out, st = C.c_int64(-1), C.c_int32(-1)
-    _check(lib().ts_accumulate(_grad_array(grads), len(grads), rule, d, V, _p(dense_out), _p(ids_out),
-                               _p(rows_out), cap, C.byref(n_out), C.byref(st), _stream(stream)), "ts_accumulate")
-    return st.value, (n_out.value if n_out.value >= 0 else None)
+    l = lib()
+    status, strategy, n_out = _marshal.accumulate(l.at_ts_accumulate, grads, rule, d, V, dense_out, ids_out, rows_out,
+                                                  stream)
+    _check(status, "ts_accumulate")
+    return strategy, (n_out if n_out >= 0 else None)
 
 
 def ts_buffer_bytes(k: int, N: int, d: int, V: int, row_dtype: int = TS_ROW_FP32):

@@ -1,7 +1,9 @@
-"""Compiles csrc/*.hip for gfx950 into libts_densify.so next to this file."""
+"""Compiles csrc/*.hip for gfx950 into libts_densify.so next to this file, and csrc/marshal.cpp, the binding's
+marshalling (host code against PyTorch's headers), into _marshal.so."""
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -9,6 +11,9 @@ SRCS = [os.path.join(HERE, "csrc", f) for f in ("ts_densify.hip", "ts_accumulate
 LIB = os.path.join(HERE, "libts_densify.so")
 LIB_SAN = os.path.join(HERE, "libts_densify_san.so")     # host code under ASan + UBSan (checks of the host logic)
 INCLUDE = os.path.join(ROOT, "include")
+
+MARSHAL_SRC = os.path.join(HERE, "csrc", "marshal.cpp")
+MARSHAL = os.path.join(HERE, "_marshal.so")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
@@ -23,11 +28,30 @@ SAN_FLAGS = ["-g", "-Xarch_host", "-fsanitize=address", "-Xarch_host", "-fsaniti
              "-Xarch_host", "-fno-sanitize-recover=undefined", "-shared-libsan"]
 
 
+def marshal_command():
+    import torch
+
+    root = os.path.dirname(torch.__file__)
+    return [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wextra",
+            "-Wno-missing-field-initializers", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+            "-isystem", os.path.join(root, "include"), "-isystem", sysconfig.get_paths()["include"], "-I", INCLUDE,
+            "-o", MARSHAL, MARSHAL_SRC, "-L", os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
+
+
+def build_marshal(force: bool = True) -> str:
+    if force or not os.path.exists(MARSHAL):
+        res = subprocess.run(marshal_command(), capture_output=True, text=True)
+        if res.returncode != 0:
+            raise RuntimeError("g++ failed:\n" + res.stderr)
+    return MARSHAL
+
+
 def build(force: bool = True, verbose: bool = False, sanitize: bool = False) -> str:
     """sanitize=True: a second library whose HOST code runs under the address and
     undefined-behaviour sanitizers (device code unchanged); the loading process must have
     clang's shared sanitizer runtime preloaded."""
     lib = LIB_SAN if sanitize else LIB
+    build_marshal(force and not sanitize)
     if not force and os.path.exists(lib):
         return lib
     cmd = [HIPCC] + FLAGS + (SAN_FLAGS if sanitize else []) + ["-o", lib] + SRCS

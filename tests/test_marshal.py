@@ -1,0 +1,85 @@
+"""The binding's native marshalling: what it refuses (AssertionError before anything reaches the library, TypeError for
+what is no tensor), and that lists, tuples, gradients and streams arrive as they are."""
+import numpy as np
+import pytest
+import torch
+
+from paper_1905_04035_amd import binding as ts
+
+V, D, N = 50, 8, 20
+
+
+def _calls(dev, change=None):
+    """(name, call) of every entry point on valid tensors, one of them put in place by change."""
+    ids = torch.randint(V, (N,), dtype=torch.int32).to(dev)
+    a = dict(ids=ids, rows=torch.ones(N, D, device=dev), dense_in=torch.zeros(V, D, device=dev),
+             out=torch.empty(V, D, device=dev), rows16=torch.ones(N, D, dtype=torch.bfloat16, device=dev))
+    if change:
+        a.update({k: v for k, v in change(dict(a)).items()})
+    i, r, h, x, o = a["ids"], a["rows"], a["rows16"], a["dense_in"], a["out"]
+    return [("densify", lambda s=None: ts.ts_densify(i, r, D, V, x, o, s)),
+            ("static", lambda s=None: ts.ts_densify_static(i, r, D, V, x, o, s)),
+            ("bf16", lambda s=None: ts.ts_densify_bf16(i, h, D, V, x, o, s)),
+            ("multi", lambda s=None: ts.ts_densify_multi([i], (r,), ts.TS_ROW_FP32, D, V, x, o, s)),
+            ("scaled", lambda s=None: ts.ts_densify_scaled((i,), [r], ts.TS_ROW_FP32, D, V, x, o, 1.0, s)),
+            ("range", lambda s=None: ts.ts_densify_range([i], [r], ts.TS_ROW_FP32, D, V, 0, V, x, o, s)),
+            ("accumulate", lambda s=None: ts.ts_accumulate([("slices", i, r), ["dense", x]], ts.TS_RULE_PROPOSED, D, V, o, stream=s))]
+
+
+def test_tensors_that_are_not_on_the_gpu_are_refused():
+    for name, call in _calls("cpu"):
+        with pytest.raises(AssertionError):
+            call()
+
+
+def test_what_is_no_tensor_or_no_sequence():
+    t = torch.zeros(4, 4)
+    for args in (([1], [t]), (1, [t]), ([t], None)):
+        with pytest.raises(TypeError):
+            ts.ts_densify_multi(*args, ts.TS_ROW_FP32, 4, 4, None, t)
+    with pytest.raises(AssertionError):
+        ts.ts_densify_multi([], [t], ts.TS_ROW_FP32, 4, 4, None, t)
+    with pytest.raises(TypeError):
+        ts.ts_densify("ids", t, 4, 4, None, t)
+    with pytest.raises(AssertionError):
+        ts.ts_accumulate([()], ts.TS_RULE_TF, 4, 4, t)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("what,names", [
+    (lambda a: dict(ids=a["ids"].long()), "all"), (lambda a: dict(ids=a["ids"].cpu()), "all"),
+    (lambda a: dict(ids=torch.stack([a["ids"]] * 2, 1)[:, 0]), "all"),
+    (lambda a: dict(rows=a["rows"].cpu()), "fp32"), (lambda a: dict(rows=a["rows"].half()), "fp32"),
+    (lambda a: dict(rows=a["rows"].t().contiguous().t()), "fp32"), (lambda a: dict(rows=a["rows"][1:]), "but accumulate"),
+    (lambda a: dict(rows16=a["rows16"].float()), "bf16"),
+    (lambda a: dict(dense_in=a["dense_in"].double()), "all"), (lambda a: dict(dense_in=a["dense_in"][:, ::2]), "all"),
+    (lambda a: dict(dense_in=a["dense_in"][1:]), "but accumulate too"), (lambda a: dict(out=a["out"][1:]), "but accumulate too"),
+    (lambda a: dict(out=a["out"].double()), "but accumulate too")])
+def test_wrong_tensors_are_refused(what, names):
+    ws = ts.Workspace(N, D, V)
+    for name, call in _calls("cuda:0", what):
+        if {"all": True, "fp32": name != "bf16", "bf16": name == "bf16", "but accumulate": name not in ("bf16", "accumulate"),
+                "but accumulate too": name != "accumulate"}[names]:
+            with pytest.raises(AssertionError):
+                call()
+    ws.close()
+
+
+@pytest.mark.gpu
+def test_every_entry_point_on_streams():
+    ws = ts.Workspace(N, D, V)
+    side = torch.cuda.Stream()
+    for name, call in _calls("cuda:0"):
+        for stream in (None, side, torch.cuda.default_stream()):
+            call(stream)
+            torch.cuda.synchronize()
+        with torch.cuda.stream(side):
+            call()
+        torch.cuda.synchronize()
+    i = torch.randint(V, (N,), dtype=torch.int32, device="cuda:0")
+    r = torch.ones(N, D, device="cuda:0")
+    out = torch.empty(V, D, device="cuda:0")
+    ts.ts_densify_multi((i[:7], i[7:]), [r[:7], r[7:]], ts.TS_ROW_FP32, D, V, None, out)
+    want = np.bincount(i.cpu().numpy(), minlength=V).astype(np.float32)
+    assert np.array_equal(out.cpu().numpy(), np.repeat(want[:, None], D, 1))
+    ws.close()
