@@ -45,7 +45,7 @@ int ts_call_workspace_bytes(int64_t n_total, int32_t row_dtype, int32_t d, int32
  * [5] pieces; [6] levels of the tree in which the shares of a cut row are added up;
  * [7] bit 0: the call was in place; bits 1-2: how rows with at most C pairs were added up
  * (0 in the pieces, 1 row by row with the long rows by lone wavefronts, 2 row by row with the
- * long rows by work-groups); bit 3: in the pieces a wavefront had 16 fp32 or 8 bf16 value rows (d a
+ * long rows by work-groups, 3: the whole call was one launch, of work-groups that own [4] ids, and X = 0); bit 3: in the pieces a wavefront had 16 fp32 or 8 bf16 value rows (d a
  * multiple of 8) in flight instead of half as many.
  */
 int ts_last_launch_info(int32_t* info);

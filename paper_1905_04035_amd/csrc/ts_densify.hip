@@ -6,8 +6,8 @@
 //
 //     dense_out[v,:] = dense_in[v,:] + sum_{t : ids[t] == v} rows[t,:]
 //
-// Two launches per call (three when the pairs need more than one sort slice), all on the
-// caller's stream, no host synchronisation, no allocation:
+// Two launches per call (three when the pairs need more than one sort slice, one for the smallest calls:
+// small_kernel), all on the caller's stream, no host synchronisation, no allocation:
 //
 //   sort_kernel     stable counting sort of the pairs by id.  Work-group (g, s) owns `part`
 //                   consecutive ids (128 .. 2048) and slice s of the pairs; its 16
@@ -1674,6 +1674,363 @@ __global__ __launch_bounds__(64 * GP) void reduce_kernel(ReduceParams p)
         if (ref[t].k >= 0) combine_if_last<NV, EPI>(p, ref[t], cb, col, colok, lane, answer[t]);
 }
 
+// ------------------------------------------------------------------ small calls: one launch
+// A call with few pairs and a small output is as long as its chain of latencies: two launches of 5 us each with one
+// and a half between them.  small_kernel does it in one: V = 1000, d = 64, 2048 pairs with uniform ids 10.7 -> 7.4 us per call (more
+// sizes at small_call).  Work-group (g, cb) owns `part` consecutive ids and a block of 256 columns.  It sorts the pairs of
+// its ids as sort_kernel does (all pairs are looked at, its own listed, counted, scanned and ranked; dense_in of its rows is on
+// its way meanwhile), keeps the sorted pairs in LDS and adds up its own rows: longer rows by pieces of C sorted positions,
+// whose sums, and the shares of groups of pieces, meet in LDS; rows of at most C pairs, and rows without pairs, by the lanes of one
+// row.  Same order of additions as in the other kernels, same bits.  Rows narrower than 256 columns go several to a wavefront.
+constexpr int kSmallWaves = 16;
+constexpr int kSmallTiles = 4;              // of 64 pairs per wavefront
+constexpr int kSmallMax = kSmallWaves * kSmallTiles * 64;
+constexpr int kSmallSums = kSmallWaves * 64 * 2;
+constexpr int kSmallRows = 4;               // rows per lane at most
+
+struct SmallParams {
+    int32_t n, V, G, id_base, V_total, part, row_bytes, d;
+    int32_t C, lanes, rounds, combine_batch;    // lanes of a row; rounds of rows; shares that are added as a balanced tree
+    int32_t* count;
+    int32_t* row_start;
+    SortedPair* sorted;
+    int32_t* n_valid;
+    int32_t* n_bad;
+    const float* dense_in;
+    void* dense_out;
+    int32_t copy_untouched;
+    float scale;
+};
+
+// LDS: the counts per (wavefront, id), per id its pairs and first position, per sorted pair the address of its value row
+// its id within the part, the lists of owned pairs or the pieces' sums, and the shares of long rows.
+constexpr size_t small_lds(int n, int part, int lanes)
+{
+    return (size_t)kSmallWaves * part * 2 + (size_t)part * 8 + (size_t)((n + 7) / 8 * 8) * 10 + kSmallSums * 16 +
+           (size_t)(n / 64 + 2) * 2 * lanes * 16;
+}
+static_assert(kSmallMax * 4 <= kSmallSums * 16, "the lists fit in the place of the sums");
+
+template <typename RowT, int EPI>
+__global__ __launch_bounds__(64 * kSmallWaves) void small_kernel(SmallParams p, ShardTable sh)
+{
+    extern __shared__ __align__(16) uint32_t lds[];
+    __shared__ uint32_t red[2 * kSmallWaves];
+    typedef typename RowLoad<RowT, 1>::Raw Raw;
+
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int g = (int)blockIdx.x % p.G;
+    const int cb = (int)blockIdx.x / p.G;
+    const int part = p.part;
+    const int words = part / 2;
+    const int lo = g * part;
+    const uint32_t span = (uint32_t)min(part, p.V - lo);
+    const uint32_t first = (uint32_t)p.id_base + (uint32_t)lo;
+    const int L = ((p.n + kSmallWaves * 64 - 1) / (kSmallWaves * 64)) * 64;
+    uint32_t* const mycnt = lds + w * words;
+    u2* const id_info = reinterpret_cast<u2*>(lds + kSmallWaves * words);       // pairs of the id, its first sorted position
+    uint64_t* const row_addr = reinterpret_cast<uint64_t*>(id_info + part);
+    uint16_t* const pair_rel = reinterpret_cast<uint16_t*>(row_addr + (p.n + 7) / 8 * 8);
+    // the lists of owned pairs, and later in their place the pieces' sums: [piece][0: of a row that began before it, 1: of
+    // a row that begins in it][lane of the row]
+    f4* const chain = reinterpret_cast<f4*>(pair_rel + (p.n + 7) / 8 * 8);
+    // shares of long rows: two per group of 64 positions, as in the reduce kernel (share_slot, from the part's first group on)
+    f4* const share = chain + kSmallSums;
+    uint32_t* const list = reinterpret_cast<uint32_t*>(chain) + w * L;
+
+    const int a = min(p.n, w * L), b = min(p.n, a + L);
+    const ShardView v = view_shards(sh, a, b, p.row_bytes, lane);
+    int32_t idr[kSmallTiles];
+    if (a < b) {
+#pragma unroll
+        for (int u = 0; u < kSmallTiles; ++u) {
+            if (u * 64 < L) {
+                const int idx = min(a + u * 64 + lane, b - 1);
+                idr[u] = load_id(v.j0 == v.j1 ? v.ids0 : shard_base(v, v.ids0, v.ids_l, idx), idx);
+            }
+        }
+    }
+    // the lanes of a row; a lane past the row's last column reads the last columns again and stores nothing
+    const int sub = lane / p.lanes, sl = lane - sub * p.lanes, per_wave = 64 / p.lanes;
+    const int col = cb * kColBlock + sl * 4;
+    const bool colok = col < p.d;
+    const int colr = min(col, p.d - 4);
+    f4 dn[kSmallRows];
+#pragma unroll
+    for (int it = 0; it < kSmallRows; ++it) {
+        dn[it] = (f4)(0.0f);
+        const int r = (it * kSmallWaves + w) * per_wave + sub;
+        if (it < p.rounds && p.dense_in && p.copy_untouched)
+            dn[it] = load_f4_stream(p.dense_in + (size_t)(lo + min(r, (int)span - 1)) * p.d + colr);
+    }
+    for (int i = lane; i < words; i += 64) mycnt[i] = 0u;
+
+    const Tally t = tally_of(g, lo, p.id_base, p.V_total);
+    uint32_t tally = 0, nown = 0;
+#pragma unroll
+    for (int u = 0; u < kSmallTiles; ++u) {
+        if (a + u * 64 < b) {
+            const uint32_t idg = (uint32_t)(a + u * 64 + lane < b ? idr[u] : kNoId);
+            const uint32_t rel = idg - first;
+            const bool own = rel < span;
+            const uint64_t m = ballot64(own);
+            tally += idg - t.off < t.below ? 1u : 0u;
+            if (own) list[lanes_below(m, nown)] = (rel << kListPosBits) | (uint32_t)(u * 64 + lane);
+            nown += (uint32_t)__popcll(m);
+        }
+    }
+    for (uint32_t e0 = 0; e0 < nown; e0 += 64)
+        count_ids<false>(mycnt, e0 + lane < nown ? list[e0 + lane] >> kListPosBits : 0xFFFFFFFFu, 0, lane);
+    tally = wave_sum(tally);
+    if (lane == 0) red[w] = tally;
+    __syncthreads();
+    const uint32_t all = wave_sum(lane < kSmallWaves ? red[lane] : 0u);
+    const uint32_t base = g == 0 ? 0u : all;        // first sorted position of the part
+    if (g == 0 && cb == 0 && tid == 0) *p.n_bad = (int32_t)((uint32_t)p.n - all);
+    {
+        const bool idt = tid < words;
+        uint32_t c[kSmallWaves], sum = 0;
+        if (idt) {
+#pragma unroll
+            for (int ww = 0; ww < kSmallWaves; ++ww) {
+                c[ww] = lds[ww * words + tid];
+                sum += c[ww];
+            }
+        }
+        const uint32_t t0 = sum & 0xFFFFu, t1 = sum >> 16;
+        const uint32_t incl = wave_inclusive_scan(t0 + t1, lane);
+        if (lane == 63) red[kSmallWaves + w] = incl;
+        __syncthreads();
+        const uint32_t woff = wave_sum(lane < w ? red[kSmallWaves + lane] : 0u);
+        const uint32_t s0 = base + woff + incl - t0 - t1, s1 = s0 + t0;
+        if (idt) {
+            u4 info;
+            info.x = t0;
+            info.y = s0;
+            info.z = t1;
+            info.w = s1;
+            *reinterpret_cast<u4*>(id_info + 2 * tid) = info;
+            uint32_t o = 0;
+#pragma unroll
+            for (int ww = 0; ww < kSmallWaves; ++ww) {
+                lds[ww * words + tid] = o;
+                o += c[ww];
+            }
+            if (cb == 0) {
+                const int i = lo + 2 * tid;
+                if (2 * tid < (int)span) {
+                    p.count[i] = (int32_t)t0;
+                    p.row_start[i] = (int32_t)s0;
+                    if (i == p.V - 1) {
+                        p.row_start[p.V] = (int32_t)s1;
+                        *p.n_valid = (int32_t)s1;
+                    }
+                }
+                if (2 * tid + 1 < (int)span) {
+                    p.count[i + 1] = (int32_t)t1;
+                    p.row_start[i + 1] = (int32_t)s1;
+                    if (i + 1 == p.V - 1) {
+                        p.row_start[p.V] = (int32_t)(s1 + t1);
+                        *p.n_valid = (int32_t)(s1 + t1);
+                    }
+                }
+            }
+        }
+        __syncthreads();
+    }
+    // (as in sort_kernel)
+    for (uint32_t e0 = 0; e0 < nown; e0 += 64) {
+        const bool own = e0 + lane < nown;
+        const uint32_t ent = own ? list[e0 + lane] : 0u;
+        const uint32_t rel = ent >> kListPosBits;
+        const int idx = a + (int)(ent & ((1u << kListPosBits) - 1u));
+        uint32_t* const word = mycnt + tab_word<false>(rel);
+        const uint32_t shift = tab_shift<false>(rel);
+        const u2 info = id_info[rel];
+        const uint32_t relx = own ? rel : 0xFFFFFFFFu;
+        const uint32_t rel0 = bcast(relx, 0);
+        const uint64_t sm0 = ballot64(relx == rel0);
+        uint32_t number = 0, after = 1;
+        if (lane == 0 || (own && rel != rel0)) {
+            const uint32_t add = lane == 0 ? (uint32_t)__popcll(sm0) : 1u;
+            number = tab_get<false>(__hip_atomic_fetch_add(word, add << shift, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP), shift);
+            after = tab_get<false>(__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP), shift);
+        }
+        const uint32_t number0 = bcast(number, 0);
+        uint64_t m = ballot64(after != number + 1u) & ~sm0;
+        if (relx == rel0) number = number0 + lanes_below(sm0);
+        while (m) {
+            const uint32_t rl = bcast(rel, (int)__builtin_ctzll(m));
+            const uint64_t sm = ballot64(relx == rl);
+            if (relx == rl) number = after - (uint32_t)__popcll(sm) + lanes_below(sm);
+            m &= ~sm;
+        }
+        const uint64_t rows = v.j0 == v.j1 ? v.rows0 : shard_base(v, v.rows0, v.rows_l, idx);
+        if (own) {
+            const uint64_t addr = rows + (uint64_t)(uint32_t)idx * (uint64_t)(uint32_t)p.row_bytes;
+            const uint32_t pos = info.y + number;
+            row_addr[pos - base] = addr;
+            pair_rel[pos - base] = (uint16_t)rel;
+            if (cb == 0) {
+                u4* rec = reinterpret_cast<u4*>(p.sorted + pos);
+                u4 r0, r1;
+                r0.x = (uint32_t)addr;
+                r0.y = (uint32_t)(addr >> 32);
+                r0.z = (uint32_t)lo + rel;
+                r0.w = (uint32_t)idx;
+                r1.x = info.x;
+                r1.y = info.y;
+                r1.z = 0u;
+                r1.w = 0u;
+                rec[0] = r0;
+                rec[1] = r1;
+            }
+        }
+    }
+    __syncthreads();
+
+    const uint32_t off = (uint32_t)colr * (uint32_t)sizeof(RowT);
+    const auto load_pair = [&](int lp) {
+        typedef const Raw __attribute__((address_space(1))) * global_raw;
+        return __builtin_nontemporal_load(reinterpret_cast<global_raw>(row_addr[lp] + off));
+    };
+    // Longer rows, piece by piece: a piece to the lanes of one row, as many groups of pieces at a time as there are such
+    // lanes.  A piece holds a part of a long row that began before it, and of one that begins in it.
+    const int own_end = (int)(id_info[span - 1].x + id_info[span - 1].y);       // one behind the part's last position
+    const int k_first = (int)base >> 6, k_last = own_end > (int)base ? (own_end - 1) >> 6 : k_first - 1;
+    const int slots = kSmallWaves * per_wave, slot = w * per_wave + sub;
+    const int logC = 31 - __builtin_clz((unsigned)p.C), log_pieces = 6 - logC;
+    for (int kt = k_first; kt <= k_last; kt += slots >> log_pieces) {
+        const int q0 = kt << log_pieces, piece = q0 + slot;             // first piece of this turn, and the one at hand
+        const int group = piece >> log_pieces, g_first = group << log_pieces, g_last = g_first + (1 << log_pieces) - 1;
+        const int begin = max(piece << logC, (int)base), end = min((piece + 1) << logC, own_end);
+        // the row that has the piece's first position, and the one that has its last
+        int rel[2] = {0, 0}, s[2] = {0, 0}, c[2] = {0, 0};
+        f4 d0[2];
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            d0[t] = (f4)(0.0f);
+            if (begin < end) {
+                rel[t] = pair_rel[(t == 0 ? begin : end - 1) - (int)base];
+                const u2 info = id_info[rel[t]];
+                s[t] = (int)info.y;
+                c[t] = (int)info.x > p.C && (t == 0 || rel[1] != rel[0]) ? (int)info.x : 0;
+            }
+            if (c[t]) {
+                const int p0 = max(begin, s[t]), p1 = min(end, s[t] + c[t]);
+                if (p.dense_in && s[t] >= group << 6 && (s[t] + c[t] - 1) >> logC == piece)
+                    d0[t] = load_f4_stream(p.dense_in + (size_t)(lo + rel[t]) * p.d + colr);
+                f4 acc = (f4)(0.0f);
+                for (int at = p0; at < p1; at += 8) {
+                    Raw raw[8];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) {
+                        raw[u] = Raw{};
+                        if (at + u < p1) raw[u] = load_pair(at + u - (int)base);
+                    }
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) {
+                        f4 x[1];
+                        RowLoad<RowT, 1>::widen(raw[u], x);
+                        if (at + u < p1) acc = acc + x[0];
+                    }
+                }
+                chain[(slot * 2 + (s[t] >= piece << logC ? 1 : 0)) * p.lanes + sl] = acc;
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            if (c[t]) {
+                const int piece_first = s[t] >> logC, piece_last = (s[t] + c[t] - 1) >> logC;
+                if (piece == min(piece_last, g_last)) {
+                    const int x0 = max(piece_first, g_first);
+                    f4 tot = chain[((x0 - q0) * 2 + (x0 == piece_first ? 1 : 0)) * p.lanes + sl];
+                    for (int x = x0 + 1; x <= piece; ++x) tot = tot + chain[(x - q0) * 2 * p.lanes + sl];
+                    if (piece_first >= g_first && piece_last <= g_last) {
+                        if (colok) store_out<EPI>(p.dense_out, (size_t)(lo + rel[t]) * p.d + col, tot + d0[t], p.scale);
+                    } else {
+                        share[(share_slot(s[t] >> 6, group - (s[t] >> 6)) - 2 * k_first) * p.lanes + sl] = tot;
+                    }
+                }
+            }
+        }
+        if (kt + (slots >> log_pieces) <= k_last) __syncthreads();      // the sums are overwritten next
+    }
+
+    // rows without pairs and of at most C pairs
+#pragma unroll
+    for (int it = 0; it < kSmallRows; ++it) {
+        const int r = (it * kSmallWaves + w) * per_wave + sub;
+        if (it < p.rounds && r < (int)span) {
+            const u2 info = id_info[r];
+            const int c = (int)info.x, lp = (int)(info.y - base);
+            if (c <= p.C && (c > 0 || p.copy_untouched)) {
+                f4 out[1] = {dn[it]};
+                if (c > 0) {
+                    if (!p.copy_untouched && p.dense_in) dn[it] = load_f4_stream(p.dense_in + (size_t)(lo + r) * p.d + colr);
+                    f4 acc[1] = {(f4)(0.0f)};
+                    for (int j0 = 0; j0 < c; j0 += 8) {
+                        Raw raw[8];
+#pragma unroll
+                        for (int u = 0; u < 8; ++u) {
+                            raw[u] = Raw{};
+                            if (j0 + u < c) raw[u] = load_pair(lp + j0 + u);
+                        }
+#pragma unroll
+                        for (int u = 0; u < 8; ++u) {
+                            f4 x[1];
+                            RowLoad<RowT, 1>::widen(raw[u], x);
+                            if (j0 + u < c) acc[0] = acc[0] + x[0];
+                        }
+                    }
+                    out[0] = acc[0] + dn[it];
+                }
+                if (colok) store_out<EPI>(p.dense_out, (size_t)(lo + r) * p.d + col, out[0], p.scale);
+            }
+        }
+    }
+
+    if (k_first >= k_last) return;          // (the same for the whole work-group)
+    __syncthreads();
+    // rows that span several groups: the shares as combine_if_last adds them, by the lanes of group k, the row's second one
+    for (int k = k_first + 1 + slot; k <= k_last; k += slots) {
+        const int rel = pair_rel[(k << 6) - (int)base];
+        const u2 info = id_info[rel];
+        const int c = (int)info.x, s = (int)info.y;
+        const int k0 = s >> 6;
+        if (c <= p.C || k0 != k - 1) continue;
+        f4 d0 = (f4)(0.0f);
+        if (p.dense_in) d0 = load_f4_stream(p.dense_in + (size_t)(lo + rel) * p.d + colr);
+        int Pl = ((s + c - 1) >> 6) - k0 + 1;
+        f4 tot = (f4)(0.0f);
+        for (int shift = 0;; shift += kLogFanIn) {
+            const int sums = (Pl + kFanIn - 1) >> kLogFanIn;
+            for (int q = 0; q < sums; ++q) {
+                const int m = min(kFanIn, Pl - (q << kLogFanIn));
+                tot = (f4)(0.0f);
+                for (int i0 = 0; i0 < m; i0 += p.combine_batch) {
+                    f4 x[8];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) {
+                        const int j = ((q << kLogFanIn) + min(i0 + u, m - 1)) << shift;       // the share's group within the row
+                        const f4 y = share[(share_slot(k0, j) - 2 * k_first) * p.lanes + sl];
+                        x[u] = i0 + u < m && u < p.combine_batch ? y : (f4)(0.0f);
+                    }
+                    const f4 h0 = (x[0] + x[1]) + (x[2] + x[3]);
+                    tot = tot + (p.combine_batch > 4 ? h0 + ((x[4] + x[5]) + (x[6] + x[7])) : h0);
+                }
+                share[(share_slot(k0, (q << kLogFanIn) << shift) - 2 * k_first) * p.lanes + sl] = tot;
+            }
+            if (sums == 1) break;
+            Pl = sums;
+        }
+        if (colok) store_out<EPI>(p.dense_out, (size_t)(lo + rel) * p.d + col, tot + d0, p.scale);
+    }
+}
+
 // ------------------------------------------------------------------ unique ids (introspection)
 __global__ __launch_bounds__(1024) void unique_kernel(const int32_t* count, int V, int32_t* out,
                                                       int32_t* n_out)
@@ -2029,6 +2386,102 @@ void launch_reduce(unsigned grid, bool wide, bool deep, int32_t row_dtype, hipSt
         else fn<EPI_SCALE_BF16>(__VA_ARGS__);                      \
     } while (0)
 
+void remember(const Plan& pl, void* ws, int32_t V, int32_t copied_beside, int32_t form)
+{
+    g_last_plan = pl;
+    g_last_ws = ws;
+    g_last_V = V;
+    g_last_info[0] = pl.C;
+    g_last_info[1] = copied_beside;
+    g_last_info[2] = V;
+    g_last_info[3] = pl.S;
+    g_last_info[4] = pl.part;
+    g_last_info[5] = pl.NB;
+    g_last_info[6] = pl.levels;
+    g_last_info[7] = form;
+    g_have_last = true;
+}
+
+// Calls that small_kernel takes.  The pairs of a row, however many, are added up by one work-group of a compute unit
+// and block of columns, 16 pieces at a time for rows of 132 columns or more, 64 for rows of 64, so the limit falls with the
+// width; and the work-groups hold little more than a copy each, so large outputs are better copied beside a sort.  us with
+// two launches / one: d = 64, 2048 pairs, V = 1000 12.0 / 9.3 (uniform ids 10.7 / 7.4), 4000 12.2 / 8.6, 16000 12.4 / 10.1, 32768 13.8 / 10.8;
+// d = 64, 1024 pairs, V = 40000 13.9 / 11.2, 45000 13.7 / 13.3, 65536 14.1 / 14.6; d = 128, 1024 pairs, V = 10000 12.4 / 10.3, 20000
+// 13.7 / 12.0; d = 512, 512 pairs, V = 4000 13.8 / 10.0.  A third of the pairs on one id: d = 64, 2048 pairs 12.3 / 10.8, d = 128, 1024
+// pairs 12.0 / 11.8, 2048 pairs 12.4 / 15.5, d = 256, 2048 pairs 12.7 / 25.1; nine tenths: d = 64, 1024 pairs 12.4 / 12.8, 2048 14.2 / 17.3.
+// (A setting that says how to split the work over the launches is for the two-launch form.)
+constexpr int64_t kSmallPairLanes = 32768;
+constexpr int64_t kSmallElems = 5 << 19;
+
+int small_lanes(int32_t d)
+{
+    int lanes = 1;
+    while (lanes < 64 && lanes * 4 < d) lanes *= 2;
+    return lanes;
+}
+
+bool small_call(int64_t n, int32_t d, int32_t V)
+{
+    if (g_piece_override || g_part_override || g_short_rows >= 0 || g_overlap_sort >= 0) return false;
+    return n >= 1 && n <= kSmallMax && n * small_lanes(d) <= kSmallPairLanes && (int64_t)V * d <= kSmallElems;
+}
+
+template <int EPI>
+void launch_small(unsigned grid, size_t lds, int32_t row_dtype, hipStream_t stream, hipEvent_t begin, hipEvent_t end,
+                  const SmallParams& q, const ShardTable& sh)
+{
+    const dim3 threads(64 * kSmallWaves);
+    if (row_dtype == TS_ROW_BF16) {
+        if (begin) hipExtLaunchKernelGGL((small_kernel<uint16_t, EPI>), dim3(grid), threads, lds, stream, begin, end, 0, q, sh);
+        else hipLaunchKernelGGL((small_kernel<uint16_t, EPI>), dim3(grid), threads, lds, stream, q, sh);
+    } else {
+        if (begin) hipExtLaunchKernelGGL((small_kernel<float, EPI>), dim3(grid), threads, lds, stream, begin, end, 0, q, sh);
+        else hipLaunchKernelGGL((small_kernel<float, EPI>), dim3(grid), threads, lds, stream, q, sh);
+    }
+}
+
+int densify_small(const ShardTable& sh, Plan& pl, int32_t row_dtype, int32_t d, int32_t V, int32_t id_base, int32_t V_total,
+                  const float* dense_in, void* dense_out, int epi, float scale, hipStream_t stream, char* ws, bool in_place, bool wide)
+{
+    SmallParams q;
+    q.n = sh.off[sh.k];
+    q.V = V;
+    q.id_base = id_base;
+    q.V_total = V_total;
+    q.row_bytes = d * (row_dtype == TS_ROW_BF16 ? 2 : 4);
+    q.d = d;
+    q.C = pl.C;
+    q.lanes = small_lanes(d);
+    q.combine_batch = wide ? 4 : 8;
+    const int ncb = (d + kColBlock - 1) / kColBlock;
+    // as many rows to a work-group as it takes for every one to have a compute unit of its own (V = 32768, d = 64 / V = 10000,
+    // d = 128 / V = 40000, d = 64 with 512, 313, 625 work-groups 14.5, 11.7, -, with 256, 157, 313 10.8, 10.3, 12.4, with 128, 79, 157 12.3, 11.5, 11.2)
+    const int rows = kSmallWaves * (64 / q.lanes);              // of a work-group in one round
+    const int64_t cus = compute_units() > 0 ? compute_units() : 256;
+    q.rounds = 1;
+    while (q.rounds < kSmallRows && rows * q.rounds * 2 <= 1024 && ((int64_t)V + rows * q.rounds - 1) / (rows * q.rounds) * ncb > cus)
+        q.rounds *= 2;
+    q.part = rows * q.rounds;
+    q.G = (V + q.part - 1) / q.part;
+    q.count = (int32_t*)(ws + pl.off_count);
+    q.row_start = (int32_t*)(ws + pl.off_row_start);
+    q.sorted = (SortedPair*)(ws + pl.off_sorted);
+    q.n_valid = (int32_t*)(ws + pl.off_nvalid);
+    q.n_bad = (int32_t*)(ws + pl.off_nbad);
+    q.dense_in = dense_in;
+    q.dense_out = dense_out;
+    q.copy_untouched = !(in_place && epi == EPI_NONE);
+    q.scale = scale;
+    const bool prof = g_prof_used < g_prof_cap;
+    hipEvent_t ev_begin = prof ? g_ev[2 * g_prof_used] : nullptr, ev_end = prof ? g_ev[2 * g_prof_used + 1] : nullptr;
+    TS_DISPATCH_EPI(epi, launch_small, (unsigned)(q.G * ncb), small_lds(q.n, q.part, q.lanes), row_dtype, stream, ev_begin, ev_end, q, sh);
+    if (prof) ++g_prof_used;
+    if (hipGetLastError() != hipSuccess) return TS_ERR_HIP;
+    pl.part = q.part;
+    remember(pl, ws, V, 0, (in_place ? 1 : 0) | 3 << 1);
+    return TS_OK;
+}
+
 // V rows are produced: ids id_base .. id_base + V - 1 of a vocabulary of V_total ids.
 int densify_impl(const ShardTable& sh, int64_t n, int32_t row_dtype, int32_t d, int32_t V, int32_t id_base,
                  int32_t V_total, const float* dense_in, void* dense_out, int epi, float scale, void* stream_v,
@@ -2055,6 +2508,8 @@ int densify_impl(const ShardTable& sh, int64_t n, int32_t row_dtype, int32_t d, 
         return TS_ERR_OVERFLOW;
     hipStream_t stream = (hipStream_t)stream_v;
     char* ws = (char*)ws_v;
+
+    if (small_call(n, d, V)) return densify_small(sh, pl, row_dtype, d, V, id_base, V_total, dense_in, dense_out, epi, scale, stream, ws, in_place, wide);
 
     SortParams sp;
     sp.n = (int32_t)n;
@@ -2207,21 +2662,10 @@ int densify_impl(const ShardTable& sh, int64_t n, int32_t row_dtype, int32_t d, 
     if (prof) ++g_prof_used;
     if (hipGetLastError() != hipSuccess) return TS_ERR_HIP;
 
-    g_last_plan = pl;
-    g_last_ws = ws_v;
-    g_last_V = V;
-    g_last_info[0] = pl.C;
-    g_last_info[1] = copy_done;
-    g_last_info[2] = V;
-    g_last_info[3] = pl.S;
-    g_last_info[4] = pl.part;
-    g_last_info[5] = pl.NB;
-    g_last_info[6] = pl.levels;
     // bit 0: in place; bits 1-2: how short rows were added up (0 in the pieces, 1 row by row with the long
     // rows by lone wavefronts, 2 row by row with the long rows by work-groups); bit 3: the deep batches
     const bool deep_form = rp.short_max == 0 && (gp == 8 || deep) && (wide || row_dtype == TS_ROW_FP32);
-    g_last_info[7] = (in_place ? 1 : 0) | ((rp.short_max == 0 ? 0 : (rp.logG <= 6 ? 1 : 2)) << 1) | (deep_form ? 8 : 0);
-    g_have_last = true;
+    remember(pl, ws, V, copy_done, (in_place ? 1 : 0) | ((rp.short_max == 0 ? 0 : (rp.logG <= 6 ? 1 : 2)) << 1) | (deep_form ? 8 : 0));
     return TS_OK;
 }
 
