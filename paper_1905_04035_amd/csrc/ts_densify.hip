@@ -83,7 +83,6 @@ static_assert(sizeof(SortedPair) == 32, "two 16-byte accesses per record");
 
 constexpr int kMaxPart = 2048;     // most ids one sort work-group owns (LDS: 88 KiB of tables and 68 KiB of lists)
 constexpr int kMinPart = 128;
-constexpr int kSortWaves = 16;     // wavefronts per sort work-group
 constexpr int kColBlock = 256;     // fp32 columns per wavefront item (64 lanes x 4)
 constexpr int kMaxSlices = 64;
 constexpr int kSliceTokens = 16384;
@@ -272,27 +271,28 @@ __device__ __forceinline__ void store_out(void* out, size_t idx, f4 v, float sca
     }
 }
 
-// One wavefront copies the elements [e, e + 2048) that lie below e_end, from dense_in to the output: the
-// copies beside the sort take whole rows, one behind the other, so where a row ends does not matter
-// here.  All loads are issued before the first store.  (Two rows per wavefront, as it used to be, is the
-// same 8 KiB at d = 1024 but a fraction of it in narrow rows: V = 32768, d = 512, 8192 pairs, the
-// launch had 320 copying work-groups and now has 192, one per compute unit that does not sort: call
-// 30.4 -> 29.9 us; V = 20000, d = 2048, 9000 pairs 75.6 -> 73.0.  Loads that are the same for every lane, with
+// A work-group of the sort launches copies the elements [e, e + 2048 * kSortWaves) that lie below e_end, from dense_in to
+// the output: the copies beside the sort take whole rows, one behind the other, so where a row ends does not matter
+// here.  All loads are issued before the first store.  At every step the work-group's wavefronts move 1 KiB each of one
+// stretch of 16 KiB.  (A wavefront that moves 8 KiB of its own takes longer: 192 such work-groups by themselves 50.3 MB in 10.3 us, now
+// in 9.6, 256 of them 67.1 MB in 12.6, now in 11.9; calls with V = 32768, d = 512, 8192 pairs 28.4 -> 27.7, d = 1024, 2048 pairs 46.3 ->
+// 45.6, 16384 pairs 58.4 -> 57.7; V = 100000, d = 256, 5000 pairs 36.9 -> 36.3; without a dense operand level.  Loads that are the same for every lane, with
 // the index clamped, cost 1.3 us at d = 1024 and 1.4 us at d = 512: beside the sort gentler copies are better.)
 constexpr int kBlindElems = 2048;
+constexpr int kSortWaves = 16;     // wavefronts per sort work-group
 
 template <int EPI>
-__device__ __forceinline__ void copy_flat(const float* dense_in, void* dense_out, int64_t e, int64_t e_end, int lane,
+__device__ __forceinline__ void copy_flat(const float* dense_in, void* dense_out, int64_t e, int64_t e_end, int w, int lane,
                                           float scale)
 {
     constexpr int U = kBlindElems / kColBlock;
     if (e >= e_end) return;
-    const int rest = (int)min(e_end - e, (int64_t)kBlindElems);
+    const int rest = (int)min(e_end - e, (int64_t)kBlindElems * kSortWaves);
     f4 x[U];
     if (dense_in) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int i = u * kColBlock + lane * 4;
+            const int i = (u * kSortWaves + w) * kColBlock + lane * 4;
             x[u] = (f4)(0.0f);
             if (i < rest) x[u] = load_f4_stream(dense_in + e + i);
         }
@@ -319,7 +319,7 @@ __device__ __forceinline__ void copy_flat(const float* dense_in, void* dense_out
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-        const int i = u * kColBlock + lane * 4;
+        const int i = (u * kSortWaves + w) * kColBlock + lane * 4;
         if (i < rest) {
             if constexpr (EPI == EPI_SCALE_BF16)
                 __builtin_nontemporal_store(packed[u], reinterpret_cast<u2*>(reinterpret_cast<uint16_t*>(dense_out) + e + i));
@@ -509,8 +509,8 @@ enum { SORT_FUSED = 0, SORT_SCATTER = 2 };
 template <int EPI>
 __device__ __forceinline__ void blind_copy(const SortParams& p, int cw, int w, int lane)
 {
-    const int64_t e = p.copy_e0 + (int64_t)(cw * kSortWaves + w) * kBlindElems;
-    copy_flat<EPI>(p.copy_in, p.copy_out, e, p.copy_e1, lane, p.scale);
+    const int64_t e = p.copy_e0 + (int64_t)cw * (kSortWaves * kBlindElems);
+    copy_flat<EPI>(p.copy_in, p.copy_out, e, p.copy_e1, w, lane, p.scale);
 }
 
 // One wavefront walks its sub-slice [a, b) in rounds of kRoundTiles tiles of 64 pairs.  All ids of a round are
