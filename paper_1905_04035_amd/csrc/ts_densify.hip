@@ -759,41 +759,17 @@ __global__ __launch_bounds__(1024) void sort_kernel(SortParams p, ShardTable sh)
     }
 
     uint32_t base = 0, nbad = 0;            // first sorted position of the part; bad ids
+    // Everything the counting launch has left, asked for here and looked at behind the listing, so that the latency runs
+    // beside it (V = 131072, d = 64, 200000 pairs 72.7 -> 67.9 us, V = 32768, 60000 pairs 27.8 -> 27.3, eight shards of 80011 pairs
+    // averaged to bf16 80.8 -> 80.2; with loads beyond the last slice as well, so that none is conditional, 69.5, 28.0 and 80.6).  Per slice (lane s2 speaks for slice s2, at most 64 slices): the pairs below the part and the
+    // bad ids.  Per id: its count in all slices and in the slices before this one, the first sixteen here.
+    const size_t GW = (size_t)p.G * words;
+    uint32_t bl = 0, bd = 0, tot[16];
     if (MODE == SORT_SCATTER) {
-        // Everything the counting launch has left, fetched here so that the latency runs beside
-        // the ids'.  Per slice (lane s2 speaks for slice s2, at most 64 slices): the pairs below
-        // the part and the bad ids.  Per id: its count in all slices and in the slices before this one,
-        // sixteen loads in flight at a time, kept where the scan below finds them.  (Measured: issuing
-        // more of these loads at once, or issuing them before the tables are cleared, lengthens the launch
-        // by 2-3 us.)
-        const uint32_t bl = lane < p.S ? p.below[lane * p.G + g] : 0u;
-        const uint32_t bd = lane < p.S ? p.bad[lane] : 0u;
-        const size_t GW = (size_t)p.G * words;
-        if (tid < words) {
-            uint32_t total[E], pre[E];
+        bl = p.below[min(lane, p.S - 1) * p.G + g];
+        bd = p.bad[min(lane, p.S - 1)];
 #pragma unroll
-            for (int e = 0; e < E; ++e) total[e] = pre[e] = 0u;
-            for (int sb = 0; sb < p.S; sb += 16) {
-                uint32_t x[16];
-#pragma unroll
-                for (int q = 0; q < 16; ++q) x[q] = sb + q < p.S ? p.tot[(size_t)(sb + q) * GW + (size_t)g * words + tid] : 0u;
-#pragma unroll
-                for (int q = 0; q < 16; ++q)
-#pragma unroll
-                    for (int e = 0; e < E; ++e) {
-                        const uint32_t c = tab_get<WIDE>(x[q], 16u * e);
-                        total[e] += c;
-                        if (sb + q < sl) pre[e] += c;
-                    }
-            }
-#pragma unroll
-            for (int e = 0; e < E; ++e) {
-                id_info[tid * E + e].x = total[e];
-                id_pos[tid * E + e] = pre[e];
-            }
-        }
-        base = wave_sum(bl);
-        nbad = wave_sum(bd);
+        for (int q = 0; q < 16; ++q) tot[q] = q < p.S ? p.tot[(size_t)q * GW + (size_t)g * words + min(tid, words - 1)] : 0u;
     }
     // every wavefront clears its own table of counts, so none has to wait for the others before it
     // starts to list and count (the tables meet at the barrier before the scan)
@@ -840,6 +816,34 @@ __global__ __launch_bounds__(1024) void sort_kernel(SortParams p, ShardTable sh)
         }
     }
     count_listed();
+    if (MODE == SORT_SCATTER) {
+        if (tid < words) {
+            uint32_t total[E], pre[E];
+#pragma unroll
+            for (int e = 0; e < E; ++e) total[e] = pre[e] = 0u;
+            for (int sb = 0; sb < p.S; sb += 16) {
+                if (sb > 0) {
+#pragma unroll
+                    for (int q = 0; q < 16; ++q) tot[q] = sb + q < p.S ? p.tot[(size_t)(sb + q) * GW + (size_t)g * words + tid] : 0u;
+                }
+#pragma unroll
+                for (int q = 0; q < 16; ++q)
+#pragma unroll
+                    for (int e = 0; e < E; ++e) {
+                        const uint32_t c = tab_get<WIDE>(tot[q], 16u * e);
+                        total[e] += c;
+                        if (sb + q < sl) pre[e] += c;
+                    }
+            }
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                id_info[tid * E + e].x = total[e];
+                id_pos[tid * E + e] = pre[e];
+            }
+        }
+        base = wave_sum(lane < p.S ? bl : 0u);
+        nbad = wave_sum(lane < p.S ? bd : 0u);
+    }
     if (MODE == SORT_FUSED) {
         tally = wave_sum(tally);
         if (lane == 0) red[w] = tally;
