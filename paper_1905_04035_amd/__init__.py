@@ -1,6 +1,6 @@
 """MI355X-native densify of assumed-sparse gradients (arXiv 1905.04035).
 
-`binding` is the ctypes front end of the C-ABI library built from `csrc/`;
+`binding` is the front end of the C-ABI library built from `csrc/`;
 `workloads` draws seeded synthetic inputs; `build` compiles the library.
 The binding is imported on first use so that `workloads` stays importable on a
 machine where the library has not been built.

@@ -1,7 +1,7 @@
-"""ctypes binding of libts_densify.so: the same names as include/ts_densify.h and
+"""Binding of libts_densify.so: the same names as include/ts_densify.h and
 include/ts_densify_tools.h (the calls for tests, benchmarks and tuning).
 
-Argument marshalling only, for the calls of a training step in native code
+Argument marshalling only: by ctypes, for the calls of a training step in native code
 (csrc/marshal.cpp, an extension module next to the library).  Tensors are PyTorch tensors on
 the GPU (PyTorch is used for device memory and streams, nothing else); every step of the path
 runs in the library's kernels.  There is no fallback: if the library or the module is missing or a
