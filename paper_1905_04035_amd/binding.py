@@ -90,7 +90,7 @@ def lib():
             getattr(l, name).restype = C.c_int
         # what the extension module calls: addresses of the entry points
         for name in ("ts_densify", "ts_densify_static", "ts_densify_bf16", "ts_densify_multi", "ts_densify_scaled",
-                     "ts_densify_range", "ts_accumulate"):
+                     "ts_densify_range", "ts_accumulate", "ts_accumulate_strategy"):
             setattr(l, "at_" + name, C.cast(getattr(l, name), C.c_void_p).value)
         _load_marshal()
         _lib = l
@@ -222,8 +222,8 @@ def ts_accumulate(grads, rule: int, d: int, V: int, dense_out: Optional[torch.Te
                   ids_out: Optional[torch.Tensor] = None, rows_out: Optional[torch.Tensor] = None, stream=None):
     """Returns (strategy, n_slices); n_slices is None when the result is dense."""
     l = lib()
-    status, strategy, n_out = _marshal.accumulate(l.at_ts_accumulate, grads, rule, d, V, dense_out, ids_out, rows_out,
-                                                  stream)
+    status, strategy, n_out = _marshal.accumulate(l.at_ts_accumulate, l.at_ts_accumulate_strategy, grads, rule, d, V, dense_out,
+                                                  ids_out, rows_out, stream)
     _check(status, "ts_accumulate")
     return strategy, (n_out if n_out >= 0 else None)
 

@@ -238,15 +238,20 @@ PyObject* range(PyObject*, PyObject* const* a, Py_ssize_t nargs)
     });
 }
 
-// accumulate(entry, grads, rule, d, V, dense_out, ids_out, rows_out, stream) -> (status, strategy, slices)
-// grads: ("dense", tensor) or ("slices", ids, rows)
+// accumulate(entry, strategy entry, grads, rule, d, V, dense_out, ids_out, rows_out, stream) -> (status, strategy, slices)
+// grads: ("dense", tensor) or ("slices", ids, rows).  Gradients and the outputs that the rule's branch writes hold at least
+// what the call reads and writes (flat and longer buffers are fine); outputs that it does not write are not looked at, but for
+// rows_out, which holds what ids_out has room for.
 PyObject* accumulate(PyObject*, PyObject* const* a, Py_ssize_t nargs)
 {
-    return guarded(nargs, 9, [&]() -> PyObject* {
+    return guarded(nargs, 10, [&]() -> PyObject* {
         const auto fn = reinterpret_cast<decltype(&ts_accumulate)>(address(a[0]));
-        const int32_t rule = integer32(a[2]), d = integer32(a[3]), V = integer32(a[4]);
+        const auto strategy_fn = reinterpret_cast<decltype(&ts_accumulate_strategy)>(address(a[1]));
+        const int32_t rule = integer32(a[3]), d = integer32(a[4]), V = integer32(a[5]);
+        const bool shape_ok = V > 0 && d > 0 && d % 4 == 0;             // (else the entry point refuses the call)
+        const int64_t vd = shape_ok ? (int64_t)V * d : 0;
         std::vector<ts_grad> grads;
-        PyObject* const list = PySequence_Fast(a[1], "grads is not a sequence");
+        PyObject* const list = PySequence_Fast(a[2], "grads is not a sequence");
         if (!list) throw Failed();
         try {
             const Py_ssize_t m = PySequence_Fast_GET_SIZE(list);
@@ -264,13 +269,13 @@ PyObject* accumulate(PyObject*, PyObject* const* a, Py_ssize_t nargs)
                     require(parts >= (is_dense ? 2 : 3));
                     if (is_dense) {
                         const at::Tensor& t = tensor(PySequence_Fast_GET_ITEM(one, 1));
-                        require(fp32_on_gpu(t));
+                        require(fp32_on_gpu(t) && t.numel() >= vd);
                         g.kind = TS_GRAD_DENSE;
                         g.values = static_cast<const float*>(t.data_ptr());
                     } else {
                         const at::Tensor &ids = tensor(PySequence_Fast_GET_ITEM(one, 1)), &rows = tensor(PySequence_Fast_GET_ITEM(one, 2));
                         require(ids.is_cuda() && ids.scalar_type() == at::kInt && ids.is_contiguous());
-                        require(fp32_on_gpu(rows));
+                        require(fp32_on_gpu(rows) && (!shape_ok || rows.numel() / d >= ids.numel()));
                         g.kind = TS_GRAD_SLICES;
                         g.ids = static_cast<const int32_t*>(ids.data_ptr());
                         g.values = static_cast<const float*>(rows.data_ptr());
@@ -289,20 +294,31 @@ PyObject* accumulate(PyObject*, PyObject* const* a, Py_ssize_t nargs)
         }
         Py_DECREF(list);
         const int32_t m = (int32_t)grads.size() - 1;
+        int32_t branch = -1;
+        const bool known = strategy_fn(grads.data(), m, rule, &branch) == TS_OK;
+        const bool to_dense = known && (branch == TS_ACC_REDUCE || branch == TS_ACC_DENSIFY_REDUCE ||
+                                        (branch == TS_ACC_PASS_THROUGH && grads[0].kind == TS_GRAD_DENSE));
         int64_t capacity = 0;
         int32_t* ids_out = nullptr;
         float *rows_out = nullptr, *dense_out = nullptr;
-        if (a[6] != Py_None) {
-            capacity = tensor(a[6]).numel();
-            ids_out = static_cast<int32_t*>(tensor(a[6]).data_ptr());
-        }
         if (a[7] != Py_None) {
             const at::Tensor& t = tensor(a[7]);
+            require(!known || to_dense || (t.is_cuda() && t.scalar_type() == at::kInt && t.is_contiguous()));
+            capacity = t.numel();
+            ids_out = static_cast<int32_t*>(t.data_ptr());
+        }
+        if (a[8] != Py_None) {
+            const at::Tensor& t = tensor(a[8]);
             require(t.is_cuda() && t.scalar_type() == at::kFloat && t.numel() >= capacity * d);
+            require(!known || to_dense || t.is_contiguous());
             rows_out = static_cast<float*>(t.data_ptr());
         }
-        if (a[5] != Py_None) dense_out = static_cast<float*>(tensor(a[5]).data_ptr());
-        void* const stream = stream_of(a[8]);
+        if (a[6] != Py_None) {
+            const at::Tensor& t = tensor(a[6]);
+            require(!to_dense || (fp32_on_gpu(t) && t.numel() >= vd));
+            dense_out = static_cast<float*>(t.data_ptr());
+        }
+        void* const stream = stream_of(a[9]);
         int64_t slices = -1;
         int32_t strategy = -1;
         int rc;

@@ -50,16 +50,15 @@ def test_what_is_no_tensor_or_no_sequence():
     (lambda a: dict(ids=a["ids"].long()), "all"), (lambda a: dict(ids=a["ids"].cpu()), "all"),
     (lambda a: dict(ids=torch.stack([a["ids"]] * 2, 1)[:, 0]), "all"),
     (lambda a: dict(rows=a["rows"].cpu()), "fp32"), (lambda a: dict(rows=a["rows"].half()), "fp32"),
-    (lambda a: dict(rows=a["rows"].t().contiguous().t()), "fp32"), (lambda a: dict(rows=a["rows"][1:]), "but accumulate"),
+    (lambda a: dict(rows=a["rows"].t().contiguous().t()), "fp32"), (lambda a: dict(rows=a["rows"][1:]), "fp32"),
     (lambda a: dict(rows16=a["rows16"].float()), "bf16"),
     (lambda a: dict(dense_in=a["dense_in"].double()), "all"), (lambda a: dict(dense_in=a["dense_in"][:, ::2]), "all"),
-    (lambda a: dict(dense_in=a["dense_in"][1:]), "but accumulate too"), (lambda a: dict(out=a["out"][1:]), "but accumulate too"),
-    (lambda a: dict(out=a["out"].double()), "but accumulate too")])
+    (lambda a: dict(dense_in=a["dense_in"][1:]), "all"), (lambda a: dict(out=a["out"][1:]), "all"),
+    (lambda a: dict(out=a["out"].double()), "all")])
 def test_wrong_tensors_are_refused(what, names):
     ws = ts.Workspace(N, D, V)
     for name, call in _calls("cuda:0", what):
-        if {"all": True, "fp32": name != "bf16", "bf16": name == "bf16", "but accumulate": name not in ("bf16", "accumulate"),
-                "but accumulate too": name != "accumulate"}[names]:
+        if {"all": True, "fp32": name != "bf16", "bf16": name == "bf16"}[names]:
             with pytest.raises(AssertionError):
                 call()
     ws.close()
@@ -83,3 +82,48 @@ def test_every_entry_point_on_streams():
     want = np.bincount(i.cpu().numpy(), minlength=V).astype(np.float32)
     assert np.array_equal(out.cpu().numpy(), np.repeat(want[:, None], D, 1))
     ws.close()
+
+
+def _gathered(**change):
+    """A gather of two slice gradients and a dense one into outputs of exactly its size, or with some tensors replaced."""
+    i = torch.randint(V, (N,), dtype=torch.int32, device="cuda:0")
+    a = dict(ids=i, rows=torch.randn(N, D, device="cuda:0"), dense=torch.randn(V, D, device="cuda:0"), out=None,
+             ids_out=torch.empty(2 * N + V, dtype=torch.int32, device="cuda:0"),
+             rows_out=torch.empty(2 * N + V, D, device="cuda:0"))
+    a.update({k: f(a[k]) for k, f in change.items()})
+    grads = [("slices", a["ids"], a["rows"]), ("dense", a["dense"]), ("slices", a["ids"], a["rows"])]
+    return a, ts.ts_accumulate(grads, ts.TS_RULE_TF, D, V, a["out"], a["ids_out"], a["rows_out"])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("change", [
+    dict(ids_out=lambda t: t.cpu()), dict(ids_out=lambda t: t.long()), dict(ids_out=lambda t: torch.stack([t, t], 1)[:, 0]),
+    dict(rows_out=lambda t: t.cpu()), dict(rows_out=lambda t: t.double()), dict(rows_out=lambda t: t[1:]),
+    dict(rows_out=lambda t: t.t().contiguous().t()), dict(rows=lambda t: t[1:]), dict(dense=lambda t: t[1:])])
+def test_wrong_tensors_of_a_gather_are_refused(change):
+    with pytest.raises(AssertionError):
+        _gathered(**change)
+
+
+@pytest.mark.gpu
+def test_accumulate_takes_flat_and_longer_buffers_and_leaves_unused_outputs_alone():
+    def longer(t):
+        return torch.cat([t, t])
+
+    for change in (dict(), dict(rows=longer, dense=longer, ids_out=longer, rows_out=longer), dict(dense=lambda t: t.flatten()),
+                   dict(rows=lambda t: t.flatten(), rows_out=lambda t: t.flatten()), dict(out=lambda t: torch.empty(3))):
+        a, (strategy, total) = _gathered(**change)
+        assert strategy == ts.TS_ACC_GATHER and total == 2 * N + V
+        rows, dense = a["rows"].reshape(-1, D)[:N], a["dense"].reshape(-1, D)[:V]
+        assert torch.equal(a["rows_out"].reshape(-1, D)[:total], torch.cat([rows, dense, rows]))
+        ids = torch.cat([a["ids"], torch.arange(V, dtype=torch.int32, device="cuda:0"), a["ids"]])
+        assert torch.equal(a["ids_out"][:total], ids)
+    x = torch.randn(V, D, device="cuda:0")
+    out = torch.empty(V * D + 5, device="cuda:0")
+    for ids_out in (None, torch.empty(0), torch.empty(0, dtype=torch.int64, device="cuda:0")):
+        assert ts.ts_accumulate([("dense", x), ("dense", x)], ts.TS_RULE_TF, D, V, out, ids_out) == (ts.TS_ACC_REDUCE, None)
+        assert torch.equal(out[:V * D], (x + x).flatten())
+    for shape in ((0, V), (D, 0), (-D, -V), (D + 1, V)):
+        with pytest.raises(ts.TsError) as e:
+            ts.ts_accumulate([("dense", longer(x))], ts.TS_RULE_TF, *shape, out)
+        assert e.value.status == ts.TS_ERR_SHAPE
