@@ -103,6 +103,15 @@ Pair pair(PyObject* ids_o, PyObject* rows_o, int64_t d, int elem, bool any_type)
     return Pair{static_cast<const int32_t*>(ids.data_ptr()), rows.data_ptr(), n};
 }
 
+// The items of something that has a length (an iterator, whose items nobody else holds, has none: TypeError).  New reference.
+PyObject* items(PyObject* o, const char* otherwise)
+{
+    if (PyObject_Size(o) < 0) throw Failed();
+    PyObject* const list = PySequence_Fast(o, otherwise);
+    if (!list) throw Failed();
+    return list;
+}
+
 struct Shards {
     std::vector<const int32_t*> ids;
     std::vector<const void*> rows;
@@ -111,14 +120,10 @@ struct Shards {
 
     Shards(PyObject* ids_k, PyObject* rows_k, int32_t row_dtype, int64_t d)
     {
-        PyObject* const i = PySequence_Fast(ids_k, "ids_k is not a sequence");
-        if (!i) throw Failed();
-        PyObject* const r = PySequence_Fast(rows_k, "rows_k is not a sequence");
-        if (!r) {
-            Py_DECREF(i);
-            throw Failed();
-        }
+        PyObject* const i = items(ids_k, "ids_k is not a sequence");
+        PyObject* r = nullptr;
         try {
+            r = items(rows_k, "rows_k is not a sequence");
             const Py_ssize_t m = PySequence_Fast_GET_SIZE(i);
             require(m == PySequence_Fast_GET_SIZE(r) && m == (int32_t)m);
             k = (int32_t)m;
@@ -133,7 +138,7 @@ struct Shards {
             }
         } catch (...) {
             Py_DECREF(i);
-            Py_DECREF(r);
+            Py_XDECREF(r);
             throw;
         }
         Py_DECREF(i);
@@ -251,15 +256,13 @@ PyObject* accumulate(PyObject*, PyObject* const* a, Py_ssize_t nargs)
         const bool shape_ok = V > 0 && d > 0 && d % 4 == 0;             // (else the entry point refuses the call)
         const int64_t vd = shape_ok ? (int64_t)V * d : 0;
         std::vector<ts_grad> grads;
-        PyObject* const list = PySequence_Fast(a[2], "grads is not a sequence");
-        if (!list) throw Failed();
+        PyObject* const list = items(a[2], "grads is not a sequence");
         try {
             const Py_ssize_t m = PySequence_Fast_GET_SIZE(list);
             require(m == (int32_t)m);
             grads.resize(m + 1);
             for (Py_ssize_t j = 0; j < m; ++j) {
-                PyObject* const one = PySequence_Fast(PySequence_Fast_GET_ITEM(list, j), "a gradient is not a sequence");
-                if (!one) throw Failed();
+                PyObject* const one = items(PySequence_Fast_GET_ITEM(list, j), "a gradient is not a sequence");
                 try {
                     ts_grad g{};
                     const Py_ssize_t parts = PySequence_Fast_GET_SIZE(one);

@@ -45,6 +45,20 @@ def test_what_is_no_tensor_or_no_sequence():
         ts.ts_accumulate([()], ts.TS_RULE_TF, 4, 4, t)
 
 
+def test_iterators_are_no_sequences():
+    t, i = torch.zeros(4, 4), torch.zeros(4, dtype=torch.int32)
+    for ids_k, rows_k in ((iter([i]), [t]), ([i], iter([t])), ((x for x in [i]), (x for x in [t]))):
+        with pytest.raises(TypeError):
+            ts.ts_densify_multi(ids_k, rows_k, ts.TS_ROW_FP32, 4, 4, None, t)
+        with pytest.raises(TypeError):
+            ts.ts_densify_scaled(ids_k, rows_k, ts.TS_ROW_FP32, 4, 4, None, t, 1.0)
+        with pytest.raises(TypeError):
+            ts.ts_densify_range(ids_k, rows_k, ts.TS_ROW_FP32, 4, 4, 0, 4, None, t)
+    for grads in (iter([("dense", t)]), [iter(("dense", t))]):
+        with pytest.raises(TypeError):
+            ts.ts_accumulate(grads, ts.TS_RULE_TF, 4, 4, t)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("what,names", [
     (lambda a: dict(ids=a["ids"].long()), "all"), (lambda a: dict(ids=a["ids"].cpu()), "all"),
