@@ -105,7 +105,8 @@ def main():
     assert torch.cuda.is_available(), "bench.py needs a GPU"
     dev = "cuda:0"
     torch.cuda.set_device(0)
-    ts.lib()      # fail loudly if the HIP library has not been built
+    ts.lib()      # fail loudly if the HIP library or the marshalling has not been built
+    ts.marshal()
     if args.overlap_mib >= 0:
         ts.ts_set_overlap_bytes(int(args.overlap_mib * (1 << 20)))
     if args.piece_tokens:

@@ -32,7 +32,7 @@ LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)),
 MARSHAL_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "_marshal.so")
 
 _lib = None
-_marshal = None     # the extension module, loaded with the library
+_marshal = None     # the extension module, loaded by the first call that needs it
 
 
 class TsGrad(C.Structure):
@@ -92,12 +92,12 @@ def lib():
         for name in ("ts_densify", "ts_densify_static", "ts_densify_bf16", "ts_densify_multi", "ts_densify_scaled",
                      "ts_densify_range", "ts_accumulate", "ts_accumulate_strategy"):
             setattr(l, "at_" + name, C.cast(getattr(l, name), C.c_void_p).value)
-        _load_marshal()
         _lib = l
     return _lib
 
 
-def _load_marshal():
+def marshal():
+    """The loaded extension module.  Raises if it has not been built; the calls that launch nothing do without it."""
     global _marshal
     if _marshal is None:
         if not os.path.exists(MARSHAL_PATH):
@@ -107,6 +107,7 @@ def _load_marshal():
         module = importlib.util.module_from_spec(spec)
         spec.loader.exec_module(module)
         _marshal = module
+    return _marshal
 
 
 def status_string(status: int) -> str:
@@ -138,8 +139,8 @@ def ts_densify_raw(ids_ptr, rows_ptr, n, d, V, dense_in_ptr, dense_out_ptr, stre
 # calls the entry point; stream None is PyTorch's current stream.
 def ts_densify(ids: torch.Tensor, rows: torch.Tensor, d: int, V: int,
                dense_in: Optional[torch.Tensor], dense_out: torch.Tensor, stream=None) -> None:
-    l = lib()
-    _check(_marshal.densify(l.at_ts_densify, 4, ids, rows, d, V, dense_in, dense_out, stream), "ts_densify")
+    l, m = lib(), _marshal or marshal()
+    _check(m.densify(l.at_ts_densify, 4, ids, rows, d, V, dense_in, dense_out, stream), "ts_densify")
 
 
 TS_STATIC_SCRATCH_BYTES = 16 << 20
@@ -148,23 +149,23 @@ TS_STATIC_SCRATCH_BYTES = 16 << 20
 def ts_densify_static(ids: torch.Tensor, rows: torch.Tensor, d: int, V: int,
                       dense_in: Optional[torch.Tensor], dense_out: torch.Tensor, stream=None) -> None:
     """ts_densify on the library's built-in workspace: nothing is allocated or bound."""
-    l = lib()
-    _check(_marshal.densify(l.at_ts_densify_static, 4, ids, rows, d, V, dense_in, dense_out, stream),
+    l, m = lib(), _marshal or marshal()
+    _check(m.densify(l.at_ts_densify_static, 4, ids, rows, d, V, dense_in, dense_out, stream),
            "ts_densify_static")
 
 
 def ts_densify_bf16(ids: torch.Tensor, rows: torch.Tensor, d: int, V: int,
                     dense_in: Optional[torch.Tensor], dense_out: torch.Tensor, stream=None) -> None:
     """rows: uint16 / int16 / bfloat16 tensor holding bf16 bit patterns."""
-    l = lib()
-    _check(_marshal.densify(l.at_ts_densify_bf16, 2, ids, rows, d, V, dense_in, dense_out, stream), "ts_densify_bf16")
+    l, m = lib(), _marshal or marshal()
+    _check(m.densify(l.at_ts_densify_bf16, 2, ids, rows, d, V, dense_in, dense_out, stream), "ts_densify_bf16")
 
 
 def ts_densify_multi(ids_k: Sequence[torch.Tensor], rows_k: Sequence[torch.Tensor], row_dtype: int,
                      d: int, V: int, dense_in: Optional[torch.Tensor], dense_out: torch.Tensor,
                      stream=None) -> None:
-    l = lib()
-    _check(_marshal.multi(l.at_ts_densify_multi, ids_k, rows_k, row_dtype, d, V, dense_in, dense_out, stream),
+    l, m = lib(), _marshal or marshal()
+    _check(m.multi(l.at_ts_densify_multi, ids_k, rows_k, row_dtype, d, V, dense_in, dense_out, stream),
            "ts_densify_multi")
 
 
@@ -173,8 +174,8 @@ def ts_densify_scaled(ids_k: Sequence[torch.Tensor], rows_k: Sequence[torch.Tens
                       stream=None) -> None:
     """out: [V, d] float32, or a 2-byte dtype (bfloat16 / int16 / uint16) for bf16 output; it may
     be a view into a larger buffer (a fusion buffer at the offset ts_fusion_place gives)."""
-    l = lib()
-    _check(_marshal.scaled(l.at_ts_densify_scaled, ids_k, rows_k, row_dtype, d, V, dense_in, out, scale, stream),
+    l, m = lib(), _marshal or marshal()
+    _check(m.scaled(l.at_ts_densify_scaled, ids_k, rows_k, row_dtype, d, V, dense_in, out, scale, stream),
            "ts_densify_scaled")
 
 
@@ -182,9 +183,9 @@ def ts_densify_range(ids_k: Sequence[torch.Tensor], rows_k: Sequence[torch.Tenso
                      d: int, V: int, v_begin: int, v_end: int, dense_in: Optional[torch.Tensor],
                      dense_out: torch.Tensor, stream=None) -> None:
     """dense_in / dense_out: the [v_end - v_begin, d] slice of the owner of rows v_begin .. v_end - 1."""
-    l = lib()
-    _check(_marshal.range(l.at_ts_densify_range, ids_k, rows_k, row_dtype, d, V, v_begin, v_end, dense_in, dense_out,
-                          stream), "ts_densify_range")
+    l, m = lib(), _marshal or marshal()
+    _check(m.range(l.at_ts_densify_range, ids_k, rows_k, row_dtype, d, V, v_begin, v_end, dense_in, dense_out, stream),
+           "ts_densify_range")
 
 
 def ts_fusion_place(capacity_bytes: int, used_bytes: int, d: int, V: int, out_dtype: int = TS_OUT_FP32):
@@ -221,9 +222,9 @@ def ts_accumulate_strategy(grads, rule: int) -> int:
 def ts_accumulate(grads, rule: int, d: int, V: int, dense_out: Optional[torch.Tensor] = None,
                   ids_out: Optional[torch.Tensor] = None, rows_out: Optional[torch.Tensor] = None, stream=None):
     """Returns (strategy, n_slices); n_slices is None when the result is dense."""
-    l = lib()
-    status, strategy, n_out = _marshal.accumulate(l.at_ts_accumulate, l.at_ts_accumulate_strategy, grads, rule, d, V, dense_out,
-                                                  ids_out, rows_out, stream)
+    l, m = lib(), _marshal or marshal()
+    status, strategy, n_out = m.accumulate(l.at_ts_accumulate, l.at_ts_accumulate_strategy, grads, rule, d, V, dense_out,
+                                           ids_out, rows_out, stream)
     _check(status, "ts_accumulate")
     return strategy, (n_out if n_out >= 0 else None)
 

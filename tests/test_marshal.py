@@ -1,5 +1,7 @@
 """The binding's native marshalling: what it refuses (AssertionError before anything reaches the library, TypeError for
 what is no tensor), and that lists, tuples, gradients and streams arrive as they are."""
+import os
+
 import numpy as np
 import pytest
 import torch
@@ -57,6 +59,21 @@ def test_iterators_are_no_sequences():
     for grads in (iter([("dense", t)]), [iter(("dense", t))]):
         with pytest.raises(TypeError):
             ts.ts_accumulate(grads, ts.TS_RULE_TF, 4, 4, t)
+
+
+def test_calls_that_launch_nothing_do_without_the_module(monkeypatch):
+    t, i = torch.zeros(4, 4), torch.zeros(4, dtype=torch.int32)
+    monkeypatch.setattr(ts, "MARSHAL_PATH", os.path.join(os.path.dirname(ts.MARSHAL_PATH), "not_built.so"))
+    monkeypatch.setattr(ts, "_marshal", None)
+    monkeypatch.setattr(ts, "_lib", None)
+    assert ts.ts_workspace_bytes(100, 64, 1000) > 0
+    assert ts.ts_buffer_bytes(1, 1, 4, 1) == (20, 16)
+    assert ts.ts_fusion_place(1 << 20, 1, 4, 1) == (256, 272)
+    assert ts.status_string(ts.TS_ERR_SHAPE)
+    for call in (lambda: ts.ts_densify(i, t, 4, 4, None, t), lambda: ts.ts_densify_multi([i], [t], ts.TS_ROW_FP32, 4, 4, None, t),
+                 lambda: ts.ts_accumulate([("dense", t)], ts.TS_RULE_TF, 4, 4, t)):
+        with pytest.raises(FileNotFoundError, match="not_built.so"):
+            call()
 
 
 @pytest.mark.gpu
