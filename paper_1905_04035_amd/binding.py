@@ -12,6 +12,7 @@ from __future__ import annotations
 import ctypes as C
 import importlib.util
 import os
+import sysconfig
 from typing import Optional, Sequence
 
 import torch
@@ -29,7 +30,7 @@ TS_MAX_SHARDS = 64
 LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)),
                         "libts_densify_san.so" if os.environ.get("TS_SANITIZE") == "1" else "libts_densify.so")
 
-MARSHAL_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "_marshal.so")
+MARSHAL_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "_marshal" + sysconfig.get_config_var("EXT_SUFFIX"))
 
 _lib = None
 _marshal = None     # the extension module, loaded by the first call that needs it

@@ -1,5 +1,5 @@
 """Compiles csrc/*.hip for gfx950 into libts_densify.so next to this file, and csrc/marshal.cpp, the binding's
-marshalling (host code against PyTorch's headers), into _marshal.so."""
+marshalling (host code against PyTorch's headers), into the extension module _marshal."""
 import os
 import subprocess
 import sys
@@ -13,7 +13,8 @@ LIB_SAN = os.path.join(HERE, "libts_densify_san.so")     # host code under ASan 
 INCLUDE = os.path.join(ROOT, "include")
 
 MARSHAL_SRC = os.path.join(HERE, "csrc", "marshal.cpp")
-MARSHAL = os.path.join(HERE, "_marshal.so")
+MARSHAL_USES = [MARSHAL_SRC, os.path.join(INCLUDE, "ts_densify.h")]
+MARSHAL = os.path.join(HERE, "_marshal" + sysconfig.get_config_var("EXT_SUFFIX"))     # of this interpreter
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
@@ -39,7 +40,10 @@ def marshal_command():
 
 
 def build_marshal(force: bool = True) -> str:
-    if force or not os.path.exists(MARSHAL):
+    """force=False: only if it is missing or older than what it is made from (it calls the library's entry points by
+    their addresses, with the signatures of the header that it was compiled with)."""
+    old = not os.path.exists(MARSHAL) or os.path.getmtime(MARSHAL) < max(os.path.getmtime(f) for f in MARSHAL_USES)
+    if force or old:
         res = subprocess.run(marshal_command(), capture_output=True, text=True)
         if res.returncode != 0:
             raise RuntimeError("g++ failed:\n" + res.stderr)
@@ -51,9 +55,13 @@ def build(force: bool = True, verbose: bool = False, sanitize: bool = False) -> 
     undefined-behaviour sanitizers (device code unchanged); the loading process must have
     clang's shared sanitizer runtime preloaded."""
     lib = LIB_SAN if sanitize else LIB
+    if force or not os.path.exists(lib):
+        build_library(lib, verbose, sanitize)
     build_marshal(force and not sanitize)
-    if not force and os.path.exists(lib):
-        return lib
+    return lib
+
+
+def build_library(lib: str, verbose: bool = False, sanitize: bool = False) -> None:
     cmd = [HIPCC] + FLAGS + (SAN_FLAGS if sanitize else []) + ["-o", lib] + SRCS
     if verbose:
         print(" ".join(cmd))
@@ -64,7 +72,6 @@ def build(force: bool = True, verbose: bool = False, sanitize: bool = False) -> 
         raise RuntimeError("hipcc failed:\n" + err)
     if err.strip() and verbose:
         print(err)
-    return lib
 
 
 if __name__ == "__main__":
