@@ -26,11 +26,10 @@ TS_ROW_FP32, TS_ROW_BF16 = 0, 1
 TS_OUT_FP32, TS_OUT_BF16 = 0, 1
 TS_MAX_SHARDS = 64
 
-# TS_SANITIZE=1 selects the build whose host code runs under ASan + UBSan (build.py, sanitize=True)
-LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)),
-                        "libts_densify_san.so" if os.environ.get("TS_SANITIZE") == "1" else "libts_densify.so")
-
-MARSHAL_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "_marshal" + sysconfig.get_config_var("EXT_SUFFIX"))
+# TS_SANITIZE=1 selects the builds whose host code runs under ASan + UBSan (build.py, sanitize=True)
+_HERE, _SAN = os.path.dirname(os.path.abspath(__file__)), "_san" if os.environ.get("TS_SANITIZE") == "1" else ""
+LIB_PATH = os.path.join(_HERE, f"libts_densify{_SAN}.so")
+MARSHAL_PATH = os.path.join(_HERE, f"_marshal{_SAN}" + sysconfig.get_config_var("EXT_SUFFIX"))
 
 _lib = None
 _marshal = None     # the extension module, loaded by the first call that needs it

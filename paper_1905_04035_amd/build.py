@@ -16,6 +16,8 @@ MARSHAL_SRC = os.path.join(HERE, "csrc", "marshal.cpp")
 MARSHAL_USES = [MARSHAL_SRC, os.path.join(INCLUDE, "ts_densify.h")]
 MARSHAL = os.path.join(HERE, "_marshal" + sysconfig.get_config_var("EXT_SUFFIX"))     # of this interpreter
 
+MARSHAL_SAN = os.path.join(HERE, "_marshal_san" + sysconfig.get_config_var("EXT_SUFFIX"))
+
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
@@ -27,37 +29,41 @@ FLAGS = [
 
 SAN_FLAGS = ["-g", "-Xarch_host", "-fsanitize=address", "-Xarch_host", "-fsanitize=undefined",
              "-Xarch_host", "-fno-sanitize-recover=undefined", "-shared-libsan"]
+CLANGXX = os.environ.get("CLANGXX", "/opt/rocm/llvm/bin/clang++")
+MARSHAL_SAN_FLAGS = ["-g", "-fsanitize=address,undefined", "-fno-sanitize-recover=undefined", "-shared-libsan"]
 
 
-def marshal_command():
+def marshal_command(sanitize: bool = False):
     import torch
 
     root = os.path.dirname(torch.__file__)
-    return [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wextra",
+    return [CLANGXX if sanitize else os.environ.get("CXX", "g++"), *(MARSHAL_SAN_FLAGS if sanitize else []), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wextra",
             "-Wno-missing-field-initializers", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
             "-isystem", os.path.join(root, "include"), "-isystem", sysconfig.get_paths()["include"], "-I", INCLUDE,
-            "-o", MARSHAL, MARSHAL_SRC, "-L", os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
+            "-o", MARSHAL_SAN if sanitize else MARSHAL, MARSHAL_SRC, "-L", os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
 
 
-def build_marshal(force: bool = True) -> str:
+def build_marshal(force: bool = True, sanitize: bool = False) -> str:
     """force=False: only if it is missing or older than what it is made from (it calls the library's entry points by
     their addresses, with the signatures of the header that it was compiled with)."""
-    old = not os.path.exists(MARSHAL) or os.path.getmtime(MARSHAL) < max(os.path.getmtime(f) for f in MARSHAL_USES)
+    module = MARSHAL_SAN if sanitize else MARSHAL
+    old = not os.path.exists(module) or os.path.getmtime(module) < max(os.path.getmtime(f) for f in MARSHAL_USES)
     if force or old:
-        res = subprocess.run(marshal_command(), capture_output=True, text=True)
+        cmd = marshal_command(sanitize)
+        res = subprocess.run(cmd, capture_output=True, text=True)
         if res.returncode != 0:
-            raise RuntimeError("g++ failed:\n" + res.stderr)
-    return MARSHAL
+            raise RuntimeError(cmd[0] + " failed:\n" + res.stderr)
+    return module
 
 
 def build(force: bool = True, verbose: bool = False, sanitize: bool = False) -> str:
     """sanitize=True: a second library whose HOST code runs under the address and
-    undefined-behaviour sanitizers (device code unchanged); the loading process must have
-    clang's shared sanitizer runtime preloaded."""
+    undefined-behaviour sanitizers (device code unchanged), and a second module that does; the loading
+    process must have clang's shared sanitizer runtime preloaded."""
     lib = LIB_SAN if sanitize else LIB
     if force or not os.path.exists(lib):
         build_library(lib, verbose, sanitize)
-    build_marshal(force and not sanitize)
+    build_marshal(force, sanitize)
     return lib
 
 

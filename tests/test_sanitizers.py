@@ -1,8 +1,8 @@
 """The CPU checker and the host side of the C-ABI library under the address and
 undefined-behaviour sanitizers (no GPU): the checker's pins and the library's host checks
-(plan arithmetic, argument validation, byte queries, placement in a fusion buffer) run in a
-child process that has clang's sanitizer runtime preloaded and loads the sanitized builds
-of both libraries.  Any report ends the child with a non-zero status."""
+(plan arithmetic, argument validation, byte queries, placement in a fusion buffer) and the refusals
+of the binding's marshalling run in a child process that has clang's sanitizer runtime preloaded and loads the
+sanitized builds of all three.  Any report ends the child with a non-zero status."""
 import os
 import subprocess
 import sys
@@ -12,7 +12,7 @@ import pytest
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 SUITES = ["tests/test_oracle_pins.py", "tests/test_epilogue_oracle.py", "tests/test_accumulate_oracle.py",
-          "tests/test_abi_and_host_logic.py"]
+          "tests/test_abi_and_host_logic.py", "tests/test_marshal.py"]
 
 
 @pytest.mark.timeout(900)
