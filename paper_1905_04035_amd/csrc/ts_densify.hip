@@ -628,6 +628,46 @@ __device__ __forceinline__ void count_ids(uint32_t* tab, uint32_t rel, int ll, i
     if (rel != rl && rel != 0xFFFFFFFFu) atomicAdd(&tab[tab_word<WIDE>(rel)], 1u << tab_shift<WIDE>(rel));
 }
 
+// The numbers that 64 list entries take from a table of their wavefront (what the table holds for an id is the number of
+// its next pair; a lane without an entry passes rel of an id of the part and own = false).  The entries of the first one's id
+// take theirs together (a hot id would be 64 LDS atomics on one address, one after the other: of 51200 pairs, 14 % on
+// one id, its work-group ended 2 us later), the others with one LDS atomic each.  Entries of one id take theirs in no order
+// that could be relied on, so what the table holds afterwards is read back: an id is among the 64 several times if and
+// only if one of its entries finds more there than its own number and one.  The entries of such ids, and only those, are
+// numbered again, by lane.
+template <bool WIDE>
+__device__ __forceinline__ uint32_t number_entries(uint32_t* tab, uint32_t rel, bool own, int lane)
+{
+    uint32_t* const word = tab + tab_word<WIDE>(rel);
+    const uint32_t shift = tab_shift<WIDE>(rel);
+    const uint32_t relx = own ? rel : 0xFFFFFFFFu;
+    const uint32_t rel0 = bcast(relx, 0);
+    const uint64_t sm0 = ballot64(relx == rel0);
+    // (no short circuits: they become branches, which cost a call with a dominating id half a per cent)
+    const bool first = lane == 0;
+    const bool takes = first | (own & (rel != rel0));
+    const uint32_t add = first ? (uint32_t)__popcll(sm0) : 1u;
+    uint32_t number = 0, after = 1;
+    if (takes) {
+        number = tab_get<WIDE>(__hip_atomic_fetch_add(word, add << shift, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP), shift);
+        // every lane's addition comes before any lane's look (no instruction: LDS operations of a wavefront are carried
+        // out in order, this keeps the compiler from another one)
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        after = tab_get<WIDE>(__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP), shift);
+    }
+    const uint32_t number0 = bcast(number, 0);
+    uint64_t m = ballot64(after != number + 1u) & ~sm0;
+    if (relx == rel0) number = number0 + lanes_below(sm0);
+    while (m) {
+        const uint32_t rl = bcast(rel, (int)__builtin_ctzll(m));
+        const uint64_t sm = ballot64(relx == rl);
+        if (relx == rl) number = after - (uint32_t)__popcll(sm) + lanes_below(sm);
+        m &= ~sm;
+    }
+    return number;
+}
+
 // The counting launch of a sort that takes several slices: work-group (g, s) counts the pairs of
 // slice s per id of part g (p.tot: 16 bits each, WIDE 32), those with a valid id below the part (p.below) and
 // those with an id outside the vocabulary (p.bad).  One LDS table for the whole work-group: the order
@@ -927,40 +967,16 @@ __global__ __launch_bounds__(1024) void sort_kernel(SortParams p, ShardTable sh)
     }
 
     // pass 2: every owned pair takes the next position of its id.  The list keeps the pairs in
-    // input order and wavefronts own consecutive sub-slices, so the sort is stable.  64 list entries at a time
-    // take numbers from the table, those of the first entry's id together (a hot id would be 64 LDS atomics on one
-    // address, one after the other: of 51200 pairs, 14 % on one id, its work-group ended 2 us later), the others with one
-    // LDS atomic each.  Entries of one id take theirs in no order that could be relied on, so what the table holds afterwards is
-    // read back: an id is among the 64 several times if and only if one of its entries finds more there than
-    // its own number and one.  The entries of such ids, and only those, are numbered again, by lane.
+    // input order and wavefronts own consecutive sub-slices, so the sort is stable.
     auto rank_listed = [&]() {
         for (uint32_t e0 = 0; e0 < nown; e0 += 64) {
             const bool own = e0 + lane < nown;
             const uint32_t ent = own ? list[e0 + lane] : 0u;
             const uint32_t rel = ent >> kListPosBits;       // (a lane without an entry looks where id 0 of the part stands)
             const int idx = a + (int)(ent & ((1u << kListPosBits) - 1u));
-            uint32_t* const word = mycnt + tab_word<WIDE>(rel);
-            const uint32_t shift = tab_shift<WIDE>(rel);
             const u2 info = id_info[rel];
             const uint32_t pos = MODE == SORT_SCATTER ? id_pos[rel] : info.y;
-            const uint32_t relx = own ? rel : 0xFFFFFFFFu;
-            const uint32_t rel0 = bcast(relx, 0);
-            const uint64_t sm0 = ballot64(relx == rel0);
-            uint32_t number = 0, after = 1;
-            if (lane == 0 || (own && rel != rel0)) {
-                const uint32_t add = lane == 0 ? (uint32_t)__popcll(sm0) : 1u;
-                number = tab_get<WIDE>(__hip_atomic_fetch_add(word, add << shift, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP), shift);
-                after = tab_get<WIDE>(__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP), shift);
-            }
-            const uint32_t number0 = bcast(number, 0);
-            uint64_t m = ballot64(after != number + 1u) & ~sm0;
-            if (relx == rel0) number = number0 + lanes_below(sm0);
-            while (m) {
-                const uint32_t rl = bcast(rel, (int)__builtin_ctzll(m));
-                const uint64_t sm = ballot64(relx == rl);
-                if (relx == rl) number = after - (uint32_t)__popcll(sm) + lanes_below(sm);
-                m &= ~sm;
-            }
+            const uint32_t number = number_entries<WIDE>(mycnt, rel, own, lane);
             const uint64_t rows = v.j0 == v.j1 ? v.rows0 : shard_base(v, v.rows0, v.rows_l, idx);
             if (own) {
                 const uint64_t row_addr = rows + (uint64_t)(uint32_t)idx * (uint64_t)(uint32_t)p.row_bytes;
@@ -1850,27 +1866,8 @@ __global__ __launch_bounds__(64 * kSmallWaves) void small_kernel(SmallParams p, 
         const uint32_t ent = own ? list[e0 + lane] : 0u;
         const uint32_t rel = ent >> kListPosBits;
         const int idx = a + (int)(ent & ((1u << kListPosBits) - 1u));
-        uint32_t* const word = mycnt + tab_word<false>(rel);
-        const uint32_t shift = tab_shift<false>(rel);
         const u2 info = id_info[rel];
-        const uint32_t relx = own ? rel : 0xFFFFFFFFu;
-        const uint32_t rel0 = bcast(relx, 0);
-        const uint64_t sm0 = ballot64(relx == rel0);
-        uint32_t number = 0, after = 1;
-        if (lane == 0 || (own && rel != rel0)) {
-            const uint32_t add = lane == 0 ? (uint32_t)__popcll(sm0) : 1u;
-            number = tab_get<false>(__hip_atomic_fetch_add(word, add << shift, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP), shift);
-            after = tab_get<false>(__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP), shift);
-        }
-        const uint32_t number0 = bcast(number, 0);
-        uint64_t m = ballot64(after != number + 1u) & ~sm0;
-        if (relx == rel0) number = number0 + lanes_below(sm0);
-        while (m) {
-            const uint32_t rl = bcast(rel, (int)__builtin_ctzll(m));
-            const uint64_t sm = ballot64(relx == rl);
-            if (relx == rl) number = after - (uint32_t)__popcll(sm) + lanes_below(sm);
-            m &= ~sm;
-        }
+        const uint32_t number = number_entries<false>(mycnt, rel, own, lane);
         const uint64_t rows = v.j0 == v.j1 ? v.rows0 : shard_base(v, v.rows0, v.rows_l, idx);
         if (own) {
             const uint64_t addr = rows + (uint64_t)(uint32_t)idx * (uint64_t)(uint32_t)p.row_bytes;
