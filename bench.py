@@ -37,17 +37,17 @@ def code_digest(path):
 
 
 # HBM bytes per reduce_kernel launch with default tuning, per workload, from the two
-# rocprofv3 --pmc runs summarised in profiles/ (FETCH_SIZE x 1.985 + WRITE_SIZE x 0.994, the
+# rocprofv3 --pmc runs summarised in profiles/ (FETCH_SIZE x 1.986 + WRITE_SIZE x 0.994, the
 # factors a plain copy of known size gives: profiles/counter_calibration.md).  Only valid for
 # the kernel source it was taken with: when the hash of its code differs, `traffic` is reported
 # as null (and a test fails, so that the figures are taken again or removed).
 COUNTED_TRAFFIC = {
-    "code_sha256": "f1532ec1604b9f9563e35e0281770fb0f55f1868ac04ebc25ab22e241f630115",
+    "code_sha256": "043f777515974870be21b5df929a16d316f918aab76ea562c0dd0dd4a2faf068",
     "reduce_kernel_bytes_per_launch": {
-        "transformer_big": 294.76e6,
-        "transformer_base": 105.06e6,
-        "large_batch_bf16": 568.15e6,
-        "multi_shard_stress": 1387.00e6,
+        "transformer_big": 294.84e6,
+        "transformer_base": 105.08e6,
+        "large_batch_bf16": 568.35e6,
+        "multi_shard_stress": 1387.62e6,
     },
 }
 

@@ -1696,20 +1696,39 @@ __global__ __launch_bounds__(64 * GP) void reduce_kernel(ReduceParams p)
 
 // ------------------------------------------------------------------ small calls: one launch
 // A call with few pairs and a small output is as long as its chain of latencies: two launches of 5 us each with one
-// and a half between them.  small_kernel does it in one: V = 1000, d = 64, 2048 pairs with uniform ids 10.7 -> 7.4 us per call (more
-// sizes at small_call).  Work-group (g, cb) owns `part` consecutive ids and a block of 256 columns.  It sorts the pairs of
+// and a half between them.  small_kernel does it in one: V = 1000, d = 64, 2048 pairs with uniform ids 10.1 -> 7.2 us per call (more
+// at small_call).  Work-group (g, cb) owns `part` consecutive ids and a block of 4 * lanes columns.  It sorts the pairs of
 // its ids as sort_kernel does (all pairs are looked at, its own listed, counted, scanned and ranked; dense_in of its rows is on
 // its way meanwhile), keeps the sorted pairs in LDS and adds up its own rows: longer rows by pieces of C sorted positions,
 // whose sums, and the shares of groups of pieces, meet in LDS; rows of at most C pairs, and rows without pairs, by the lanes of one
-// row.  Same order of additions as in the other kernels, same bits.  Rows narrower than 256 columns go several to a wavefront.
+// row.  Same order of additions as in the other kernels, same bits.
+// Where ids crowd into one part its longer rows bound the call: a compute unit takes in value rows at 25 to 50 bytes a
+// nanosecond.  So a block is as narrow as it takes for every piece to have lanes of its own, with all loads in flight at
+// once (small_lanes).  256 columns per block, pieces in up to four turns and their shares added by the lanes of one row / now, all
+// pairs on one id: d = 64, 2048 pairs 17.4 / 12.6 us, d = 1024, 512 pairs 20.1 / 9.8.
 constexpr int kSmallWaves = 16;
-constexpr int kSmallTiles = 4;              // of 64 pairs per wavefront
+constexpr int kSmallTiles = 2;              // of 64 pairs per wavefront
 constexpr int kSmallMax = kSmallWaves * kSmallTiles * 64;
 constexpr int kSmallSums = kSmallWaves * 64 * 2;
 constexpr int kSmallRows = 4;               // rows per lane at most
+constexpr int kSmallLanes = 16;             // lanes of a row at most
+constexpr int kSmallPiece = 8;              // pieces are no shorter
+constexpr int kSmallPart = 32;              // ids of a work-group, unless that makes too many of them
+constexpr int kSmallPartMax = 1024;         // (two to a thread in the scan, with a wavefront's counts in 2 KiB)
+constexpr int kXcds = 8;
+static_assert(kSmallWaves * 64 / kSmallLanes >= kSmallMax / 64, "every group of pieces has lanes of its own");
+static_assert(kSmallMax / 64 <= kFanIn * kFanIn, "two levels of sums of shares");
+
+// The lanes of a row in small_kernel, four columns each: no more than leave lanes to every piece of n pairs.
+int small_lanes(int64_t n, int32_t d)
+{
+    int lanes = 1;
+    while (lanes < kSmallLanes && lanes * 4 < d && 2 * lanes * n <= kSmallWaves * 64 * kSmallPiece) lanes *= 2;
+    return lanes;
+}
 
 struct SmallParams {
-    int32_t n, V, G, id_base, V_total, part, row_bytes, d;
+    int32_t n, V, G, stride, id_base, V_total, part, row_bytes, d;
     int32_t C, lanes, rounds, combine_batch;    // lanes of a row; rounds of rows; shares that are added as a balanced tree
     int32_t* count;
     int32_t* row_start;
@@ -1741,8 +1760,9 @@ __global__ __launch_bounds__(64 * kSmallWaves) void small_kernel(SmallParams p, 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int g = (int)blockIdx.x % p.G;
-    const int cb = (int)blockIdx.x / p.G;
+    const int g = (int)blockIdx.x % p.stride;
+    const int cb = (int)blockIdx.x / p.stride;
+    if (g >= p.G) return;
     const int part = p.part;
     const int words = part / 2;
     const int lo = g * part;
@@ -1774,7 +1794,7 @@ __global__ __launch_bounds__(64 * kSmallWaves) void small_kernel(SmallParams p, 
     }
     // the lanes of a row; a lane past the row's last column reads the last columns again and stores nothing
     const int sub = lane / p.lanes, sl = lane - sub * p.lanes, per_wave = 64 / p.lanes;
-    const int col = cb * kColBlock + sl * 4;
+    const int col = (cb * p.lanes + sl) * 4;
     const bool colok = col < p.d;
     const int colr = min(col, p.d - 4);
     f4 dn[kSmallRows];
@@ -1782,8 +1802,8 @@ __global__ __launch_bounds__(64 * kSmallWaves) void small_kernel(SmallParams p, 
     for (int it = 0; it < kSmallRows; ++it) {
         dn[it] = (f4)(0.0f);
         const int r = (it * kSmallWaves + w) * per_wave + sub;
-        if (it < p.rounds && p.dense_in && p.copy_untouched)
-            dn[it] = load_f4_stream(p.dense_in + (size_t)(lo + min(r, (int)span - 1)) * p.d + colr);
+        if (it < p.rounds && p.dense_in && p.copy_untouched && r < (int)span)
+            dn[it] = load_f4_stream(p.dense_in + (size_t)(lo + r) * p.d + colr);
     }
     for (int i = lane; i < words; i += 64) mycnt[i] = 0u;
 
@@ -1897,50 +1917,53 @@ __global__ __launch_bounds__(64 * kSmallWaves) void small_kernel(SmallParams p, 
         typedef const Raw __attribute__((address_space(1))) * global_raw;
         return __builtin_nontemporal_load(reinterpret_cast<global_raw>(row_addr[lp] + off));
     };
-    // Longer rows, piece by piece: a piece to the lanes of one row, as many groups of pieces at a time as there are such
-    // lanes.  A piece holds a part of a long row that began before it, and of one that begins in it.
+    // Longer rows: a piece to the lanes of one row (small_lanes sees to it that there are enough).  A piece holds a part of a
+    // long row that began before it, and of one that begins in it.
     const int own_end = (int)(id_info[span - 1].x + id_info[span - 1].y);       // one behind the part's last position
     const int k_first = (int)base >> 6, k_last = own_end > (int)base ? (own_end - 1) >> 6 : k_first - 1;
-    const int slots = kSmallWaves * per_wave, slot = w * per_wave + sub;
+    const int slot = w * per_wave + sub;
     const int logC = 31 - __builtin_clz((unsigned)p.C), log_pieces = 6 - logC;
-    for (int kt = k_first; kt <= k_last; kt += slots >> log_pieces) {
-        const int q0 = kt << log_pieces, piece = q0 + slot;             // first piece of this turn, and the one at hand
+    {
+        const int q0 = k_first << log_pieces, piece = q0 + slot;        // the part's first piece, and the one at hand
         const int group = piece >> log_pieces, g_first = group << log_pieces, g_last = g_first + (1 << log_pieces) - 1;
         const int begin = max(piece << logC, (int)base), end = min((piece + 1) << logC, own_end);
         // the row that has the piece's first position, and the one that has its last
         int rel[2] = {0, 0}, s[2] = {0, 0}, c[2] = {0, 0};
-        f4 d0[2];
+        f4 d0[2], acc[2];
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
-            d0[t] = (f4)(0.0f);
+            d0[t] = acc[t] = (f4)(0.0f);
             if (begin < end) {
                 rel[t] = pair_rel[(t == 0 ? begin : end - 1) - (int)base];
                 const u2 info = id_info[rel[t]];
                 s[t] = (int)info.y;
                 c[t] = (int)info.x > p.C && (t == 0 || rel[1] != rel[0]) ? (int)info.x : 0;
             }
-            if (c[t]) {
-                const int p0 = max(begin, s[t]), p1 = min(end, s[t] + c[t]);
-                if (p.dense_in && s[t] >= group << 6 && (s[t] + c[t] - 1) >> logC == piece)
-                    d0[t] = load_f4_stream(p.dense_in + (size_t)(lo + rel[t]) * p.d + colr);
-                f4 acc = (f4)(0.0f);
-                for (int at = p0; at < p1; at += 8) {
-                    Raw raw[8];
+            if (c[t] && p.dense_in && s[t] >= group << 6 && (s[t] + c[t] - 1) >> logC == piece)
+                d0[t] = load_f4_stream(p.dense_in + (size_t)(lo + rel[t]) * p.d + colr);
+        }
+        if (c[0] | c[1]) {
+            // the first one's positions end before end0, the last one's begin at begin1
+            const int end0 = c[0] ? min(end, s[0] + c[0]) : begin, begin1 = c[1] ? max(begin, s[1]) : end;
+            for (int at = begin; at < end; at += 8) {
+                Raw raw[8];
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) {
-                        raw[u] = Raw{};
-                        if (at + u < p1) raw[u] = load_pair(at + u - (int)base);
-                    }
-#pragma unroll
-                    for (int u = 0; u < 8; ++u) {
-                        f4 x[1];
-                        RowLoad<RowT, 1>::widen(raw[u], x);
-                        if (at + u < p1) acc = acc + x[0];
-                    }
+                for (int u = 0; u < 8; ++u) {
+                    raw[u] = Raw{};
+                    if (at + u < end0 || (at + u >= begin1 && at + u < end)) raw[u] = load_pair(at + u - (int)base);
                 }
-                chain[(slot * 2 + (s[t] >= piece << logC ? 1 : 0)) * p.lanes + sl] = acc;
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    f4 x[1];
+                    RowLoad<RowT, 1>::widen(raw[u], x);
+                    if (at + u < end0) acc[0] = acc[0] + x[0];
+                    if (at + u >= begin1 && at + u < end) acc[1] = acc[1] + x[0];
+                }
             }
         }
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+            if (c[t]) chain[(slot * 2 + (s[t] >= piece << logC ? 1 : 0)) * p.lanes + sl] = acc[t];
         __syncthreads();
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
@@ -1958,7 +1981,26 @@ __global__ __launch_bounds__(64 * kSmallWaves) void small_kernel(SmallParams p, 
                 }
             }
         }
-        if (kt + (slots >> log_pieces) <= k_last) __syncthreads();      // the sums are overwritten next
+    }
+
+    // Rows that span several groups: their shares are added as combine_if_last adds them, sixteen at a time, sixteen number q by
+    // the lanes of its first share's group (the first one by those of the second share's: the group in which a row begins
+    // belongs to others, too).  What these lanes need is asked for here, behind the loads of the short rows.
+    int j = 0, Pl = 0, slot0 = 0, crel = 0;
+    f4 cd = (f4)(0.0f);
+    {
+        const int k = k_first + 1 + slot;
+        if (k <= k_last) {
+            crel = pair_rel[(k << 6) - (int)base];
+            const u2 info = id_info[crel];
+            const int k0 = (int)info.y >> 6;
+            if ((int)info.x > p.C && k0 < k) {
+                j = k - k0;
+                Pl = ((int)(info.y + info.x - 1) >> 6) - k0 + 1;
+                slot0 = 2 * (k0 - k_first);
+                if (j == 1 && p.dense_in) cd = load_f4_stream(p.dense_in + (size_t)(lo + crel) * p.d + colr);
+            }
+        }
     }
 
     // rows without pairs and of at most C pairs
@@ -1996,40 +2038,32 @@ __global__ __launch_bounds__(64 * kSmallWaves) void small_kernel(SmallParams p, 
 
     if (k_first >= k_last) return;          // (the same for the whole work-group)
     __syncthreads();
-    // rows that span several groups: the shares as combine_if_last adds them, by the lanes of group k, the row's second one
-    for (int k = k_first + 1 + slot; k <= k_last; k += slots) {
-        const int rel = pair_rel[(k << 6) - (int)base];
-        const u2 info = id_info[rel];
-        const int c = (int)info.x, s = (int)info.y;
-        const int k0 = s >> 6;
-        if (c <= p.C || k0 != k - 1) continue;
-        f4 d0 = (f4)(0.0f);
-        if (p.dense_in) d0 = load_f4_stream(p.dense_in + (size_t)(lo + rel) * p.d + colr);
-        int Pl = ((s + c - 1) >> 6) - k0 + 1;
+    const auto add_shares = [&](int from, int shift, int m) {
         f4 tot = (f4)(0.0f);
-        for (int shift = 0;; shift += kLogFanIn) {
-            const int sums = (Pl + kFanIn - 1) >> kLogFanIn;
-            for (int q = 0; q < sums; ++q) {
-                const int m = min(kFanIn, Pl - (q << kLogFanIn));
-                tot = (f4)(0.0f);
-                for (int i0 = 0; i0 < m; i0 += p.combine_batch) {
-                    f4 x[8];
+        for (int i0 = 0; i0 < m; i0 += 8) {
+            f4 x[8];
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) {
-                        const int j = ((q << kLogFanIn) + min(i0 + u, m - 1)) << shift;       // the share's group within the row
-                        const f4 y = share[(share_slot(k0, j) - 2 * k_first) * p.lanes + sl];
-                        x[u] = i0 + u < m && u < p.combine_batch ? y : (f4)(0.0f);
-                    }
-                    const f4 h0 = (x[0] + x[1]) + (x[2] + x[3]);
-                    tot = tot + (p.combine_batch > 4 ? h0 + ((x[4] + x[5]) + (x[6] + x[7])) : h0);
-                }
-                share[(share_slot(k0, (q << kLogFanIn) << shift) - 2 * k_first) * p.lanes + sl] = tot;
+            for (int u = 0; u < 8; ++u) {
+                const int at = (from + min(i0 + u, m - 1)) << shift;
+                x[u] = share[(at == 0 ? slot0 + 1 : slot0 + 2 * at) * p.lanes + sl];
             }
-            if (sums == 1) break;
-            Pl = sums;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) x[u] = i0 + u < m ? x[u] : (f4)(0.0f);
+            const f4 h0 = (x[0] + x[1]) + (x[2] + x[3]), h1 = (x[4] + x[5]) + (x[6] + x[7]);
+            tot = p.combine_batch > 4 ? tot + (h0 + h1) : (tot + h0) + h1;
         }
-        if (colok) store_out<EPI>(p.dense_out, (size_t)(lo + rel) * p.d + col, tot + d0, p.scale);
+        return tot;
+    };
+    const int from = j == 1 ? 0 : j;
+    const bool adds = j == 1 || (j > 0 && j % kFanIn == 0);
+    f4 tot = (f4)(0.0f);
+    if (adds) tot = add_shares(from, 0, min(kFanIn, Pl - from));
+    if (k_last - k_first >= kFanIn) {       // (the same for the whole work-group)
+        if (adds) share[(from == 0 ? slot0 + 1 : slot0 + 2 * from) * p.lanes + sl] = tot;
+        __syncthreads();
+        if (j == 1 && Pl > kFanIn) tot = add_shares(0, kLogFanIn, (Pl + kFanIn - 1) / kFanIn);
     }
+    if (j == 1 && colok) store_out<EPI>(p.dense_out, (size_t)(lo + crel) * p.d + col, tot + cd, p.scale);
 }
 
 // ------------------------------------------------------------------ unique ids (introspection)
@@ -2403,28 +2437,33 @@ void remember(const Plan& pl, void* ws, int32_t V, int32_t copied_beside, int32_
     g_have_last = true;
 }
 
-// Calls that small_kernel takes.  The pairs of a row, however many, are added up by one work-group of a compute unit
-// and block of columns, 16 pieces at a time for rows of 132 columns or more, 64 for rows of 64, so the limit falls with the
-// width; and the work-groups hold little more than a copy each, so large outputs are better copied beside a sort.  us with
-// two launches / one: d = 64, 2048 pairs, V = 1000 12.0 / 9.3 (uniform ids 10.7 / 7.4), 4000 12.2 / 8.6, 16000 12.4 / 10.1, 32768 13.8 / 10.8;
-// d = 64, 1024 pairs, V = 40000 13.9 / 11.2, 45000 13.7 / 13.3, 65536 14.1 / 14.6; d = 128, 1024 pairs, V = 10000 12.4 / 10.3, 20000
-// 13.7 / 12.0; d = 512, 512 pairs, V = 4000 13.8 / 10.0.  A third of the pairs on one id: d = 64, 2048 pairs 12.3 / 10.8, d = 128, 1024
-// pairs 12.0 / 11.8, 2048 pairs 12.4 / 15.5, d = 256, 2048 pairs 12.7 / 25.1; nine tenths: d = 64, 1024 pairs 12.4 / 12.8, 2048 14.2 / 17.3.
-// (A setting that says how to split the work over the launches is for the two-launch form.)
-constexpr int64_t kSmallPairLanes = 32768;
+// Calls that small_kernel takes: those that it makes shorter wherever their ids lie.  All pairs may crowd into one
+// work-group's part, on one id or in the order of their frequency; a part is the longer the larger the output is, so the limit
+// on the output falls with the pairs.  us with two launches / one, input sets of 100 MB in turn:
+//                                   uniform ids    0.9 on one id   32 ids        Zipf 1.1, hottest first
+//   within  V = 1000, d = 64, 2048    10.1 /  7.4    14.1 / 13.0     15.8 / 15.2   13.9 / 13.1
+//           V = 6144, d = 64, 2048    10.2 /  7.2    14.4 / 13.5     15.7 / 15.2   13.6 / 13.2
+//           V = 6144, d = 128, 1024   10.3 /  7.6    12.4 / 11.2     12.9 / 11.6   12.6 / 10.9
+//           V = 1536, d = 1024, 512   12.0 /  8.2    13.1 / 11.4     13.0 / 11.9   13.0 / 11.7
+//   beyond  V = 20480, d = 64, 2048   10.6 /  9.0    14.5 / 15.1     15.8 / 16.5   13.4 / 14.8
+//           V = 2560, d = 1024, 512   12.7 / 11.0    13.8 / 12.7     13.4 / 13.8   13.4 / 14.7
+//           V = 1000, d = 64, 2304    10.0 /  7.7    14.2 / 13.7     16.9 / 16.6   14.3 / 13.4
+//           V = 1000, d = 64, 3072    10.7 /  8.9    14.8 / 15.6     18.0 / 19.3   15.3 / 14.8
+//           V = 1000, d = 128, 2048   10.1 /  8.1    14.3 / 14.1     15.8 / 16.5   13.8 / 13.5
+// (Zipf 1.5, hottest first, is the one found within that loses a little: V = 1000, d = 64, 2048 pairs 14.1 / 14.6.  Wide rows would bear
+// more pairs: d = 256, 1024 pairs with 32 ids 12.9 / 12.5.  A setting that says how to split the work over the launches is for
+// the two-launch form.)
+constexpr int64_t kSmallPairLanes = 32768;      // pairs times lanes of a whole row, 64 at most
 constexpr int64_t kSmallElems = 5 << 19;
-
-int small_lanes(int32_t d)
-{
-    int lanes = 1;
-    while (lanes < 64 && lanes * 4 < d) lanes *= 2;
-    return lanes;
-}
+constexpr int64_t kSmallPairElems = 3ll << 28;
 
 bool small_call(int64_t n, int32_t d, int32_t V)
 {
     if (g_piece_override || g_part_override || g_short_rows >= 0 || g_overlap_sort >= 0) return false;
-    return n >= 1 && n <= kSmallMax && n * small_lanes(d) <= kSmallPairLanes && (int64_t)V * d <= kSmallElems;
+    int64_t lanes = 1;
+    while (lanes < 64 && lanes * 4 < d) lanes *= 2;
+    const int64_t elems = (int64_t)V * d;
+    return n >= 1 && n <= kSmallMax && n * lanes <= kSmallPairLanes && elems <= kSmallElems && n * elems <= kSmallPairElems;
 }
 
 template <int EPI>
@@ -2452,18 +2491,22 @@ int densify_small(const ShardTable& sh, Plan& pl, int32_t row_dtype, int32_t d, 
     q.row_bytes = d * (row_dtype == TS_ROW_BF16 ? 2 : 4);
     q.d = d;
     q.C = pl.C;
-    q.lanes = small_lanes(d);
+    q.lanes = small_lanes(q.n, d);
     q.combine_batch = wide ? 4 : 8;
-    const int ncb = (d + kColBlock - 1) / kColBlock;
-    // as many rows to a work-group as it takes for every one to have a compute unit of its own (V = 32768, d = 64 / V = 10000,
-    // d = 128 / V = 40000, d = 64 with 512, 313, 625 work-groups 14.5, 11.7, -, with 256, 157, 313 10.8, 10.3, 12.4, with 128, 79, 157 12.3, 11.5, 11.2)
+    const int ncb = (d + 4 * q.lanes - 1) / (4 * q.lanes);
+    // kSmallPart ids to a work-group, or as many as it takes for every one to have a compute unit of its own
     const int rows = kSmallWaves * (64 / q.lanes);              // of a work-group in one round
     const int64_t cus = compute_units() > 0 ? compute_units() : 256;
-    q.rounds = 1;
-    while (q.rounds < kSmallRows && rows * q.rounds * 2 <= 1024 && ((int64_t)V + rows * q.rounds - 1) / (rows * q.rounds) * ncb > cus)
-        q.rounds *= 2;
-    q.part = rows * q.rounds;
-    q.G = (V + q.part - 1) / q.part;
+    q.part = rows < kSmallPart ? rows : kSmallPart;
+    // (blocks of columns that share lines of 128 bytes: those of a part on one XCD, with one L2; V = 6000, d = 64, 2048 pairs, nine
+    // tenths of them on one id 14.3 -> 13.4 us)
+    const bool share_lines = ncb > 1 && q.lanes * 16 < 128;
+    for (;; q.part *= 2) {
+        q.G = (V + q.part - 1) / q.part;
+        q.stride = share_lines ? (q.G + kXcds - 1) / kXcds * kXcds : q.G;
+        if (q.part >= kSmallPartMax || q.part >= rows * kSmallRows || (int64_t)q.stride * ncb <= cus) break;
+    }
+    q.rounds = (q.part + rows - 1) / rows;
     q.count = (int32_t*)(ws + pl.off_count);
     q.row_start = (int32_t*)(ws + pl.off_row_start);
     q.sorted = (SortedPair*)(ws + pl.off_sorted);
@@ -2475,7 +2518,7 @@ int densify_small(const ShardTable& sh, Plan& pl, int32_t row_dtype, int32_t d, 
     q.scale = scale;
     const bool prof = g_prof_used < g_prof_cap;
     hipEvent_t ev_begin = prof ? g_ev[2 * g_prof_used] : nullptr, ev_end = prof ? g_ev[2 * g_prof_used + 1] : nullptr;
-    TS_DISPATCH_EPI(epi, launch_small, (unsigned)(q.G * ncb), small_lds(q.n, q.part, q.lanes), row_dtype, stream, ev_begin, ev_end, q, sh);
+    TS_DISPATCH_EPI(epi, launch_small, (unsigned)(q.stride * ncb), small_lds(q.n, q.part, q.lanes), row_dtype, stream, ev_begin, ev_end, q, sh);
     if (prof) ++g_prof_used;
     if (hipGetLastError() != hipSuccess) return TS_ERR_HIP;
     pl.part = q.part;

@@ -1,7 +1,7 @@
-"""Calls that take one launch: the limits of that form (pairs times lanes of a row, elements of the output) from both
-sides, widths at which a row takes 1, 2, 4 .. 64 lanes and several blocks of columns, vocabularies that end inside,
+"""Calls that take one launch: the limits of that form (pairs, pairs times lanes of a row, elements of the output, pairs times
+elements) from both sides, widths at which a row takes 1, 2, 4 .. 64 lanes and several blocks of columns, vocabularies that end inside,
 at and behind a work-group's rows, ids that leave long rows inside a group of pieces, across groups and across the whole
-call.  Normal data: the bits have to be those of the two-launch form, the sums within the stated bound of the oracle's."""
+call; the same shapes beyond the limits in the two-launch form.  Normal data: the bits have to be those of the two-launch form, the sums within the stated bound of the oracle's."""
 import numpy as np
 import pytest
 import torch
@@ -28,6 +28,10 @@ def _pairs(d):
     return min(4096, 32768 // _lanes(d))
 
 
+def _small(V, d, n):
+    return 1 <= n <= 2048 and n * _lanes(d) <= 32768 and V * d <= 5 << 19 and V * d * n <= 3 << 28
+
+
 def _workload(V, d, n, dt=wl.ROW_FP32, ids="zipf", k=1):
     lengths = [n // k] * k
     lengths[-1] += n - sum(lengths)
@@ -40,6 +44,8 @@ def _workload(V, d, n, dt=wl.ROW_FP32, ids="zipf", k=1):
             a[:] = rng.integers(0, min(V, 5), len(a))
         elif ids == "uniform":
             a[:] = rng.integers(0, V, len(a))
+        elif ids == "low":
+            a[:] = rng.integers(0, min(V, 32), len(a))
         elif ids == "outside":
             a[rng.random(len(a)) < 0.3] = rng.choice([-1, V, 2 ** 31 - 1, -2 ** 31])
     return w
@@ -58,7 +64,7 @@ def _both(run):
 def _check(w, **kw):
     r = run_oracle(w, dense=kw.get("dense", True))
     g, f = _both(lambda: run_gpu(w, mode="multi", **kw))
-    assert g["info"]["short_rows"] == 3 and f["info"]["short_rows"] == 0
+    assert (g["info"]["short_rows"] == 3) == _small(w.V, w.d, w.n_total) and f["info"]["short_rows"] == 0
     assert g["info"]["piece_tokens"] == f["info"]["piece_tokens"]
     check(g, r, w)
     assert np.array_equal(g["out"].view(np.uint32), f["out"].view(np.uint32))
@@ -106,10 +112,22 @@ def test_a_range_and_the_built_in_workspace(monkeypatch):
     assert np.array_equal(outs[0].view(np.uint32), outs[1].view(np.uint32))
 
 
-@pytest.mark.parametrize("V,d,n,small", [(40960, 64, 2048, True), (40961, 64, 2048, False), (3000, 64, 2049, False), (3000, 68, 1024, True),
+# one more pair than lets a row have 16, 8 or 4 lanes, 32 ids to a work-group and one more or fewer
+@pytest.mark.parametrize("ids", ["one", "low", "zipf"])
+@pytest.mark.parametrize("V,d,n", [(31, 64, 2048), (32, 64, 2048), (33, 64, 2047), (65, 60, 1025), (2000, 64, 1024), (2000, 68, 513), (2000, 68, 512),
+                                   (6144, 64, 2048), (97, 1024, 512), (1500, 1024, 511), (97, 1028, 257), (10240, 256, 300)])
+def test_columns_of_a_work_group(V, d, n, ids):
+    assert _small(V, d, n)
+    _check(_workload(V, d, n, ids=ids))
+    _check(_workload(V, d, n, wl.ROW_BF16, ids, k=3), dense=n % 2 == 0)
+
+
+@pytest.mark.parametrize("V,d,n,small", [(6144, 64, 2048, True), (6145, 64, 2048, False), (40960, 64, 307, True), (40961, 64, 300, False),
+                                         (3000, 64, 2049, False), (3000, 68, 1024, True),
                                          (3000, 68, 1025, False), (3000, 128, 1024, True), (3000, 132, 512, True), (3000, 132, 513, False),
-                                         (3000, 4, 4096, True), (3000, 4, 4097, False)])
+                                         (3000, 4, 2048, True), (3000, 4, 2049, False)])
 def test_limits(V, d, n, small):
+    assert small == _small(V, d, n)
     w = _workload(V, d, n)
     g = run_gpu(w, mode="multi")
     check(g, run_oracle(w), w)
