@@ -2235,8 +2235,7 @@ void make_plan(int64_t n, int32_t d, int32_t V, int32_t C, Plan* pl, bool bound 
         pl->SL = (int32_t)SL;
     }
     // ids per sort work-group: smaller parts shorten the sort (fewer owned pairs per
-    // work-group), but every sorting work-group holds half of a compute unit and slows the
-    // copy that runs beside it; about 64 work-groups per slice measured best
+    // work-group), but every sorting work-group holds a compute unit that could copy; about 64 work-groups per slice measured best
     // (with several slices every part looks at every slice, and that dominates: the largest
     // parts that still give every compute unit a work-group)
     int part = (pl->S > 1 && (int64_t)((V + kMaxPart - 1) / kMaxPart) * pl->S >= 256) ? kMaxPart : 1024;
@@ -2580,24 +2579,28 @@ int densify_impl(const ShardTable& sh, int64_t n, int32_t row_dtype, int32_t d, 
     // to be scaled, by the item that reads them; only the copy made before the pairs are
     // sorted must go, because the reduce kernel would read scaled values.
     const bool skip_untouched = in_place && epi == EPI_NONE;
-    // Rows copied by the sort launches: about as many bytes as HBM moves while a sort runs
-    // (measured defaults).  One slice: 32 MiB plus 1 MiB per 1024 pairs up to 16384 pairs, 1.25 MiB
-    // per 1024 pairs beyond (the wavefronts then walk their shares in several rounds).  With 2.5 MiB, as it
-    // used to be, too many rows were copied that receive pairs: V = 32768, d = 1024, 40000 pairs 86.5 us (now
-    // 84.9; 32 / 48 / 112 MiB 89.8 / 88.1 / 86.5), 51200 pairs 95.3 (94.3; 99.6 / 98.3 / 94.3); d = 512,
-    // 40000 pairs 51.5 (48.4; 52.2 / 49.9 / 51.5).  Where a wavefront's share of the pairs holds the begin of a
-    // shard, though, it looks up every id of the share in the shard table and the sort launch takes 2-10 us
-    // longer: 2.5 MiB there.  V = 32768, d = 1024, 2.5 / 1.25: 57000 pairs in 2 / 4 / 8 shards 101.9 / 106.3, 105.6 / 111.1,
-    // 109.3 / 114.9 us (in one 100.9 / 99.9), 40000 in 3 shards 85.3 / 88.7; 28000 in 4 of bf16 rows 64.2 / 66.0.  A sort
-    // of a few slices leaves compute units idle, and a smaller blind copy beside
-    // each of its two launches still pays (+4 % at 3-4 slices); a sort of many slices keeps the
-    // whole GPU busy by itself (a copying work-group beside every sorting one lengthens the sort
-    // by more than the copy is worth), and with that many pairs a large share of the rows
+    // Rows copied by the sort launches: about as many bytes as HBM moves while a sort runs.  One slice: 32 MiB plus 1 MiB
+    // per 1024 pairs up to 16384 pairs, 1.25 MiB per 1024 pairs beyond (the wavefronts then walk their shares in several
+    // rounds; 2.5 MiB copies too many rows that receive pairs: V = 32768, d = 1024, 40000 pairs 84.9 us with 1.25, 86.5 with
+    // 2.5, d = 512 48.4 and 51.5).  Where shards begin inside the shares of three or more wavefronts, these look their ids'
+    // shards up and the sort is longer: 2.5 MiB there.  V = 32768, d = 1024, even shards, us with 1.25 / 2.5: 57000 pairs in 2 / 3 /
+    // 4 / 8 shards 99.3 / 101.5, 99.9 / 101.4, 102.5 / 101.9, 105.6 / 101.7; d = 512, 40000 pairs in 2 / 3 / 8 47.1 / 50.2, 48.0 / 50.0,
+    // 53.1 / 52.3.  (Not for fewer pairs, beside which the copies are made one per compute unit, below: V = 60000, d = 512, 6000 pairs
+    // in 3 shards 43.8, with more 47.2; 16000 in 16 level.)
+    // A sort of a few slices leaves compute units idle, and a smaller blind copy beside each of its two launches still
+    // pays (+4 % at 3-4 slices); a sort of many slices keeps the whole GPU busy by itself (a copying work-group beside every
+    // sorting one lengthens the sort by more than the copy is worth), and with that many pairs a large share of the rows
     // copied blindly would be overwritten: no blind copy then.
-    bool cut_share = false;
-    for (int j = 1; j < sh.k; ++j) cut_share |= sh.off[j] < n && sh.off[j] % (pl.SL / kSortWaves) != 0;
+    int32_t cut_shares = 0;
+    for (int32_t j = 1, last = -1; n > 16384 && j < sh.k; ++j) {
+        const int32_t share = pl.SL / kSortWaves, at = sh.off[j];
+        if (at >= n || at % share == 0 || at / share == last) continue;
+        last = at / share;
+        ++cut_shares;
+    }
+    const bool cut = cut_shares >= 3;
     const int64_t budget_single = n <= 16384 ? (32ll << 20) + (n / 1024 << 20)
-                                             : (48ll << 20) + (n - 16384) / 1024 * ((cut_share ? 10ll : 5ll) << 18);
+                                             : (48ll << 20) + (n - 16384) / 1024 * ((cut ? 10ll : 5ll) << 18);
     const int64_t slices = (n + kSliceTokens - 1) / kSliceTokens;      // a range may have more, smaller ones
     const int64_t budget_multi = slices <= 4 ? (32ll << 20) : (slices <= 6 ? (16ll << 20) : 0);
     const int64_t budget = g_overlap_sort >= 0 ? g_overlap_sort
@@ -2612,19 +2615,16 @@ int densify_impl(const ShardTable& sh, int64_t n, int32_t row_dtype, int32_t d, 
     if (elem_bytes < 4 && n <= 22528 && g_overlap_sort < 0) elem_bytes = 4;
     const int64_t wg_elems = (int64_t)kBlindElems * kSortWaves;
     int64_t copy_wgs = in_place ? 0 : budget / (elem_bytes * wg_elems);
-    // A work-group of these launches holds a compute unit (1024 threads, most of the LDS).  Where the
-    // default budget comes to a little less than one work-group per compute unit in all, make it exactly
-    // one: fewer leave compute units idle, and a few more than one leave a second round of stragglers
-    // (measured on 256 compute units, d = 1024: 192 copying work-groups beside 64 sorting ones take
-    // 2048-12800 pairs 1-2 % faster than 136-178 do, and 208 cost 1.5 us more than 192 at 16384 pairs).  So it is made
-    // one where it comes to more, too, unless the sort is a long one or the copies read nothing: us with more / exactly one,
-    // V = 32768, 18500 pairs, d = 1024 64.1 / 62.0, d = 512 36.5 / 34.5, d = 256 27.6 / 26.2; V = 60000, 5000 pairs, d = 512 47.3 / 44.7,
-    // d = 256 28.6 / 25.9; 21000 pairs 32.0 / 31.2, 26000 pairs V = 131072 54.6 / 55.5; without a dense operand V = 60000, d = 512, 5000 pairs
-    // 24.1 / 27.0; 16000 pairs in 16 shards that begin inside shares, V = 57566, d = 512 51.8 / 53.3, V = 131072, d = 128 32.3 / 34.5.)
+    // A work-group of these launches holds a compute unit (1024 threads, most of the LDS).  Where the default budget comes
+    // to a little less than one work-group per compute unit in all, make it exactly one (fewer leave compute units idle:
+    // V = 32768, d = 1024, 2048-12800 pairs 1-2 %); where it comes to more, too (a few more leave a second round of
+    // stragglers), unless the sort is a long one or the copies read nothing.  us with more / exactly one: V = 32768, 18500 pairs, d = 1024
+    // 64.1 / 62.0, d = 256 27.6 / 26.2; V = 60000, d = 512, 5000 pairs 47.3 / 44.7, without a dense operand 24.1 / 27.0; V = 60000,
+    // d = 512, 21000 pairs 32.0 / 31.2; V = 131072, 26000 pairs 54.6 / 55.5.
     if (pl.S == 1 && g_overlap_sort < 0 && copy_wgs > 0) {
         const int64_t cus = compute_units();
         const int64_t all = pl.G + copy_wgs;
-        const bool long_sort = n > 22528 || cut_share || !dense_in;
+        const bool long_sort = n > 22528 || cut || !dense_in;
         if (cus > pl.G && 4 * all >= 3 * cus && (all < cus || !long_sort)) copy_wgs = cus - pl.G;
     }
     // Beside a sliced sort that leaves compute units idle: no more of them than that.  (More wait for the sort's, and the

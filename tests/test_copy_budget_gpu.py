@@ -1,5 +1,5 @@
-"""How many dense rows are copied beside a one-launch sort of more than 16384 pairs: more of them where a
-shard begins inside a wavefront's share of the pairs, which makes the sort longer.  Small integers:
+"""How many dense rows are copied beside a one-launch sort of more than 16384 pairs: more of them where shards begin
+inside the shares of three or more wavefronts, which makes the sort longer.  Small integers:
 every bit is fixed, whatever was copied."""
 import pytest
 import torch
@@ -25,9 +25,10 @@ def _rows_copied(V, d, lengths, dt=wl.ROW_FP32):
 def test_a_shard_that_begins_inside_a_share(dt):
     # 40000 pairs: shares of 2560; 48 MiB and 1.25 or 2.5 MiB per whole 1024 pairs beyond 16384, in work-groups of 256 KiB
     budget = lambda quarters: ((48 << 20) + 23 * (quarters << 18)) // (256 << 10) * 32
-    for lengths in ([40000], [25600, 14400], [2560, 0, 37440], [40000, 0]):
+    for lengths in ([40000], [25600, 14400], [2560, 0, 37440], [40000, 0], [20000, 20000], [25601, 14399], [13333, 13333, 13334], [39999, 1],
+                    [1, 0, 39999], [1, 1, 1, 1, 39996], [10000, 10000, 5600, 14400]):
         assert _rows_copied(32768, 1024, lengths, dt) == budget(5)
-    for lengths in ([20000, 20000], [25601, 14399], [13333, 13333, 13334], [39999, 1], [1, 0, 39999]):
+    for lengths in ([10000] * 4, [1, 2560, 2560, 34879], [13333, 13333, 1, 13332, 1], [5000] * 8):
         assert _rows_copied(32768, 1024, lengths, dt) == budget(10)
 
 
@@ -36,9 +37,9 @@ def test_a_shard_that_begins_inside_a_share(dt):
 def test_one_work_group_per_compute_unit_in_small_calls(V, d, n):
     cus = torch.cuda.get_device_properties(0).multi_processor_count
     G = -(-V // 512)
-    for lengths in ([n], [n // 2 + 1, n - n // 2 - 1]):         # the second begins inside a share
+    for lengths in ([n], [n // 2 + 1, n - n // 2 - 1], [n // 9] * 8 + [n - n // 9 * 8]):          # begin inside shares
         wgs = (32 + n // 1024) * 4
-        if 4 * (G + wgs) >= 3 * cus and (len(lengths) == 1 or G + wgs < cus):
+        if 4 * (G + wgs) >= 3 * cus:
             wgs = cus - G
         assert _rows_copied(V, d, lengths) == min(V, wgs * 32768 // d)
 
@@ -51,10 +52,11 @@ def test_one_work_group_per_compute_unit_instead_of_a_few_more(V, d, part, n):
     wgs = ((48 << 20) + (n - 16384) // 1024 * (5 << 18)) // (256 << 10)
     if G + wgs > cus and n <= 22528:
         wgs = cus - G
-    assert _rows_copied(V, d, [n]) == min(V, wgs * 32 * 1024 // d)
-    # a shard that begins inside a share: the copies that the longer sort has room for
+    for lengths in ([n], [n // 2 + 1, n - n // 2 - 1]):
+        assert _rows_copied(V, d, lengths) == min(V, wgs * 32 * 1024 // d)
+    # shards that begin inside three shares: the copies that the longer sort has room for
     wgs = ((48 << 20) + (n - 16384) // 1024 * (10 << 18)) // (256 << 10)
-    assert _rows_copied(V, d, [n // 2 + 1, n - n // 2 - 1]) == min(V, wgs * 32 * 1024 // d)
+    assert _rows_copied(V, d, [n // 4 + 1] * 3 + [n - 3 * (n // 4 + 1)]) == min(V, wgs * 32 * 1024 // d)
 
 
 @pytest.mark.parametrize("V,d,n", [(41900, 256, 65536), (32768, 512, 65536), (60000, 64, 58000), (60000, 64, 66000), (5000, 512, 60000)])
