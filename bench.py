@@ -37,17 +37,17 @@ def code_digest(path):
 
 
 # HBM bytes per reduce_kernel launch with default tuning, per workload, from the two
-# rocprofv3 --pmc runs summarised in profiles/ (FETCH_SIZE x 1.986 + WRITE_SIZE x 0.994, the
+# rocprofv3 --pmc runs summarised in profiles/ (FETCH_SIZE x 1.986 + WRITE_SIZE x 0.995, the
 # factors a plain copy of known size gives: profiles/counter_calibration.md).  Only valid for
 # the kernel source it was taken with: when the hash of its code differs, `traffic` is reported
 # as null (and a test fails, so that the figures are taken again or removed).
 COUNTED_TRAFFIC = {
-    "code_sha256": "8cfa765a43f819ceef8fe89b9e3aa0cac1468f2b914ff238079751b511181ba3",
+    "code_sha256": "86a5a69cf8c53c9980c19cc006afb5a698d36e988e05b93d993d319179496e25",
     "reduce_kernel_bytes_per_launch": {
-        "transformer_big": 294.84e6,
-        "transformer_base": 105.08e6,
-        "large_batch_bf16": 568.36e6,
-        "multi_shard_stress": 1387.61e6,
+        "transformer_big": 294.96e6,
+        "transformer_base": 105.13e6,
+        "large_batch_bf16": 568.51e6,
+        "multi_shard_stress": 1387.76e6,
     },
 }
 

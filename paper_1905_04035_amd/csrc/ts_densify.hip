@@ -572,6 +572,22 @@ constexpr int kLdsBytes = 160 * 1024;       // LDS of a compute unit, the most a
 constexpr int kListPosBits = 21;
 constexpr int kGroupTiles = 4;              // tiles that are listed between two looks at how full the list is (room)
 
+// (SPARSE: most tiles hold no owned pair)
+template <bool TALLY, bool SPARSE>
+__device__ __forceinline__ void list_tile(int32_t id, uint32_t pos, uint32_t first, uint32_t span, const Tally& t, uint32_t* list,
+                                          uint32_t& nown, uint32_t& tally)
+{
+    const uint32_t idg = (uint32_t)id;
+    const uint32_t rel = idg - first;
+    const bool own = rel < span;
+    const uint64_t m = ballot64(own);
+    if (TALLY) tally += idg - t.off < t.below ? 1u : 0u;
+    if (!SPARSE || m) {
+        if (own) list[lanes_below(m, nown)] = (rel << kListPosBits) | pos;
+        nown += (uint32_t)__popcll(m);
+    }
+}
+
 template <bool TALLY, typename Room>
 __device__ __forceinline__ void list_round(const int32_t (&idr)[kRoundTiles], int a0, int b, uint32_t pos0, int lane, uint32_t first,
                                            uint32_t span, const Tally& t, uint32_t* list, uint32_t& nown, uint32_t& tally, Room&& room)
@@ -582,17 +598,8 @@ __device__ __forceinline__ void list_round(const int32_t (&idr)[kRoundTiles], in
         if (a0 + v * 64 < b) {
             room();
 #pragma unroll
-            for (int u = v; u < v + kGroupTiles; ++u) {
-                const uint32_t idg = (uint32_t)idr[u];
-                const uint32_t rel = idg - first;
-                const bool own = rel < span;
-                const uint64_t m = ballot64(own);
-                if (TALLY) tally += idg - t.off < t.below ? 1u : 0u;
-                if (m) {
-                    if (own) list[lanes_below(m, nown)] = (rel << kListPosBits) | (pos_l + (uint32_t)(u * 64));
-                    nown += (uint32_t)__popcll(m);
-                }
-            }
+            for (int u = v; u < v + kGroupTiles; ++u)
+                list_tile<TALLY, true>(idr[u], pos_l + (uint32_t)(u * 64), first, span, t, list, nown, tally);
         }
     }
 }
@@ -626,6 +633,13 @@ __device__ __forceinline__ void count_ids(uint32_t* tab, uint32_t rel, int ll, i
     const uint64_t sm = ballot64(rel == rl);
     if (lane == ll) atomicAdd(&tab[tab_word<WIDE>(rl)], (uint32_t)__popcll(sm) << tab_shift<WIDE>(rl));
     if (rel != rl && rel != 0xFFFFFFFFu) atomicAdd(&tab[tab_word<WIDE>(rel)], 1u << tab_shift<WIDE>(rel));
+}
+
+template <bool WIDE>
+__device__ __forceinline__ void count_listed(uint32_t* tab, const uint32_t* list, uint32_t nown, int lane)
+{
+    for (uint32_t e0 = 0; e0 < nown; e0 += 64)
+        count_ids<WIDE>(tab, e0 + lane < nown ? list[e0 + lane] >> kListPosBits : 0xFFFFFFFFu, 0, lane);
 }
 
 // The numbers that 64 list entries take from a table of their wavefront (what the table holds for an id is the number of
@@ -666,6 +680,42 @@ __device__ __forceinline__ uint32_t number_entries(uint32_t* tab, uint32_t rel, 
         m &= ~sm;
     }
     return number;
+}
+
+// Every pair of a wavefront's list takes the next position of its id: put(position, address of the value row, id within the part,
+// index of the pair, the id's count and first position).  The list keeps the pairs in input order and wavefronts own consecutive
+// sub-slices (this one's begins at pair a), so the sort is stable.  id_pos: where the slice's pairs of an id begin (SLICES).
+template <bool WIDE, bool SLICES, typename Put>
+__device__ __forceinline__ void rank_listed(uint32_t* tab, const uint32_t* list, uint32_t nown, const u2* id_info, const uint32_t* id_pos,
+                                            const ShardView& v, int a, int row_bytes, int lane, Put&& put)
+{
+    for (uint32_t e0 = 0; e0 < nown; e0 += 64) {
+        const bool own = e0 + lane < nown;
+        const uint32_t ent = own ? list[e0 + lane] : 0u;
+        const uint32_t rel = ent >> kListPosBits;       // (a lane without an entry looks where id 0 of the part stands)
+        const int idx = a + (int)(ent & ((1u << kListPosBits) - 1u));
+        const u2 info = id_info[rel];
+        const uint32_t pos = SLICES ? id_pos[rel] : info.y;
+        const uint32_t number = number_entries<WIDE>(tab, rel, own, lane);
+        const uint64_t rows = v.j0 == v.j1 ? v.rows0 : shard_base(v, v.rows0, v.rows_l, idx);
+        if (own) put(pos + number, rows + (uint64_t)(uint32_t)idx * (uint64_t)(uint32_t)row_bytes, rel, idx, info);
+    }
+}
+
+__device__ __forceinline__ void write_record(SortedPair* at, uint64_t row_addr, uint32_t id, int idx, u2 info)
+{
+    u4* const rec = reinterpret_cast<u4*>(at);
+    u4 r0, r1;
+    r0.x = (uint32_t)row_addr;
+    r0.y = (uint32_t)(row_addr >> 32);
+    r0.z = id;
+    r0.w = (uint32_t)idx;
+    r1.x = info.x;
+    r1.y = info.y;
+    r1.z = 0u;
+    r1.w = 0u;
+    rec[0] = r0;
+    rec[1] = r1;
 }
 
 // The counting launch of a sort that takes several slices: work-group (g, s) counts the pairs of
@@ -824,16 +874,12 @@ __global__ __launch_bounds__(1024) void sort_kernel(SortParams p, ShardTable sh)
     const Tally t = tally_of(g, lo, p.id_base, p.V_total);
     uint32_t tally = 0, nown = 0;
     bool flushed = false;
-    auto count_listed = [&]() {
-        for (uint32_t e0 = 0; e0 < nown; e0 += 64)
-            count_ids<WIDE>(mycnt, e0 + lane < nown ? list[e0 + lane] >> kListPosBits : 0xFFFFFFFFu, 0, lane);
-    };
     auto pass1 = [&](int32_t (&ids)[kRoundTiles], int rd) {
         const int a0 = a + rd * kRoundPairs;
         mask_tail(ids, a0, b, lane);
         list_round<MODE == SORT_FUSED>(ids, a0, b, (uint32_t)(rd * kRoundPairs), lane, first, span, t, list, nown, tally, [&] {
             if (nown > p.list_full) {
-                count_listed();
+                count_listed<WIDE>(mycnt, list, nown, lane);
                 nown = 0;
                 flushed = true;
             }
@@ -855,7 +901,7 @@ __global__ __launch_bounds__(1024) void sort_kernel(SortParams p, ShardTable sh)
             pass1(idr, rd);
         }
     }
-    count_listed();
+    count_listed<WIDE>(mycnt, list, nown, lane);
     if (MODE == SORT_SCATTER) {
         if (tid < words) {
             uint32_t total[E], pre[E];
@@ -966,37 +1012,15 @@ __global__ __launch_bounds__(1024) void sort_kernel(SortParams p, ShardTable sh)
         __syncthreads();
     }
 
-    // pass 2: every owned pair takes the next position of its id.  The list keeps the pairs in
-    // input order and wavefronts own consecutive sub-slices, so the sort is stable.
-    auto rank_listed = [&]() {
-        for (uint32_t e0 = 0; e0 < nown; e0 += 64) {
-            const bool own = e0 + lane < nown;
-            const uint32_t ent = own ? list[e0 + lane] : 0u;
-            const uint32_t rel = ent >> kListPosBits;       // (a lane without an entry looks where id 0 of the part stands)
-            const int idx = a + (int)(ent & ((1u << kListPosBits) - 1u));
-            const u2 info = id_info[rel];
-            const uint32_t pos = MODE == SORT_SCATTER ? id_pos[rel] : info.y;
-            const uint32_t number = number_entries<WIDE>(mycnt, rel, own, lane);
-            const uint64_t rows = v.j0 == v.j1 ? v.rows0 : shard_base(v, v.rows0, v.rows_l, idx);
-            if (own) {
-                const uint64_t row_addr = rows + (uint64_t)(uint32_t)idx * (uint64_t)(uint32_t)p.row_bytes;
-                u4* rec = reinterpret_cast<u4*>(p.sorted + (pos + number));
-                u4 r0, r1;
-                r0.x = (uint32_t)row_addr;
-                r0.y = (uint32_t)(row_addr >> 32);
-                r0.z = (uint32_t)lo + rel;
-                r0.w = (uint32_t)idx;
-                r1.x = info.x;
-                r1.y = info.y;
-                r1.z = 0u;
-                r1.w = 0u;
-                rec[0] = r0;
-                rec[1] = r1;
-            }
-        }
+    // pass 2
+    const auto rank = [&] {
+        rank_listed<WIDE, MODE == SORT_SCATTER>(mycnt, list, nown, id_info, id_pos, v, a, p.row_bytes, lane,
+                                                [&](uint32_t pos, uint64_t row_addr, uint32_t rel, int idx, u2 info) {
+            write_record(p.sorted + pos, row_addr, (uint32_t)lo + rel, idx, info);
+        });
     };
     if (!flushed) {
-        rank_listed();
+        rank();
         return;
     }
     // the list did not hold all owned pairs: the sub-slice once more, round by round
@@ -1006,7 +1030,7 @@ __global__ __launch_bounds__(1024) void sort_kernel(SortParams p, ShardTable sh)
         mask_tail(idr, a0, b, lane);
         nown = 0;
         list_round<false>(idr, a0, b, (uint32_t)(rd * kRoundPairs), lane, first, span, t, list, nown, tally, [] {});
-        rank_listed();
+        rank();
     }
 }
 
@@ -1706,7 +1730,7 @@ __global__ __launch_bounds__(64 * GP) void reduce_kernel(ReduceParams p)
 // nanosecond.  So a block is as narrow as it takes for every piece to have lanes of its own, with all loads in flight at
 // once (small_lanes).  256 columns per block, pieces in up to four turns and their shares added by the lanes of one row / now, all
 // pairs on one id: d = 64, 2048 pairs 17.4 / 12.6 us, d = 1024, 512 pairs 20.1 / 9.8.
-constexpr int kSmallWaves = 16;
+constexpr int kSmallWaves = kSortWaves;
 constexpr int kSmallTiles = 2;              // of 64 pairs per wavefront
 constexpr int kSmallMax = kSmallWaves * kSmallTiles * 64;
 constexpr int kSmallSums = kSmallWaves * 64 * 2;
@@ -1811,24 +1835,18 @@ __global__ __launch_bounds__(64 * kSmallWaves) void small_kernel(SmallParams p, 
     uint32_t tally = 0, nown = 0;
 #pragma unroll
     for (int u = 0; u < kSmallTiles; ++u) {
-        if (a + u * 64 < b) {
-            const uint32_t idg = (uint32_t)(a + u * 64 + lane < b ? idr[u] : kNoId);
-            const uint32_t rel = idg - first;
-            const bool own = rel < span;
-            const uint64_t m = ballot64(own);
-            tally += idg - t.off < t.below ? 1u : 0u;
-            if (own) list[lanes_below(m, nown)] = (rel << kListPosBits) | (uint32_t)(u * 64 + lane);
-            nown += (uint32_t)__popcll(m);
-        }
+        if (a + u * 64 < b)
+            list_tile<true, false>(a + u * 64 + lane < b ? idr[u] : kNoId, (uint32_t)(u * 64 + lane), first, span, t, list, nown, tally);
     }
-    for (uint32_t e0 = 0; e0 < nown; e0 += 64)
-        count_ids<false>(mycnt, e0 + lane < nown ? list[e0 + lane] >> kListPosBits : 0xFFFFFFFFu, 0, lane);
+    count_listed<false>(mycnt, list, nown, lane);
     tally = wave_sum(tally);
     if (lane == 0) red[w] = tally;
     __syncthreads();
     const uint32_t all = wave_sum(lane < kSmallWaves ? red[lane] : 0u);
     const uint32_t base = g == 0 ? 0u : all;        // first sorted position of the part
     if (g == 0 && cb == 0 && tid == 0) *p.n_bad = (int32_t)((uint32_t)p.n - all);
+    // The scan of sort_kernel for one slice and two ids to a word, what the ranking waits for first (one function for both
+    // kernels: V = 1000, d = 64, 2048 pairs 6.60 -> 6.69 us, 80011 pairs averaged to bf16 79.8 -> 80.1).
     {
         const bool idt = tid < words;
         uint32_t c[kSmallWaves], sum = 0;
@@ -1880,36 +1898,12 @@ __global__ __launch_bounds__(64 * kSmallWaves) void small_kernel(SmallParams p, 
         }
         __syncthreads();
     }
-    // (as in sort_kernel)
-    for (uint32_t e0 = 0; e0 < nown; e0 += 64) {
-        const bool own = e0 + lane < nown;
-        const uint32_t ent = own ? list[e0 + lane] : 0u;
-        const uint32_t rel = ent >> kListPosBits;
-        const int idx = a + (int)(ent & ((1u << kListPosBits) - 1u));
-        const u2 info = id_info[rel];
-        const uint32_t number = number_entries<false>(mycnt, rel, own, lane);
-        const uint64_t rows = v.j0 == v.j1 ? v.rows0 : shard_base(v, v.rows0, v.rows_l, idx);
-        if (own) {
-            const uint64_t addr = rows + (uint64_t)(uint32_t)idx * (uint64_t)(uint32_t)p.row_bytes;
-            const uint32_t pos = info.y + number;
-            row_addr[pos - base] = addr;
-            pair_rel[pos - base] = (uint16_t)rel;
-            if (cb == 0) {
-                u4* rec = reinterpret_cast<u4*>(p.sorted + pos);
-                u4 r0, r1;
-                r0.x = (uint32_t)addr;
-                r0.y = (uint32_t)(addr >> 32);
-                r0.z = (uint32_t)lo + rel;
-                r0.w = (uint32_t)idx;
-                r1.x = info.x;
-                r1.y = info.y;
-                r1.z = 0u;
-                r1.w = 0u;
-                rec[0] = r0;
-                rec[1] = r1;
-            }
-        }
-    }
+    rank_listed<false, false>(mycnt, list, nown, id_info, nullptr, v, a, p.row_bytes, lane,
+                              [&](uint32_t pos, uint64_t addr, uint32_t rel, int idx, u2 info) {
+        row_addr[pos - base] = addr;
+        pair_rel[pos - base] = (uint16_t)rel;
+        if (cb == 0) write_record(p.sorted + pos, addr, (uint32_t)lo + rel, idx, info);
+    });
     __syncthreads();
 
     const uint32_t off = (uint32_t)colr * (uint32_t)sizeof(RowT);
