@@ -274,10 +274,13 @@ __device__ __forceinline__ void store_out(void* out, size_t idx, f4 v, float sca
 // A work-group of the sort launches copies the elements [e, e + 2048 * kSortWaves) that lie below e_end, from dense_in to
 // the output: the copies beside the sort take whole rows, one behind the other, so where a row ends does not matter
 // here.  All loads are issued before the first store.  At every step the work-group's wavefronts move 1 KiB each of one
-// stretch of 16 KiB.  (A wavefront that moves 8 KiB of its own takes longer: 192 such work-groups by themselves 50.3 MB in 10.3 us, now
-// in 9.6, 256 of them 67.1 MB in 12.6, now in 11.9; calls with V = 32768, d = 512, 8192 pairs 28.4 -> 27.7, d = 1024, 2048 pairs 46.3 ->
-// 45.6, 16384 pairs 58.4 -> 57.7; V = 100000, d = 256, 5000 pairs 36.9 -> 36.3; without a dense operand level.  Loads that are the same for every lane, with
-// the index clamped, cost 1.3 us at d = 1024 and 1.4 us at d = 512: beside the sort gentler copies are better.)
+// stretch of 16 KiB.  Bound by HBM.  us where every wavefront moves 8 KiB of its own / so:
+//   192 such work-groups by themselves, 50.3 MB        10.3 /  9.6
+//   256 of them, 67.1 MB                               12.6 / 11.9
+//   calls: V = 32768, d = 512, 8192 pairs              28.4 / 27.7      (without a dense operand level)
+//          V = 32768, d = 1024, 16384 pairs            58.4 / 57.7
+// The loads are conditional: the same loads for every lane with the index clamped take 1.3 us more at d = 1024 (they
+// disturb the sort beside them).
 constexpr int kBlindElems = 2048;
 constexpr int kSortWaves = 16;     // wavefronts per sort work-group
 
@@ -604,12 +607,15 @@ __device__ __forceinline__ void list_round(const int32_t (&idr)[kRoundTiles], in
     }
 }
 
-// Bound by its chain of latencies and, in the listing and in the work-groups that own the hottest ids, by its
-// instructions.  Launch (launches: counting + scattering) in us before / after the shard table is looked up by
-// lanes, the tables hold 16 bits, the lists a whole round, a round's ids are loaded while the one before is listed,
-// one tally is kept instead of two, and only ids that really meet in 64 list entries are ranked in a loop:
-// 16384 pairs, d = 1024, in place 9.5 / 8.2; 51200 pairs (95 MB of copies beside) 22.3 / 20.0; 80011 pairs in 8 shards of
-// several lengths 10.1 + 14.0 / 7.0 + 10.6; 131072 pairs 7.1 + 12.3 / 5.4 + 9.9; 262144 pairs, 38 % on one id, 8.5 + 22.8 / 7.6 + 17.5.
+// The sort is bound by its chain of latencies and, in the listing and in the work-groups that own the hottest ids, by its
+// instructions.  So the shard table is looked up by lanes, the tables hold 16 bits, the lists a whole round, a round's ids
+// are loaded while the one before is listed, one tally is kept instead of two, and only ids that really meet in 64 list
+// entries are ranked in a loop.  us of the launch (counting + scattering) before all of these / with them:
+//   16384 pairs, d = 1024, in place                     9.5        /  8.2
+//   51200 pairs, 95 MB of copies beside                22.3        / 20.0
+//   80011 pairs in 8 shards of several lengths  10.1 + 14.0        /  7.0 + 10.6
+//   131072 pairs                                 7.1 + 12.3        /  5.4 +  9.9
+//   262144 pairs, 38 % on one id                 8.5 + 22.8        /  7.6 + 17.5
 //
 // The tables of pairs per (wavefront, id) in LDS.  Two ids share a word as long as the pairs of a slice fit
 // 16 bits: half the LDS to clear and to scan, and a work-group of 2048 ids has room for lists that hold a
@@ -850,9 +856,12 @@ __global__ __launch_bounds__(1024) void sort_kernel(SortParams p, ShardTable sh)
 
     uint32_t base = 0, nbad = 0;            // first sorted position of the part; bad ids
     // Everything the counting launch has left, asked for here and looked at behind the listing, so that the latency runs
-    // beside it (V = 131072, d = 64, 200000 pairs 72.7 -> 67.9 us, V = 32768, 60000 pairs 27.8 -> 27.3, eight shards of 80011 pairs
-    // averaged to bf16 80.8 -> 80.2; with loads beyond the last slice as well, so that none is conditional, 69.5, 28.0 and 80.6).  Per slice (lane s2 speaks for slice s2, at most 64 slices): the pairs below the part and the
-    // bad ids.  Per id: its count in all slices and in the slices before this one, the first sixteen here.
+    // beside it.  Per slice (lane s2 speaks for slice s2, at most 64 slices): the pairs below the part and the bad ids.  Per
+    // id: its count in all slices and in the slices before this one, the first sixteen here; none beyond the last slice.
+    // us of the call looked at here / behind the listing / that, with the loads beyond the last slice:
+    //   V = 131072, d = 64, 200000 pairs                     72.7 / 67.9 / 69.5
+    //   V = 32768, d = 64, 60000 pairs                       27.8 / 27.3 / 28.0
+    //   80011 pairs in eight shards, averaged to bf16        80.8 / 80.2 / 80.6
     const size_t GW = (size_t)p.G * words;
     uint32_t bl = 0, bd = 0, tot[16];
     if (MODE == SORT_SCATTER) {
@@ -2092,7 +2101,7 @@ struct Plan {
     bool wide_tab;              // tables of the sort: a word per id
     uint32_t list_full;
     size_t sort_lds;
-    int32_t S, SL, G, part, list_cap, C, NB, NBG, levels, ncb;   // NB pieces in NBG groups   // ncb: 256-column blocks of a row; levels of the combine tree
+    int32_t S, SL, G, part, list_cap, C, NB, NBG, levels, ncb;   // NB pieces in NBG groups; levels of the combine tree; 256-column blocks of a row
     size_t off_nvalid, off_nbad, off_arrive, arrive_bytes, off_count, off_row_start, off_sorted, off_tot,
         off_below, off_bad, off_partial, total;
 };
