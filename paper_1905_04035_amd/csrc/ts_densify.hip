@@ -2588,8 +2588,10 @@ int densify_impl(const ShardTable& sh, int64_t n, int32_t row_dtype, int32_t d, 
     // 2.5, d = 512 48.4 and 51.5).  Where shards begin inside the shares of three or more wavefronts, these look their ids'
     // shards up and the sort is longer: 2.5 MiB there.  V = 32768, d = 1024, even shards, us with 1.25 / 2.5: 57000 pairs in 2 / 3 /
     // 4 / 8 shards 99.3 / 101.5, 99.9 / 101.4, 102.5 / 101.9, 105.6 / 101.7; d = 512, 40000 pairs in 2 / 3 / 8 47.1 / 50.2, 48.0 / 50.0,
-    // 53.1 / 52.3.  (Not for fewer pairs, beside which the copies are made one per compute unit, below: V = 60000, d = 512, 6000 pairs
-    // in 3 shards 43.8, with more 47.2; 16000 in 16 level.)
+    // 53.1 / 52.3.  Where the copies read nothing, any such shard counts: without a dense operand, in two shards, V = 68359, d = 1024,
+    // 49901 pairs 99.2 / 96.1, V = 118817, d = 512, 49917 pairs 65.1 / 63.1, V = 33232, d = 512, 43556 pairs level.  (Right in the mean
+    // only: 40219 pairs in two shards, V = 42517, d = 256 37.1 / 35.9.  Not for fewer pairs, beside which the copies are made one per
+    // compute unit, below: V = 60000, d = 512, 6000 pairs in 3 shards 43.8, with more 47.2; 16000 in 16 level.)
     // A sort of a few slices leaves compute units idle, and a smaller blind copy beside each of its two launches still
     // pays (+4 % at 3-4 slices); a sort of many slices keeps the whole GPU busy by itself (a copying work-group beside every
     // sorting one lengthens the sort by more than the copy is worth), and with that many pairs a large share of the rows
@@ -2601,7 +2603,7 @@ int densify_impl(const ShardTable& sh, int64_t n, int32_t row_dtype, int32_t d, 
         last = at / share;
         ++cut_shares;
     }
-    const bool cut = cut_shares >= 3;
+    const bool cut = cut_shares >= (dense_in ? 3 : 1);
     const int64_t budget_single = n <= 16384 ? (32ll << 20) + (n / 1024 << 20)
                                              : (48ll << 20) + (n - 16384) / 1024 * ((cut ? 10ll : 5ll) << 18);
     const int64_t slices = (n + kSliceTokens - 1) / kSliceTokens;      // a range may have more, smaller ones

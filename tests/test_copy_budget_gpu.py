@@ -1,5 +1,5 @@
 """How many dense rows are copied beside a one-launch sort of more than 16384 pairs: more of them where shards begin
-inside the shares of three or more wavefronts, which makes the sort longer.  Small integers:
+inside the shares of three or more wavefronts (of any, where the copies read nothing), which makes the sort longer.  Small integers:
 every bit is fixed, whatever was copied."""
 import pytest
 import torch
@@ -13,10 +13,10 @@ from test_epilogue_gpu import check_scaled
 pytestmark = pytest.mark.gpu
 
 
-def _rows_copied(V, d, lengths, dt=wl.ROW_FP32):
+def _rows_copied(V, d, lengths, dt=wl.ROW_FP32, dense=True):
     w = wl.make_custom(V=V, d=d, n_list=lengths, zipf_s=1.1, seed=V + d + len(lengths), row_dtype=dt, integer_values=True)
-    g = run_gpu(w, mode="multi")
-    check(g, run_oracle(w), w, exact_bits=True)
+    g = run_gpu(w, mode="multi", dense=dense)
+    check(g, run_oracle(w, dense=dense), w, exact_bits=True)
     assert g["info"]["sort_slices"] == 1
     return g["info"]["sort_copy_rows_end"]
 
@@ -30,6 +30,15 @@ def test_a_shard_that_begins_inside_a_share(dt):
         assert _rows_copied(32768, 1024, lengths, dt) == budget(5)
     for lengths in ([10000] * 4, [1, 2560, 2560, 34879], [13333, 13333, 1, 13332, 1], [5000] * 8):
         assert _rows_copied(32768, 1024, lengths, dt) == budget(10)
+
+
+def test_a_shard_that_begins_inside_a_share_without_a_dense_operand():
+    # as above in work-groups of 128 KiB
+    budget = lambda quarters: ((48 << 20) + 23 * (quarters << 18)) // (128 << 10) * 32
+    for lengths in ([40000], [25600, 14400], [40000, 0]):
+        assert _rows_copied(32768, 1024, lengths, dense=False) == budget(5)
+    for lengths in ([20000, 20000], [39999, 1], [13333, 13333, 13334], [5000] * 8):
+        assert _rows_copied(32768, 1024, lengths, dense=False) == budget(10)
 
 
 @pytest.mark.parametrize("V,d", [(60000, 64), (60000, 260), (45000, 128)])
