@@ -42,7 +42,7 @@ def code_digest(path):
 # the kernel source it was taken with: when the hash of its code differs, `traffic` is reported
 # as null (and a test fails, so that the figures are taken again or removed).
 COUNTED_TRAFFIC = {
-    "code_sha256": "7cdbef1a7a48f576157d6bce0aed689b4280ecef6ac988ac5329807a79bcf352",
+    "code_sha256": "6d6cd7f7520ac17346d1482a8787b5dd045f2dcad2b815ce5cb3a12a311bc641",
     "reduce_kernel_bytes_per_launch": {
         "transformer_big": 294.95e6,
         "transformer_base": 105.13e6,

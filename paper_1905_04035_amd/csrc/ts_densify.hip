@@ -2439,25 +2439,32 @@ void remember(const Plan& pl, void* ws, int32_t V, int32_t copied_beside, int32_
     g_have_last = true;
 }
 
-// Calls that small_kernel takes: those that it makes shorter wherever their ids lie.  All pairs may crowd into one
-// work-group's part, on one id or in the order of their frequency; a part is the longer the larger the output is, so the limit
-// on the output falls with the pairs.  us with two launches / one, input sets of 100 MB in turn:
-//                                   uniform ids    0.9 on one id   32 ids        Zipf 1.1, hottest first
-//   within  V = 1000, d = 64, 2048    10.1 /  7.4    14.1 / 13.0     15.8 / 15.2   13.9 / 13.1
-//           V = 6144, d = 64, 2048    10.2 /  7.2    14.4 / 13.5     15.7 / 15.2   13.6 / 13.2
-//           V = 6144, d = 128, 1024   10.3 /  7.6    12.4 / 11.2     12.9 / 11.6   12.6 / 10.9
-//           V = 1536, d = 1024, 512   12.0 /  8.2    13.1 / 11.4     13.0 / 11.9   13.0 / 11.7
-//   beyond  V = 20480, d = 64, 2048   10.6 /  9.0    14.5 / 15.1     15.8 / 16.5   13.4 / 14.8
-//           V = 2560, d = 1024, 512   12.7 / 11.0    13.8 / 12.7     13.4 / 13.8   13.4 / 14.7
-//           V = 1000, d = 64, 2304    10.0 /  7.7    14.2 / 13.7     16.9 / 16.6   14.3 / 13.4
-//           V = 1000, d = 64, 3072    10.7 /  8.9    14.8 / 15.6     18.0 / 19.3   15.3 / 14.8
-//           V = 1000, d = 128, 2048   10.1 /  8.1    14.3 / 14.1     15.8 / 16.5   13.8 / 13.5
-// (Zipf 1.5, hottest first, is the one found within that loses a little: V = 1000, d = 64, 2048 pairs 14.1 / 14.6.  Wide rows would bear
+// Calls that small_kernel takes: those that it makes shorter where ids are spread, and not longer, but for some that crowd at the
+// vocabulary's begin, than two launches.  All pairs may crowd into one work-group's part, on one id or in the order of their
+// frequency; a part is the longer the larger the output is, so the limit on the output falls with the pairs.  us with two
+// launches / one, input sets of 100 MB in turn:
+//                                   uniform ids    Zipf 1.1       0.9 on one id   32 ids        Zipf 1.1, hottest first
+//   within  V = 1000, d = 64, 2048    10.1 /  7.4                  14.1 / 13.0     15.8 / 15.2   13.9 / 13.1
+//           V = 6144, d = 64, 2048    10.2 /  7.2                  14.4 / 13.5     15.7 / 15.2   13.6 / 13.2
+//           V = 13312, d = 64, 2048   10.1 /  6.9    11.9 /  9.2   14.2 / 13.8     15.7 / 15.4   13.5 / 13.2
+//           V = 26000, d = 64, 1048   11.0 /  8.1    12.8 /  9.5   13.3 / 11.6     13.9 / 12.2   12.7 / 12.7
+//           V = 40960, d = 64, 660    11.3 /  9.1    12.8 /  9.7   13.3 / 11.4     12.6 / 11.2   12.4 / 13.0
+//           V = 13600, d = 128, 1000  11.1 /  8.1    12.6 /  9.5   13.1 / 11.8     13.0 / 11.8   12.6 / 11.8
+//           V = 8192, d = 256, 512    11.9 /  7.4    13.1 /  8.9   12.9 / 10.6     12.7 / 11.7   12.6 / 11.1
+//           V = 2048, d = 1024, 512   12.1 /  8.1    13.2 /  9.6   13.4 / 11.4     12.9 / 11.9   12.9 / 11.8
+//   beyond  V = 20480, d = 64, 2048   10.5 /  8.8    12.2 / 10.4   14.4 / 14.8     15.8 / 15.9   13.6 / 14.7
+//           V = 40960, d = 64, 2048   11.5 / 12.5    13.1 / 13.3   15.1 / 17.2     15.9 / 17.4   13.9 / 18.0
+//           V = 20480, d = 128, 1000  11.7 / 10.3    13.1 / 11.1   13.7 / 13.4     13.2 / 12.8   13.0 / 14.7
+//           V = 5120, d = 512, 512    12.2 /  9.8    13.6 / 10.7   13.6 / 12.4     13.0 / 13.0   12.8 / 13.9
+//           V = 1000, d = 64, 2304    10.0 /  7.7                  14.2 / 13.7     16.9 / 16.6   14.3 / 13.4
+//           V = 1000, d = 64, 3072    10.7 /  8.9                  14.8 / 15.6     18.0 / 19.3   15.3 / 14.8
+//           V = 1000, d = 128, 2048   10.1 /  8.1                  14.3 / 14.1     15.8 / 16.5   13.8 / 13.5
+// (Zipf 1.5, hottest first, is what loses most within: V = 13312, d = 64, 2048 pairs 14.2 / 14.9.  Wide rows would bear
 // more pairs: d = 256, 1024 pairs with 32 ids 12.9 / 12.5.  A setting that says how to split the work over the launches is for
 // the two-launch form.)
 constexpr int64_t kSmallPairLanes = 32768;      // pairs times lanes of a whole row, 64 at most
 constexpr int64_t kSmallElems = 5 << 19;
-constexpr int64_t kSmallPairElems = 3ll << 28;
+constexpr int64_t kSmallPairElems = 13ll << 27, kSmallPairElemsWide = 8ll << 27;      // (wide: rows of more than 32 lanes)
 
 bool small_call(int64_t n, int32_t d, int32_t V)
 {
@@ -2465,7 +2472,7 @@ bool small_call(int64_t n, int32_t d, int32_t V)
     int64_t lanes = 1;
     while (lanes < 64 && lanes * 4 < d) lanes *= 2;
     const int64_t elems = (int64_t)V * d;
-    return n >= 1 && n <= kSmallMax && n * lanes <= kSmallPairLanes && elems <= kSmallElems && n * elems <= kSmallPairElems;
+    return n >= 1 && n <= kSmallMax && n * lanes <= kSmallPairLanes && elems <= kSmallElems && n * elems <= (lanes <= 32 ? kSmallPairElems : kSmallPairElemsWide);
 }
 
 template <int EPI>

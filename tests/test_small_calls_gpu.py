@@ -29,7 +29,7 @@ def _pairs(d):
 
 
 def _small(V, d, n):
-    return 1 <= n <= 2048 and n * _lanes(d) <= 32768 and V * d <= 5 << 19 and V * d * n <= 3 << 28
+    return 1 <= n <= 2048 and n * _lanes(d) <= 32768 and V * d <= 5 << 19 and V * d * n <= (13 if d <= 128 else 8) << 27
 
 
 def _workload(V, d, n, dt=wl.ROW_FP32, ids="zipf", k=1):
@@ -115,14 +115,16 @@ def test_a_range_and_the_built_in_workspace(monkeypatch):
 # one more pair than lets a row have 16, 8 or 4 lanes, 32 ids to a work-group and one more or fewer
 @pytest.mark.parametrize("ids", ["one", "low", "zipf"])
 @pytest.mark.parametrize("V,d,n", [(31, 64, 2048), (32, 64, 2048), (33, 64, 2047), (65, 60, 1025), (2000, 64, 1024), (2000, 68, 513), (2000, 68, 512),
-                                   (6144, 64, 2048), (97, 1024, 512), (1500, 1024, 511), (97, 1028, 257), (10240, 256, 300)])
+                                   (6144, 64, 2048), (13312, 64, 2048), (26000, 64, 1048), (13600, 128, 1000), (2048, 1024, 512),
+                                   (97, 1024, 512), (1500, 1024, 511), (97, 1028, 257), (10240, 256, 300)])
 def test_columns_of_a_work_group(V, d, n, ids):
     assert _small(V, d, n)
     _check(_workload(V, d, n, ids=ids))
     _check(_workload(V, d, n, wl.ROW_BF16, ids, k=3), dense=n % 2 == 0)
 
 
-@pytest.mark.parametrize("V,d,n,small", [(6144, 64, 2048, True), (6145, 64, 2048, False), (40960, 64, 307, True), (40961, 64, 300, False),
+@pytest.mark.parametrize("V,d,n,small", [(13312, 64, 2048, True), (13313, 64, 2048, False), (40960, 64, 665, True), (40960, 64, 666, False),
+                                         (40961, 64, 300, False), (2048, 1024, 512, True), (2049, 1024, 512, False), (8192, 132, 512, True),
                                          (3000, 64, 2049, False), (3000, 68, 1024, True),
                                          (3000, 68, 1025, False), (3000, 128, 1024, True), (3000, 132, 512, True), (3000, 132, 513, False),
                                          (3000, 4, 2048, True), (3000, 4, 2049, False)])
